@@ -148,11 +148,10 @@ lmr_status enqueue_attempt(lmr_ctx* c, const void* F, const void* M, int force) 
     pd.dp = c->dp;
     pd.force = force;
     pd.next = c->st_next;
-    LMR_HIP(launch_bwd_decide(F, M, c->img, c->Mw, c->maps, c->g, c->p, c->st, c->U[0],
-                              c->U[1], c->graw, c->graw, pd, s));
+    LMR_HIP(launch_bwd_decide(F, c->img, c->Mw, c->maps, c->g, c->p, c->st, c->graw, c->graw,
+                              pd, s));
   } else if (sim == LMR_SIM_LNCC)
-    LMR_HIP(launch_bwd(F, M, c->img, c->Mw, c->maps, c->g, c->p, c->st, c->U[0], c->U[1],
-                       nullptr, c->graw, c->graw, s));
+    LMR_HIP(launch_bwd(F, c->img, c->Mw, c->maps, c->g, c->p, c->st, c->graw, c->graw, s));
   else if (sim == LMR_SIM_MSE)
     LMR_HIP(launch_mse_bwd(F, c->img, c->Mw, c->graw, c->g, c->st, nullptr, c->graw, s));
   else if (sim == LMR_SIM_MI)
@@ -341,7 +340,7 @@ lmr_status lmr_begin(lmr_ctx* c, const void* F, const void* M, const float* fiel
   if (sim == LMR_SIM_LNCC) {
     LMR_HIP(launch_fstat(F, c->img, c->g, c->p, c->fstat, s));
     c->fstat_of = F;
-    LMR_HIP(launch_warp(M, c->img, c->U[0], c->g, c->Mw, nullptr, s));
+    LMR_HIP(launch_warp(M, c->img, c->U[0], c->g, c->Mw, c->graw, s));
     LMR_HIP(launch_fwd(F, c->img, c->Mw, c->fstat, c->g, c->p, nullptr, c->maps,
                        c->partials, c->nparts, nullptr, s));
   } else if (sim == LMR_SIM_MI) {
@@ -359,8 +358,7 @@ lmr_status lmr_begin(lmr_ctx* c, const void* F, const void* M, const float* fiel
   LMR_HIP(launch_decide(c->st, c->partials, sim == LMR_SIM_MI ? 1 : c->nparts, c->g.N, c->dp,
                         1, -1, lambda0, nullptr, s));
   if (sim == LMR_SIM_LNCC) {
-    LMR_HIP(launch_bwd(F, M, c->img, c->Mw, c->maps, c->g, c->p, nullptr, nullptr,
-                       nullptr, c->U[0], nullptr, c->graw, s));
+    LMR_HIP(launch_bwd(F, c->img, c->Mw, c->maps, c->g, c->p, nullptr, c->graw, c->graw, s));
     LMR_HIP(launch_smooth(c->graw, c->g, c->p, nullptr, c->G, s));
   } else if (sim == LMR_SIM_MSE) {
     // the state holds r = sqrt(L) of the starting field
@@ -506,7 +504,7 @@ lmr_status lmr_loss_grad(lmr_ctx* c, const void* F, const void* M, const float* 
     // a stage call may pass any fixed image: its statistics are taken here
     LMR_HIP(launch_fstat(F, c->img, c->g, c->p, c->fstat, s));
     c->fstat_of = F;
-    LMR_HIP(launch_warp(M, c->img, u, c->g, c->Mw, nullptr, s));
+    LMR_HIP(launch_warp(M, c->img, u, c->g, c->Mw, g_raw || g_smooth ? c->graw : nullptr, s));
     LMR_HIP(launch_fwd(F, c->img, c->Mw, c->fstat, c->g, c->p, nullptr, c->maps,
                        c->partials, c->nparts, cc_map, s));
   } else if (c->p.similarity == LMR_SIM_MI) {
@@ -529,8 +527,7 @@ lmr_status lmr_loss_grad(lmr_ctx* c, const void* F, const void* M, const float* 
   if (g_raw || g_smooth) {
     float* gr = g_raw ? g_raw : c->graw;
     if (c->p.similarity == LMR_SIM_LNCC)
-      LMR_HIP(launch_bwd(F, M, c->img, c->Mw, c->maps, c->g, c->p, nullptr, nullptr,
-                         nullptr, u, nullptr, gr, s));
+      LMR_HIP(launch_bwd(F, c->img, c->Mw, c->maps, c->g, c->p, nullptr, c->graw, gr, s));
     else if (c->p.similarity == LMR_SIM_MI)
       LMR_HIP(launch_mi_bwd(F, c->img, c->Mw, c->graw, c->g, c->p.mi_bins, c->mi_map,
                             c->mi_tab, nullptr, gr, s));

@@ -20,8 +20,9 @@ constexpr long long kMaxParts = 1LL << 17;   // FP64 partials of the forward pas
 //   window mean and variance of F  FP64 [2][N]
 //   the four LNCC adjoint maps     FP32 [4][N]
 //   warped moving image            FP32 [N]
-//   raw gradient (when the caller  FP32 [3][N]
-//     asks only for the smoothed one)
+//   derivative of the warped       FP32 [3][N]
+//     image, then the raw gradient when the caller asks only for the
+//     smoothed one
 //   forward partials               FP64 [kMaxParts]
 //   pair state read by the decision kernel
 constexpr size_t kOffMaps = 16 * kMaxVoxels;
@@ -92,13 +93,13 @@ extern "C" lmr_status lmr_loss_grad_noalloc(const void* F, const void* M, lmr_dt
   const DecideParams dp{p->lambda_inc, p->lambda_dec, p->lambda_min, p->lambda_max, p->tau,
                         p->max_retries};
   LMR_HIP(launch_fstat(F, img, g, *p, fstat, stream));
-  LMR_HIP(launch_warp(M, img, u, g, Mw, nullptr, stream));
+  const bool grad = g_raw || g_smooth;
+  LMR_HIP(launch_warp(M, img, u, g, Mw, grad ? graw : nullptr, stream));
   LMR_HIP(launch_fwd(F, img, Mw, fstat, g, *p, nullptr, maps, parts, nparts, cc_map, stream));
   LMR_HIP(launch_decide(dst, parts, nparts, N, dp, 2, -1, 0.0, loss_dev, stream));
-  if (g_raw || g_smooth) {
+  if (grad) {
     float* gr = g_raw ? g_raw : graw;
-    LMR_HIP(launch_bwd(F, M, img, Mw, maps, g, *p, nullptr, nullptr, nullptr, u, nullptr,
-                       gr, stream));
+    LMR_HIP(launch_bwd(F, img, Mw, maps, g, *p, nullptr, graw, gr, stream));
     if (g_smooth) LMR_HIP(launch_smooth(gr, g, *p, nullptr, g_smooth, stream));
   }
   return LMR_OK;

@@ -259,12 +259,8 @@ __device__ __forceinline__ void bwd_item(const BatchPair* __restrict__ pairs, in
   if (fresh(&P.st->stalled) || !fresh(&P.st->accepted) || other_form<FORM>(P)) return;
   BwdPol<T, Acc> pol;
   pol.F = static_cast<const T*>(P.F);
-  pol.M = static_cast<const T*>(P.M);
   pol.Mw = P.Mw;
   pol.maps = P.maps;
-  pol.U0 = P.U0;
-  pol.U1 = P.U1;
-  pol.u_explicit = fresh(&P.st->cur) ? P.U1 : P.U0;  // the accepted candidate
   pol.dMw = P.graw;  // stored there by P1 for the candidate
   pol.graw = P.graw;
   pol.g = P.g;

@@ -246,18 +246,13 @@ hipError_t fwd_t(const T* F, const float* Mw, const double* fstat, const Geom& g
 }
 
 template <typename T, typename Acc>
-hipError_t bwd_t(const T* F, const T* M, const float* Mw, const float* maps,
-                 const Geom& g, const lmr_params& p, const DevState* st,
-                 const float* U0, const float* U1, const float* ue, const float* dMw,
-                 float* graw, hipStream_t s, const PassDecision* pd = nullptr) {
+hipError_t bwd_t(const T* F, const float* Mw, const float* maps, const Geom& g,
+                 const lmr_params& p, const DevState* st, const float* dMw, float* graw,
+                 hipStream_t s, const PassDecision* pd = nullptr) {
   BwdPol<T, Acc> pol;
   pol.F = F;
-  pol.M = M;
   pol.Mw = Mw;
   pol.maps = maps;
-  pol.U0 = U0;
-  pol.U1 = U1;
-  pol.u_explicit = ue;
   pol.dMw = dMw;
   pol.graw = graw;
   pol.g = g;
@@ -328,20 +323,18 @@ hipError_t launch_fwd(const void* F, lmr_dtype t, const float* Mw, const double*
                                     s);
 }
 
-hipError_t launch_bwd(const void* F, const void* M, lmr_dtype t, const float* Mw,
-                      const float* maps, const Geom& g, const lmr_params& p,
-                      const DevState* st, const float* U0, const float* U1,
-                      const float* ue, const float* dMw, float* graw, hipStream_t s) {
+hipError_t launch_bwd(const void* F, lmr_dtype t, const float* Mw, const float* maps,
+                      const Geom& g, const lmr_params& p, const DevState* st,
+                      const float* dMw, float* graw, hipStream_t s) {
   if (t == LMR_BF16) {
-    const uint16_t *f = static_cast<const uint16_t*>(F), *m = static_cast<const uint16_t*>(M);
+    const uint16_t* f = static_cast<const uint16_t*>(F);
     return p.accum == LMR_ACC_F32C
-               ? bwd_t<uint16_t, F32C>(f, m, Mw, maps, g, p, st, U0, U1, ue, dMw, graw, s)
-               : bwd_t<uint16_t, double>(f, m, Mw, maps, g, p, st, U0, U1, ue, dMw, graw, s);
+               ? bwd_t<uint16_t, F32C>(f, Mw, maps, g, p, st, dMw, graw, s)
+               : bwd_t<uint16_t, double>(f, Mw, maps, g, p, st, dMw, graw, s);
   }
-  const float *f = static_cast<const float*>(F), *m = static_cast<const float*>(M);
-  return p.accum == LMR_ACC_F32C
-             ? bwd_t<float, F32C>(f, m, Mw, maps, g, p, st, U0, U1, ue, dMw, graw, s)
-             : bwd_t<float, double>(f, m, Mw, maps, g, p, st, U0, U1, ue, dMw, graw, s);
+  const float* f = static_cast<const float*>(F);
+  return p.accum == LMR_ACC_F32C ? bwd_t<float, F32C>(f, Mw, maps, g, p, st, dMw, graw, s)
+                                 : bwd_t<float, double>(f, Mw, maps, g, p, st, dMw, graw, s);
 }
 
 hipError_t launch_smooth(const float* graw, const Geom& g, const lmr_params& p,
@@ -363,26 +356,22 @@ bool bwd_takes_decision(const Geom& g, const lmr_params& p, int nparts) {
          !(use_cubes(g, p) && cube_tz(g) == 8);
 }
 
-hipError_t launch_bwd_decide(const void* F, const void* M, lmr_dtype t, const float* Mw,
-                             const float* maps, const Geom& g, const lmr_params& p,
-                             const DevState* st, const float* U0, const float* U1,
+hipError_t launch_bwd_decide(const void* F, lmr_dtype t, const float* Mw, const float* maps,
+                             const Geom& g, const lmr_params& p, const DevState* st,
                              const float* dMw, float* graw, const PassDecision& pd,
                              hipStream_t s) {
   if (!st || !pd.partials || !pd.next || !bwd_takes_decision(g, p, pd.nparts))
     return hipErrorInvalidValue;
   if (t == LMR_BF16) {
-    const uint16_t *f = static_cast<const uint16_t*>(F), *m = static_cast<const uint16_t*>(M);
+    const uint16_t* f = static_cast<const uint16_t*>(F);
     return p.accum == LMR_ACC_F32C
-               ? bwd_t<uint16_t, F32C>(f, m, Mw, maps, g, p, st, U0, U1, nullptr, dMw, graw,
-                                       s, &pd)
-               : bwd_t<uint16_t, double>(f, m, Mw, maps, g, p, st, U0, U1, nullptr, dMw, graw,
-                                         s, &pd);
+               ? bwd_t<uint16_t, F32C>(f, Mw, maps, g, p, st, dMw, graw, s, &pd)
+               : bwd_t<uint16_t, double>(f, Mw, maps, g, p, st, dMw, graw, s, &pd);
   }
-  const float *f = static_cast<const float*>(F), *m = static_cast<const float*>(M);
+  const float* f = static_cast<const float*>(F);
   return p.accum == LMR_ACC_F32C
-             ? bwd_t<float, F32C>(f, m, Mw, maps, g, p, st, U0, U1, nullptr, dMw, graw, s, &pd)
-             : bwd_t<float, double>(f, m, Mw, maps, g, p, st, U0, U1, nullptr, dMw, graw, s,
-                                    &pd);
+             ? bwd_t<float, F32C>(f, Mw, maps, g, p, st, dMw, graw, s, &pd)
+             : bwd_t<float, double>(f, Mw, maps, g, p, st, dMw, graw, s, &pd);
 }
 
 hipError_t launch_smooth_commit(const float* graw, const Geom& g, const lmr_params& p,

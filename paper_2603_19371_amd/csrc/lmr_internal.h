@@ -454,15 +454,11 @@ hipError_t launch_fwd(const void* F, lmr_dtype t, const float* Mw, const double*
 hipError_t launch_decide(DevState* st, const double* partials, int nparts,
                          long long N, const DecideParams& dp, int mode, int force,
                          double lambda0, double* probe, hipStream_t s);
-// P4: LNCC backward and warp backward -> raw gradient.  The field is U[cur]
-// in state mode, u_explicit otherwise.  dMw (may be null, may alias graw):
-// the derivative of M at x + u(x) stored by P1 for the accepted candidate;
-// null gathers it from M.
-hipError_t launch_bwd(const void* F, const void* M, lmr_dtype t, const float* Mw,
-                      const float* maps, const Geom& g, const lmr_params& p,
-                      const DevState* st, const float* U0, const float* U1,
-                      const float* u_explicit, const float* dMw, float* graw,
-                      hipStream_t s);
+// P4: LNCC backward and warp backward -> raw gradient.  dMw (may alias graw):
+// the derivative of M at x + u(x), stored with Mw by P1 or launch_warp.
+hipError_t launch_bwd(const void* F, lmr_dtype t, const float* Mw, const float* maps,
+                      const Geom& g, const lmr_params& p, const DevState* st,
+                      const float* dMw, float* graw, hipStream_t s);
 // P5: Gaussian smoothing of the raw gradient.
 hipError_t launch_smooth(const float* graw, const Geom& g, const lmr_params& p,
                          const DevState* st, float* out, hipStream_t s);

@@ -34,9 +34,8 @@ struct PassDecision {
 // 4-plane bricks (the 8-plane brick pass would spill registers with it).
 bool bwd_takes_decision(const Geom& g, const lmr_params& p, int nparts);
 // P4 with the decision: st is the pair state before the attempt (read only).
-hipError_t launch_bwd_decide(const void* F, const void* M, lmr_dtype t, const float* Mw,
-                             const float* maps, const Geom& g, const lmr_params& p,
-                             const DevState* st, const float* U0, const float* U1,
+hipError_t launch_bwd_decide(const void* F, lmr_dtype t, const float* Mw, const float* maps,
+                             const Geom& g, const lmr_params& p, const DevState* st,
                              const float* dMw, float* graw, const PassDecision& pd,
                              hipStream_t s);
 // P5 after it: runs on the staged state `next` and stores it into the pair

@@ -547,33 +547,27 @@ struct BwdPol {
   static constexpr int NRAW = 4, NCH = 4;
   static constexpr bool kBox = true, kSeparateLds = true;
   const T* __restrict__ F;
-  const T* __restrict__ M;
   const float* __restrict__ Mw;
   const float* __restrict__ maps;
-  const float* U0;  // field ping-pong (state mode: the field is U[cur])
-  const float* U1;
-  const float* u_explicit;  // the field when no state is given
-  // derivative of M at x + u(x) as the update kernel stored it for the
-  // candidate (null: gathered here); may alias graw (read, then overwritten,
-  // by the thread of the same voxel)
+  // derivative of M at x + u(x), stored by the kernel that warped M (P1 or
+  // k_warp): gathered here it costs the pass a dependent read of the field
+  // and eight corner loads (160x192x224 traced: gathered 152 us; stored 117 us
+  // and 14 us more in the warp).  May alias graw (read, then overwritten, by the
+  // thread of the same voxel).
   const float* dMw;
   float* graw;
   Geom g;
   double inv_n;
   struct Local {
     RBuf bmap[4];
-    RBuf bM;
-    const float* u;
   };
 
   __device__ static constexpr double wt(int) { return 1.0; }
-  __device__ Local begin_block(const DevState* st) const {
+  __device__ Local begin_block(const DevState*) const {
     const int N = static_cast<int>(g.N);
     Local l;
-    l.u = st ? (st->cur ? U1 : U0) : u_explicit;
 #pragma unroll
     for (int c = 0; c < 4; ++c) l.bmap[c] = make_rbuf_n(maps + c * N, N);
-    l.bM = make_rbuf_n(M, N);
     return l;
   }
   __device__ void load(const Local& l, unsigned i, float v[4]) const {
@@ -589,27 +583,16 @@ struct BwdPol {
         a[c] += static_cast<double>(r[c]);
     }
   }
-  __device__ void emit(const Local& loc, int i, int x, int y, int z, const Acc Bs[4]) const {
+  __device__ void emit(const Local&, int i, int, int, int, const Acc Bs[4]) const {
     const int N = static_cast<int>(g.N);
-    const float* u = loc.u;
     const double fj = ldf(F, i), mj = Mw[i];
     const double B[4] = {to_f64(Bs[0]), to_f64(Bs[1]), to_f64(Bs[2]), to_f64(Bs[3])};
     const double dS = (fj * B[0] - B[1] + 2.0 * mj * B[2] - 2.0 * B[3]) * inv_n;
     const float d = static_cast<float>(dS);
-    float gm[3];
-    if (dMw) {
-      gm[0] = dMw[i];
-      gm[1] = dMw[N + i];
-      gm[2] = dMw[2 * N + i];
-    } else {
-      float v[8];
-      const BCell c = make_bcell(g, x, y, z, u[i], u[N + i], u[2 * N + i]);
-      bcorners<T>(loc.bM, g, c, v);
-      binterp(c, v, gm);
-    }
-    graw[i] = -d * gm[0];
-    graw[N + i] = -d * gm[1];
-    graw[2 * N + i] = -d * gm[2];
+    const float g0 = dMw[i], g1 = dMw[N + i], g2 = dMw[2 * N + i];
+    graw[i] = -d * g0;
+    graw[N + i] = -d * g1;
+    graw[2 * N + i] = -d * g2;
   }
   __device__ void end_tile(Local&, int) const {}
 };
