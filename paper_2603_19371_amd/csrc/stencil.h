@@ -143,6 +143,7 @@ __device__ __forceinline__ void stencil_tile_in(
   constexpr int NR = P::NRAW, NC = P::NCH;
   constexpr int W = 2 * R + 1, LX = kTX + 2 * R, LY = TY + 2 * R, NT = kTX * TY;
   constexpr int NPOS = LX * LY, PER = (NPOS + NT - 1) / NT;
+  constexpr bool kEarly = !std::is_same<A, F32C>::value;
 
   const int lx = threadIdx.x % kTX, ly = threadIdx.x / kTX;
   const int gx = x0 + lx, gy = y0 + ly;
@@ -199,6 +200,16 @@ __device__ __forceinline__ void stencil_tile_in(
     for (int s = 0; s < W; ++s) {
       if (zi < zend) {
         commit();
+        // with FP64 sums the operands of this step's output are requested
+        // before the next plane, so that they arrive during the y pass (read
+        // at their use, a block waits a memory round trip per plane; forward
+        // pass at 160x192x224, w 7: 90.5 -> 85.5 us).  The compensated sums
+        // have no registers to hold them (121x145x119, w 9: 346 -> 351 us).
+        const int zo = zi - R;
+        const bool out = zo >= z0 && own;
+        const int io = zo * plane + gy * g.nx + gx;
+        typename P::Pre q;
+        if (kEarly && out) pol.pre(io, q);
         if (zi + 1 < zend) fetch(zi + 1);
         __syncthreads();
         for (int i = threadIdx.x; i < TY * LX; i += NT) {
@@ -251,8 +262,10 @@ __device__ __forceinline__ void stencil_tile_in(
             for (int c = 0; c < NC; ++c)
               sm[c] = fma(A(pol.wt(k)), ring[(s + 1 + k) % W][c], sm[c]);
         }
-        const int zo = zi - R;
-        if (zo >= z0 && own) pol.emit(loc, zo * plane + gy * g.nx + gx, gx, gy, zo, sm);
+        if (out) {
+          if (!kEarly) pol.pre(io, q);
+          pol.emit(loc, io, q, sm);
+        }
       }
       ++zi;
     }
@@ -415,8 +428,12 @@ __device__ __forceinline__ void stencil_cube(const P& pol, const Geom& g, int x0
           a[c] = fma(A(pol.wt(k)), sy[c][oz][oy][ox + k], a[c]);
       }
     const int gx = x0 + ox, gy = y0 + oy, gz = z0 + oz;
-    if (gx < g.nx && gy < g.ny && gz < g.nz)
-      pol.emit(loc, (gz * g.ny + gy) * g.nx + gx, gx, gy, gz, a);
+    if (gx < g.nx && gy < g.ny && gz < g.nz) {
+      const int i = (gz * g.ny + gy) * g.nx + gx;
+      typename P::Pre q;
+      pol.pre(i, q);
+      pol.emit(loc, i, q, a);
+    }
   }
 }
 
@@ -454,6 +471,7 @@ struct FStatPol {
   struct Local {
     RBuf bF;
   };
+  struct Pre {};
 
   __device__ static constexpr double wt(int) { return 1.0; }
   __device__ Local begin_block(const DevState*) const { return Local{make_rbuf_n(F, N)}; }
@@ -468,7 +486,8 @@ struct FStatPol {
       a[1] = fma(f, f, a[1]);
     }
   }
-  __device__ void emit(Local&, int i, int, int, int, const Acc S[2]) const {
+  __device__ void pre(int, Pre&) const {}
+  __device__ void emit(Local&, int i, const Pre&, const Acc S[2]) const {
     const double muF = to_f64(S[0]) * inv_n;
     fstat[i] = muF;
     fstat[N + i] = to_f64(S[1]) * inv_n - muF * muF;
@@ -496,6 +515,9 @@ struct FwdPol {
     double sum;
     RBuf bF, bM;
   };
+  struct Pre {
+    double muF, sff;
+  };
 
   __device__ static constexpr double wt(int) { return 1.0; }
   __device__ Local begin_block(const DevState*) const {
@@ -517,8 +539,12 @@ struct FwdPol {
       a[2] = fma(f, m, a[2]);
     }
   }
-  __device__ void emit(Local& loc, int i, int, int, int, const Acc S[3]) const {
-    const double muF = fstat[i], sff = fstat[N + i];
+  __device__ void pre(int i, Pre& q) const {
+    q.muF = fstat[i];
+    q.sff = fstat[N + i];
+  }
+  __device__ void emit(Local& loc, int i, const Pre& q, const Acc S[3]) const {
+    const double muF = q.muF, sff = q.sff;
     const double muM = to_f64(S[0]) * inv_n;
     const double sfm = to_f64(S[2]) * inv_n - muF * muM;
     const double smm = to_f64(S[1]) * inv_n - muM * muM;
@@ -561,6 +587,9 @@ struct BwdPol {
   struct Local {
     RBuf bmap[4];
   };
+  struct Pre {
+    float f, m, d[3];
+  };
 
   __device__ static constexpr double wt(int) { return 1.0; }
   __device__ Local begin_block(const DevState*) const {
@@ -583,16 +612,21 @@ struct BwdPol {
         a[c] += static_cast<double>(r[c]);
     }
   }
-  __device__ void emit(const Local&, int i, int, int, int, const Acc Bs[4]) const {
+  __device__ void pre(int i, Pre& q) const {
     const int N = static_cast<int>(g.N);
-    const double fj = ldf(F, i), mj = Mw[i];
+    q.f = ldf(F, i);
+    q.m = Mw[i];
+#pragma unroll
+    for (int c = 0; c < 3; ++c) q.d[c] = dMw[c * N + i];
+  }
+  __device__ void emit(const Local&, int i, const Pre& q, const Acc Bs[4]) const {
+    const int N = static_cast<int>(g.N);
+    const double fj = q.f, mj = q.m;
     const double B[4] = {to_f64(Bs[0]), to_f64(Bs[1]), to_f64(Bs[2]), to_f64(Bs[3])};
     const double dS = (fj * B[0] - B[1] + 2.0 * mj * B[2] - 2.0 * B[3]) * inv_n;
     const float d = static_cast<float>(dS);
-    const float g0 = dMw[i], g1 = dMw[N + i], g2 = dMw[2 * N + i];
-    graw[i] = -d * g0;
-    graw[N + i] = -d * g1;
-    graw[2 * N + i] = -d * g2;
+#pragma unroll
+    for (int c = 0; c < 3; ++c) graw[c * N + i] = -d * q.d[c];
   }
   __device__ void end_tile(Local&, int) const {}
 };
@@ -610,6 +644,7 @@ struct SmoothPol {
   struct Local {
     RBuf b[3];
   };
+  struct Pre {};
 
   __device__ float wt(int k) const { return w[k]; }
   __device__ Local begin_block(const DevState*) const {
@@ -623,7 +658,8 @@ struct SmoothPol {
 #pragma unroll
     for (int c = 0; c < 3; ++c) a[c] = fmaf(w[k], r[c], a[c]);
   }
-  __device__ void emit(Local&, int i, int, int, int, const float S[3]) const {
+  __device__ void pre(int, Pre&) const {}
+  __device__ void emit(Local&, int i, const Pre&, const float S[3]) const {
     out[i] = S[0];
     out[N + i] = S[1];
     out[2 * N + i] = S[2];
