@@ -127,17 +127,18 @@ lmr_status enqueue_attempt(lmr_ctx* c, const void* F, const void* M, int force) 
                        c->nparts, nullptr, s));
   else if (sim == LMR_SIM_MI)
     LMR_HIP(launch_mi_fwd(F, c->img, c->Mw, c->g, c->p.mi_bins, c->mi_map, c->mi_hpart,
-                          c->mi_p, c->mi_tab, c->partials, c->st, s));
+                          c->mi_tab, c->st, MiDecision{c->dp, 0, force, 0.0, nullptr}, s));
   else
     LMR_HIP(launch_mse_fwd(F, c->img, c->Mw, c->g, c->nparts, c->partials, nullptr, c->st, s));
   LMR_HIP(mark(LMR_K_FWD, 1));
   // levels with few partials take the decision in the backward pass, which
   // stages the decided state; the smoothing pass makes it the pair state
+  // (mutual information takes it where MI is formed)
   const bool dec_in_bwd = sim == LMR_SIM_LNCC && bwd_takes_decision(c->g, c->p, c->nparts);
   LMR_HIP(mark(LMR_K_DECIDE, 0));
-  if (!dec_in_bwd)
-    LMR_HIP(launch_decide(c->st, c->partials, sim == LMR_SIM_MI ? 1 : c->nparts, c->g.N,
-                          c->dp, 0, force, 0.0, nullptr, s));
+  if (!dec_in_bwd && sim != LMR_SIM_MI)
+    LMR_HIP(launch_decide(c->st, c->partials, c->nparts, c->g.N, c->dp, 0, force, 0.0,
+                          nullptr, s));
   LMR_HIP(mark(LMR_K_DECIDE, 1));
   LMR_HIP(mark(LMR_K_BWD, 0));
   if (dec_in_bwd) {
@@ -269,7 +270,7 @@ lmr_status lmr_create(lmr_ctx** out, int nz, int ny, int nx, lmr_dtype img,
   const size_t mv_bytes = p->optimizer == LMR_OPT_ADAM ? f3 : 0;
   const bool mi = p->similarity == LMR_SIM_MI;
   const size_t bb = mi ? static_cast<size_t>(p->mi_bins) * p->mi_bins : 0;
-  const size_t mi_sizes[5] = {align256(8 * bb * kMiBlocks), align256(8 * bb), align256(8 * bb),
+  const size_t mi_sizes[4] = {align256(8 * bb * kMiHists), align256(8 * bb),
                               mi ? align256(32) : 0, mi ? align256(16 * kMiBlocks) : 0};
   size_t mi_bytes = 0;
   for (size_t v : mi_sizes) mi_bytes += v;
@@ -306,12 +307,10 @@ lmr_status lmr_create(lmr_ctx** out, int nz, int ny, int nx, lmr_dtype img,
   q += 2 * mv_bytes;
   c->mi_hpart = mi ? reinterpret_cast<unsigned long long*>(q) : nullptr;
   q += mi_sizes[0];
-  c->mi_p = mi ? reinterpret_cast<double*>(q) : nullptr;
-  q += mi_sizes[1];
   c->mi_tab = mi ? reinterpret_cast<double*>(q) : nullptr;
-  q += mi_sizes[2];
+  q += mi_sizes[1];
   c->mi_map = mi ? reinterpret_cast<double*>(q) : nullptr;
-  q += mi_sizes[3];
+  q += mi_sizes[2];
   c->mi_rpart = mi ? reinterpret_cast<float*>(q) : nullptr;
   c->mi_of[0] = c->mi_of[1] = nullptr;
   c->begun = false;
@@ -349,14 +348,15 @@ lmr_status lmr_begin(lmr_ctx* c, const void* F, const void* M, const float* fiel
     c->mi_of[1] = M;
     LMR_HIP(launch_warp(M, c->img, c->U[0], c->g, c->Mw, c->graw, s));
     LMR_HIP(launch_mi_fwd(F, c->img, c->Mw, c->g, c->p.mi_bins, c->mi_map, c->mi_hpart,
-                          c->mi_p, c->mi_tab, c->partials, nullptr, s));
+                          c->mi_tab, c->st, MiDecision{c->dp, 1, -1, lambda0, nullptr}, s));
   } else {
     LMR_HIP(launch_warp(M, c->img, c->U[0], c->g, c->Mw, c->graw, s));
     LMR_HIP(launch_mse_fwd(F, c->img, c->Mw, c->g, c->nparts, c->partials, nullptr, nullptr,
                            s));
   }
-  LMR_HIP(launch_decide(c->st, c->partials, sim == LMR_SIM_MI ? 1 : c->nparts, c->g.N, c->dp,
-                        1, -1, lambda0, nullptr, s));
+  if (sim != LMR_SIM_MI)
+    LMR_HIP(launch_decide(c->st, c->partials, c->nparts, c->g.N, c->dp, 1, -1, lambda0,
+                          nullptr, s));
   if (sim == LMR_SIM_LNCC) {
     LMR_HIP(launch_bwd(F, c->img, c->Mw, c->maps, c->g, c->p, nullptr, c->graw, c->graw, s));
     LMR_HIP(launch_smooth(c->graw, c->g, c->p, nullptr, c->G, s));
@@ -514,16 +514,16 @@ lmr_status lmr_loss_grad(lmr_ctx* c, const void* F, const void* M, const float* 
     c->mi_of[1] = M;
     LMR_HIP(launch_warp(M, c->img, u, c->g, c->Mw, c->graw, s));
     LMR_HIP(launch_mi_fwd(F, c->img, c->Mw, c->g, c->p.mi_bins, c->mi_map, c->mi_hpart,
-                          c->mi_p, c->mi_tab, c->partials, nullptr, s));
+                          c->mi_tab, c->st, MiDecision{c->dp, 2, -1, 0.0, c->probe}, s));
   } else {
     // squared error (cc_map receives the squared errors)
     LMR_HIP(launch_warp(M, c->img, u, c->g, c->Mw, c->graw, s));
     LMR_HIP(launch_mse_fwd(F, c->img, c->Mw, c->g, c->nparts, c->partials, cc_map, nullptr,
                            s));
   }
-  LMR_HIP(launch_decide(c->st, c->partials,
-                        c->p.similarity == LMR_SIM_MI ? 1 : c->nparts, c->g.N, c->dp, 2, -1,
-                        0.0, c->probe, s));
+  if (c->p.similarity != LMR_SIM_MI)
+    LMR_HIP(launch_decide(c->st, c->partials, c->nparts, c->g.N, c->dp, 2, -1, 0.0, c->probe,
+                          s));
   if (g_raw || g_smooth) {
     float* gr = g_raw ? g_raw : c->graw;
     if (c->p.similarity == LMR_SIM_LNCC)

@@ -49,9 +49,8 @@ struct lmr_ctx {
   // Adam comparator: first and second moments [3][N] each
   float* am;
   float* av;
-  // mutual information: partial histograms, p, gradient table, bin maps
+  // mutual information: partial histograms, gradient table, bin maps
   unsigned long long* mi_hpart;
-  double* mi_p;
   double* mi_tab;
   double* mi_map;
   float* mi_rpart;

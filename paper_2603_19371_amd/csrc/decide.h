@@ -103,8 +103,35 @@ __device__ inline DevState decide_next(const DevState& cur, double L, const Deci
   return n;
 }
 
-// mode 0: attempt (force -1/0/1), mode 1: begin (lambda0), mode 2: probe
-// (*probe = L).  Called by all NT threads of one block; uses NT doubles of LDS.
+// What a decision writes for the loss L, by one thread.  mode 0: attempt
+// (force -1/0/1, cur: the state read at entry), mode 1: begin (lambda0),
+// mode 2: probe (*probe = L).
+__device__ inline void decide_write(DevState* st, const DevState& cur, double L,
+                                    const DecideParams& dp, int mode, int force,
+                                    double lambda0, double* probe) {
+  if (mode == 2) {
+    *probe = L;
+  } else if (mode == 1) {
+    st->lambda = lambda0;
+    st->loss = L;
+    st->loss_prev = L;
+    st->cand_loss = L;
+    st->r = residual_of(L, dp.similarity, dp.mi_bins);
+    st->n_hist = 1;
+    st->retries = 0;
+    st->accepted = 1;
+    st->stalled = 0;
+    st->cur = 0;
+    st->attempts = 0;
+    st->adam_pow1 = dp.adam_beta1;
+    st->adam_pow2 = dp.adam_beta2;
+  } else {
+    *st = decide_next(cur, L, dp, force);
+  }
+}
+
+// The same from the partials, by all NT threads of one block; uses NT doubles
+// of LDS.
 template <int NT>
 __device__ void decide_block(DevState* st, const double* __restrict__ partials,
                              int nparts, long long N, const DecideParams& dp, int mode,
@@ -114,29 +141,8 @@ __device__ void decide_block(DevState* st, const double* __restrict__ partials,
   DevState cur_st;
   if (threadIdx.x == 0) cur_st = *st;
   const double S = reduce_partials<NT>(partials, nparts, sh);
-  if (threadIdx.x == 0) {
-    const double L = -S / static_cast<double>(N);
-    if (mode == 2) {
-      *probe = L;
-    } else if (mode == 1) {
-      st->lambda = lambda0;
-      st->loss = L;
-      st->loss_prev = L;
-      st->cand_loss = L;
-      st->r = residual_of(L, dp.similarity, dp.mi_bins);
-      st->n_hist = 1;
-      st->retries = 0;
-      st->accepted = 1;
-      st->stalled = 0;
-      st->cur = 0;
-      st->attempts = 0;
-      st->adam_pow1 = dp.adam_beta1;
-      st->adam_pow2 = dp.adam_beta2;
-    } else {
-      // the decision on the state read at entry; the new state is written back
-      *st = decide_next(cur_st, L, dp, force);
-    }
-  }
+  if (threadIdx.x == 0)
+    decide_write(st, cur_st, -S / static_cast<double>(N), dp, mode, force, lambda0, probe);
   __syncthreads();
 }
 

@@ -397,19 +397,25 @@ hipError_t launch_update(const void* M, lmr_dtype t, const Geom& g,
                          float* u_out, double r, double lambda, float* Mw, float* dMw,
                          hipStream_t s, const StepExtra* extra = nullptr);
 // Mutual information (k_mi.hip).  Histogram blocks of the forward pass:
-// kMiBlocks at most (mi_hist_blocks(N)); their partial histograms take
-// kMiBlocks * bins^2 unsigned 64-bit counts.
-constexpr int kMiBlocks = 256;
-int mi_hist_blocks(long long N);
+// kMiBlocks at most; their partial histograms, and the sums of every kMiFold
+// of them, take kMiHists * bins^2 unsigned 64-bit counts.
+constexpr int kMiBlocks = 256, kMiFold = 8, kMiHists = kMiBlocks + kMiBlocks / kMiFold;
 // map[0..3] = (lo_F, s_F, lo_M, s_M) of the bin coordinates, from the
 // ranges of F and M (part: 4 * kMiBlocks floats of scratch).
 hipError_t launch_mi_range(const void* F, const void* M, lmr_dtype t, const Geom& g, int bins,
                            float* part, double* map, hipStream_t s);
-// Joint histogram of F and Mw, p (FP64 [bins^2]), the gradient table tab
-// (FP64 [bins^2]) and partials[0] = N MI; a frozen pair is skipped.
+// Joint histogram of F and Mw, the gradient table tab (FP64 [bins^2]) and the
+// decision on L = -MI (mode 0: attempt on the pair state st, a frozen pair is
+// skipped; 1: begin; 2: *probe = L, st unused).
+struct MiDecision {
+  DecideParams dp;
+  int mode, force;
+  double lambda0;
+  double* probe;
+};
 hipError_t launch_mi_fwd(const void* F, lmr_dtype t, const float* Mw, const Geom& g, int bins,
-                         const double* map, unsigned long long* hpart, double* p, double* tab,
-                         double* partials, const DevState* st, hipStream_t s);
+                         const double* map, unsigned long long* hpart, double* tab,
+                         DevState* st, const MiDecision& md, hipStream_t s);
 // g = N dr/du from tab (only after an acceptance with a state); dMw may
 // alias graw.
 hipError_t launch_mi_bwd(const void* F, lmr_dtype t, const float* Mw, const float* dMw,
