@@ -8,17 +8,22 @@
 // tensors sharing one buffer at different channel offsets.  Weights are FP32
 // masters [27][cin][cout] (tap t = 9 (dz+1) + 3 (dy+1) + (dx+1) reads the
 // input at v + (dx, dy, dz)), packed per step into BF16
-//   Wf [27][cout_p][cin_p]  (forward: the reduction index contiguous)
-//   Wb [27][cin_p][cout_p]  tap order reversed (gradient with respect to the
-//                           input = convolution of dZ with the flipped,
-//                           transposed kernel)
-// with cin_p, cout_p the channel counts rounded up to 16, zero padded.
+//   Wf  forward
+//   Wb  transposed, tap order reversed (gradient with respect to the input =
+//       convolution of dZ with the flipped, transposed kernel)
+// with cin_p, cout_p the channel counts rounded up to 16, zero padded.  A pack
+// is a sequence of MFMA weight operands, [output tile][input chunk][27 taps]
+// of 16 x 16 channels: lane l holds input channels 4 (l / 16) .. + 3 of
+// output channel l % 16 in elements 4 l .. 4 l + 3, so an operand is one
+// contiguous 512-byte read.
 //
 // MFMA operand layout (16x16 output tile, K = 4 g or 8 g per lane group
 // g = lane / 16): lane l feeds row l % 16 of A and column l % 16 of B with
 // the same K slots, and receives D[4 g + j][l % 16], j = 0..3.  Which K a
 // slot maps to is irrelevant as long as A and B agree.
 #include <hip/hip_runtime.h>
+
+#include <type_traits>
 
 #include "lmr_internal.h"
 #include "unet_internal.h"
@@ -57,6 +62,7 @@ struct K16 {
   typedef s4 vec;
   __device__ static vec zero() { return vec{0, 0, 0, 0}; }
   __device__ static vec load(const uint16_t* p) { return *reinterpret_cast<const s4*>(p); }
+  __device__ static vec load_w(const uint16_t* p) { return load(p); }
   __device__ static f4 mma(vec a, vec b, f4 c) {
     return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, c, 0, 0, 0);
   }
@@ -72,6 +78,10 @@ struct K32 {
     return z;
   }
   __device__ static vec load(const uint16_t* p) { return *reinterpret_cast<const b8*>(p); }
+  // two consecutive quads of a packed operand (16 lanes apart)
+  __device__ static vec load_w(const uint16_t* p) {
+    return cat_bf16(*reinterpret_cast<const s4*>(p), *reinterpret_cast<const s4*>(p + 64));
+  }
   __device__ static f4 mma(vec a, vec b, f4 c) {
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
   }
@@ -100,12 +110,14 @@ __global__ void __launch_bounds__(256) k_conv(ConvArgs a) {
                     (unsigned)xx < (unsigned)a.nx;
     const uint16_t* xp =
         a.X + (in ? ((long long)(zz * a.ny + yy) * a.nx + xx) * a.ldx : 0);
-    const uint16_t* wt = a.W + ((long long)t * a.cout_p + co0 + m) * a.cin_p;
+    const uint16_t* wt = a.W + ((long long)(co0 / 16) * (a.cin_p / 16) * 27 + t) * 256;
     for (int c0 = 0; c0 < a.cin_p; c0 += MM::KW) {
       const int ci = c0 + KL * kq;
       typename MM::vec av = MM::zero();
       if (in && ci < a.cin_valid) av = MM::load(xp + ci);
-      acc = MM::mma(av, MM::load(wt + ci), acc);
+      // quad ci / 4 of the input chunk ci / 16
+      const uint16_t* wq = wt + (ci / 16) * 27 * 256 + (((ci % 16) / 4) * 16 + m) * 4;
+      acc = MM::mma(av, MM::load_w(wq), acc);
     }
   }
   const int co = co0 + m;
@@ -118,189 +130,230 @@ __global__ void __launch_bounds__(256) k_conv(ConvArgs a) {
     const long long v = (long long)(z * a.ny + y) * a.nx + xo;
     float r = acc[j] + b;
     if (a.relu) r = fmaxf(r, 0.0f);
+    if (a.mask && !(bf2f(a.mask[v * a.ldm + co]) > 0.0f)) r = 0.0f;
     if (a.Y) a.Y[v * a.ldy + co] = f2bf(r);
     if (a.yf) a.yf[v * a.ldf + co] = r;
   }
 }
 
-// The same convolution with the operands staged in LDS.  A block owns a
-// 16 x 16 (x, y) tile of output voxels in one z plane and 16 NT output
-// channels; per chunk of 16 input channels it stages the 3 x 18 x 18 input
-// halo and the chunk's 27 weight slices, then each wave runs the MFMAs of
-// four 16-voxel rows for all 27 taps from LDS: each weight operand serves
-// the four rows, each input operand the NT output-channel tiles.  Every load
-// of a chunk is issued before the first is used (one memory latency per
-// chunk, not one per load), and the next chunk's loads are in flight while
-// the current chunk's MFMAs run.  Input positions outside the volume, and
-// channels past cin_valid, read 0 through the buffer resource (an offset
-// beyond the tensor).  (The streamed form above reads both operands from
-// memory for every MFMA and is bound by the memory unit's per-instruction
-// cost.)
+// The same convolution with the operands staged in LDS.  A block of four
+// waves owns 16 x TY (x, y) output voxels of WZ z planes, RW rows of one plane
+// per wave, and 16 NT output channels.  Per chunk of 16 input channels it
+// stages the (WZ + 2) x (TY + 2) x 18 input halo and the chunk's weight
+// operands, then each wave runs the MFMAs of its rows for all 27 taps from
+// LDS.  Every load of a chunk is issued before the first is used and the next
+// chunk's loads are in flight during the current chunk's MFMAs.  Input
+// positions outside the volume, and channels past cin_valid, read 0 through
+// the buffer resource (an offset beyond the tensor).
+//
+// What bounds it is staging and LDS, not the MFMA rate.  A tile of 4 planes x
+// 4 rows stages 648 halo voxels for 256 outputs where one plane of 16 rows
+// takes 972.  An operand read is 512 bytes per wave for one 16-cycle MFMA, so
+// a wave holds the (RW + 2) x 3 input operands of a tap plane in registers: a
+// halo row serves the y taps of up to three output rows, 18 reads where 36
+// would be made at RW = 4.  Forward pass at 80x96x112 per layer: 16 -> 16
+// channels at full resolution 39 -> 28 us, 48 -> 16 88 -> 61, 96 -> 32 at half
+// 41 -> 31, 192 -> 64 at a quarter 45 -> 24, 128 -> 128 at an eighth 29 -> 15
+// us.  Each output is the same sequence of products for every tile shape:
+// chunks, tap planes and tap pairs in order.
 //
 // The MFMA computes D[co][voxel] = sum_ci W[co][ci] X[voxel][ci] (weights as
 // the A operand), so that each lane receives four consecutive output channels
 // of one voxel: the epilogue stores them as one 8-byte (BF16) or 16-byte
-// (FP32) write.
+// (FP32) write, zeroing those whose ReLU was inactive (a.mask).
 //
-// LDS rows (one voxel, or one weight row: 16 channels) are 40 bytes apart.
-// An operand read takes the same 8-byte quad of 16 consecutive rows; with a
-// 32-byte pitch those fall on 4 bank groups (a 4-way conflict), with 40
-// bytes (10 dwords) 10 m mod 32 covers all 16 even banks.  The pitch keeps
-// every LDS address affine in the tap, so the unrolled taps read at
-// immediate offsets from one base per lane.
+// LDS input rows (one voxel: 16 channels) are 40 bytes apart.  An operand
+// read takes the same 8-byte quad of 16 consecutive rows; with a 32-byte
+// pitch those fall on 4 bank groups (a 4-way conflict), with 40 bytes (10
+// dwords) 10 m mod 32 covers all 16 even banks.  The pitch keeps every LDS
+// address affine in the tap.  Weight operands are stored as packed, read
+// lane after lane.
 //
-// Staging is arranged so that every address is a per-thread base plus a
-// compile-time or per-block constant: the input halo is 54 rows (3 planes x
-// 18 rows) of 72 items (18 voxels x 4 quads); threads 0..215 each take one
-// item position in rows r0, r0 + 3, ... (r0 = thread / 72), 18 loads.
-constexpr int kCT = 16;            // tile edge (x and y)
+// V16: the input is staged in 16-byte items (channel stride, offset and
+// count multiples of 8); otherwise in 8-byte quads, those past cin_valid
+// written as zeros without a read (the 2-channel input: 36 -> 25 us).
+constexpr int kCT = 16;            // tile edge along x
 constexpr int kCH = kCT + 2;       // halo tile edge
 constexpr int kPitch = 20;         // LDS row pitch, uint16 elements (40 bytes)
-constexpr int kXLoads = 18;        // halo loads per staging thread
-constexpr int kXThreads = 216;     // staging threads (3 rows x 72 items)
-template <int NT>
+template <int NT, int RW, int WZ, bool V16>
 __global__ void __launch_bounds__(256) k_conv_tile(ConvArgs a) {
-  constexpr int kWRows = 27 * 16 * NT;            // weight rows per chunk
-  constexpr int kWPer = (kWRows * 4 + 255) / 256;  // weight loads per thread
-  constexpr int kTStep = 64 / (16 * NT);           // taps between a thread's loads
-  __shared__ __attribute__((aligned(16))) uint16_t s_x[3 * kCH * kCH * kPitch];
-  __shared__ __attribute__((aligned(16))) uint16_t s_w[kWRows * kPitch];
+  // MFMAs on the same accumulator lie at least four apart: with fewer, the
+  // K = 16 product after a K = 32 product gave wrong sums
+  static_assert(NT * RW >= 4, "independent accumulators between dependent products");
+  constexpr int TY = RW * (4 / WZ);                        // rows of the tile
+  constexpr int HY = TY + 2, P = (WZ + 2) * HY * kCH;      // halo rows, positions
+  // staged items per thread: 16-byte halves of a voxel's 16 channels, or whole
+  // voxels in 8-byte quads
+  constexpr int XI = V16 ? 2 * P : P, XPER = (XI + 255) / 256, QPER = V16 ? 1 : 4;
+  constexpr int WC = 27 * 32;  // 16-byte items of one chunk's weight operands
+  constexpr int WI = NT * WC, WPER = (WI + 255) / 256;
+  __shared__ __attribute__((aligned(16))) uint16_t s_x[P * kPitch];
+  __shared__ __attribute__((aligned(16))) uint16_t s_w[NT * 27 * 256];
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  const int nco = a.cout_p / (16 * NT);
+  const int nco = a.cout_p / (16 * NT), nch = a.cin_p / 16;
   // tile id: channel tile fastest, then x, y, z; each XCD takes a contiguous
   // range of ids, so the blocks that read an input plane (those of output
   // planes z-1, z, z+1, and every channel tile) mostly share one L2
-  const int tiles_x = (a.nx + kCT - 1) / kCT, tiles_y = (a.ny + kCT - 1) / kCT;
+  const int tiles_x = (a.nx + kCT - 1) / kCT, tiles_y = (a.ny + TY - 1) / TY;
   int b = xcd_remap(blockIdx.x, gridDim.x);
   const int co0 = (b % nco) * 16 * NT;
   b /= nco;
   const int x0 = (b % tiles_x) * kCT;
   b /= tiles_x;
-  const int y0 = (b % tiles_y) * kCT;
-  const int z = b / tiles_y;
+  const int y0 = (b % tiles_y) * TY, z0 = (b / tiles_y) * WZ;
+  const int wz = wv % WZ, wy = (wv / WZ) * RW;  // the wave's plane and first row
   const int m = lane & 15, kq = lane >> 4;
-  const int q = tid & 3;  // the quad (4 channels) this thread stages
-  // ---- input staging: element offsets of this thread's 18 items (chunk 0)
+  // ---- input staging: element offset of each item of this thread (channel
+  // group 0; -1: outside the volume) and its channel within the group
   const long long nvox = (long long)a.nz * a.ny * a.nx;
   const RBuf bx = make_rbuf(
       a.X, static_cast<unsigned>(((nvox - 1) * a.ldx + ((a.cin_valid + 3) & ~3)) * 2));
-  const int r0 = tid / 72, xx = (tid % 72) >> 2;
-  const int gx = x0 + xx - 1;
-  const bool xok = tid < kXThreads && (unsigned)gx < (unsigned)a.nx;
-  const int row_st = a.nx * a.ldx, plane_st = a.ny * row_st;  // elements
-  // item (zz, yi): voxel (gx, y0 + r0 + 3 yi - 1, z + zz - 1)
-  const int xbase = ((z - 1) * a.ny + y0 + r0 - 1) * row_st + gx * a.ldx + 4 * q;
-  unsigned yok = 0;  // bit yi: row y0 + r0 + 3 yi - 1 inside the volume
+  auto item = [&](int j, int& pos, int& ch) {
+    const int it = tid + 256 * j;
+    pos = V16 ? it >> 1 : it;
+    ch = V16 ? 8 * (it & 1) : 0;
+    return it < XI;
+  };
+  int xoff[XPER];
 #pragma unroll
-  for (int yi = 0; yi < 6; ++yi)
-    yok |= ((unsigned)(y0 + r0 + 3 * yi - 1) < (unsigned)a.ny ? 1u : 0u) << yi;
-  const int sx_base = (r0 * kCH + xx) * kPitch + 4 * q;  // LDS element offset
-  // ---- weight staging: rows R = tid / 4 + 64 j (tap R / 16 NT, channel R % 16 NT)
+  for (int j = 0; j < XPER; ++j) {
+    int pos, ch;
+    const bool ok = item(j, pos, ch);
+    const int gz = z0 + pos / (HY * kCH) - 1, gy = y0 + (pos / kCH) % HY - 1,
+              gx = x0 + pos % kCH - 1;
+    const bool in = ok && (unsigned)gz < (unsigned)a.nz && (unsigned)gy < (unsigned)a.ny &&
+                    (unsigned)gx < (unsigned)a.nx;
+    xoff[j] = in ? ((gz * a.ny + gy) * a.nx + gx) * a.ldx + ch : -1;
+  }
   const RBuf bw = make_rbuf(a.W, static_cast<unsigned>(27LL * a.cout_p * a.cin_p * 2));
-  const int wrow = tid >> 2;
-  const int wbase = ((wrow / (16 * NT)) * a.cout_p + co0 + wrow % (16 * NT)) * a.cin_p + 4 * q;
-  const int wstep = kTStep * a.cout_p * a.cin_p;
-  s4 rx[kXLoads], rw[kWPer];
-  auto fetch = [&](int c0) {
-    const bool cok = xok && c0 + 4 * q < a.cin_valid;
+  using Item = std::conditional_t<V16, uint4, uint2>;
+  Item rx[XPER][QPER];
+  uint4 rw[WPER];
+  auto fetch = [&](int chunk) {
+    const int c0 = 16 * chunk;
 #pragma unroll
-    for (int i = 0; i < kXLoads; ++i) {
-      const int zz = i / 6, yi = i % 6;
-      const bool ok = cok && ((yok >> yi) & 1u) && (unsigned)(z + zz - 1) < (unsigned)a.nz;
-      const int e = xbase + zz * plane_st + 3 * yi * row_st + c0;
-      const unsigned o = ok ? static_cast<unsigned>(e) * 2u : kFarOffset;
-      const auto v = __builtin_amdgcn_raw_buffer_load_b64(bx.r, o, 0, 0);
-      rx[i] = s4{static_cast<short>(v[0] & 0xFFFFu), static_cast<short>(v[0] >> 16),
-                 static_cast<short>(v[1] & 0xFFFFu), static_cast<short>(v[1] >> 16)};
+    for (int j = 0; j < XPER; ++j) {
+      if constexpr (V16) {
+        int pos, ch;
+        item(j, pos, ch);
+        const unsigned o = xoff[j] >= 0 && c0 + ch < a.cin_valid
+                               ? static_cast<unsigned>(xoff[j] + c0) * 2u
+                               : kFarOffset;
+        const auto v = __builtin_amdgcn_raw_buffer_load_b128(bx.r, o, 0, 0);
+        rx[j][0] = uint4{static_cast<unsigned>(v[0]), static_cast<unsigned>(v[1]),
+                         static_cast<unsigned>(v[2]), static_cast<unsigned>(v[3])};
+      } else {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          rx[j][q] = uint2{0, 0};
+          if (c0 + 4 * q < a.cin_valid) {
+            const unsigned o =
+                xoff[j] >= 0 ? static_cast<unsigned>(xoff[j] + c0 + 4 * q) * 2u : kFarOffset;
+            const auto v = __builtin_amdgcn_raw_buffer_load_b64(bx.r, o, 0, 0);
+            rx[j][q] = uint2{static_cast<unsigned>(v[0]), static_cast<unsigned>(v[1])};
+          }
+        }
+      }
     }
 #pragma unroll
-    for (int j = 0; j < kWPer; ++j) {
-      const unsigned o = wrow + 64 * j < kWRows
-                             ? static_cast<unsigned>(wbase + j * wstep + c0) * 2u
-                             : kFarOffset;
-      const auto v = __builtin_amdgcn_raw_buffer_load_b64(bw.r, o, 0, 0);
-      rw[j] = s4{static_cast<short>(v[0] & 0xFFFFu), static_cast<short>(v[0] >> 16),
-                 static_cast<short>(v[1] & 0xFFFFu), static_cast<short>(v[1] >> 16)};
+    for (int j = 0; j < WPER; ++j) {
+      const int it = tid + 256 * j;
+      const int n = it / WC, r = it % WC;
+      const unsigned o =
+          it < WI ? static_cast<unsigned>((((co0 >> 4) + n) * nch + chunk) * WC + r) * 16u
+                  : kFarOffset;
+      const auto v = __builtin_amdgcn_raw_buffer_load_b128(bw.r, o, 0, 0);
+      rw[j] = uint4{static_cast<unsigned>(v[0]), static_cast<unsigned>(v[1]),
+                    static_cast<unsigned>(v[2]), static_cast<unsigned>(v[3])};
     }
   };
   auto commit = [&]() {
-    if (tid < kXThreads) {
 #pragma unroll
-      for (int i = 0; i < kXLoads; ++i)
-        *reinterpret_cast<s4*>(&s_x[sx_base + i * 3 * kCH * kPitch]) = rx[i];
+    for (int j = 0; j < XPER; ++j) {
+      int pos, ch;
+      if (!item(j, pos, ch)) continue;
+      uint16_t* d = s_x + pos * kPitch + ch;
+      if constexpr (V16) {
+        *reinterpret_cast<uint2*>(d) = uint2{rx[j][0].x, rx[j][0].y};
+        *reinterpret_cast<uint2*>(d + 4) = uint2{rx[j][0].z, rx[j][0].w};
+      } else {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) *reinterpret_cast<uint2*>(d + 4 * q) = rx[j][q];
+      }
     }
 #pragma unroll
-    for (int j = 0; j < kWPer; ++j)
-      if (wrow + 64 * j < kWRows)
-        *reinterpret_cast<s4*>(&s_w[(wrow + 64 * j) * kPitch + 4 * q]) = rw[j];
+    for (int j = 0; j < WPER; ++j) {
+      const int it = tid + 256 * j;
+      if (it < WI) *reinterpret_cast<uint4*>(&s_w[it * 8]) = rw[j];
+    }
   };
-  f4 acc[NT][4];
+  f4 acc[NT][RW];
 #pragma unroll
   for (int n = 0; n < NT; ++n)
 #pragma unroll
-    for (int r = 0; r < 4; ++r) acc[n][r] = f4{0.f, 0.f, 0.f, 0.f};
-  // operand bases: halo voxel (m, 4 wv) of plane 0, weight row m of tap 0
-  const int xr_base = (4 * wv * kCH + m) * kPitch + 4 * kq;
-  const int wr_base = m * kPitch + 4 * kq;
+    for (int r = 0; r < RW; ++r) acc[n][r] = f4{0.f, 0.f, 0.f, 0.f};
   fetch(0);
-  for (int c0 = 0; c0 < a.cin_p; c0 += 16) {
+  for (int chunk = 0; chunk < nch; ++chunk) {
     __syncthreads();  // the previous chunk's operands are no longer read
     commit();
     __syncthreads();
-    if (c0 + 16 < a.cin_p) fetch(c0 + 16);  // in flight during this chunk's MFMAs
-#pragma unroll 1
+    if (chunk + 1 < nch) fetch(chunk + 1);  // in flight during this chunk's MFMAs
+#pragma unroll
     for (int dz = 0; dz < 3; ++dz) {
-      const uint16_t* xp = s_x + xr_base + dz * kCH * kCH * kPitch;
-      const uint16_t* wp = s_w + wr_base + dz * 9 * 16 * NT * kPitch;
+      // halo voxel m of rows wy .. wy + RW + 1 of plane wz + dz
+      const uint16_t* xp = s_x + (((wz + dz) * HY + wy) * kCH + m) * kPitch + 4 * kq;
+      const uint16_t* wp = s_w + dz * 9 * 256 + lane * 4;
+      s4 X[RW + 2][3], w[NT][9];
+#pragma unroll
+      for (int n = 0; n < NT; ++n)
+#pragma unroll
+        for (int t = 0; t < 9; ++t)
+          w[n][t] = *reinterpret_cast<const s4*>(wp + (n * 27 + t) * 256);
+#pragma unroll
+      for (int r = 0; r < RW + 2; ++r)
+#pragma unroll
+        for (int dx = 0; dx < 3; ++dx)
+          X[r][dx] = *reinterpret_cast<const s4*>(xp + (r * kCH + dx) * kPitch);
       // taps 2p and 2p + 1 as one K = 32 product (each lane's eight K slots:
       // its four channels of the first tap, then the same four of the
       // second, in both operands); the ninth tap as a K = 16 product
 #pragma unroll
       for (int tp = 0; tp < 4; ++tp) {
         const int ta = 2 * tp, tb = ta + 1;
-        b8 w[NT];
+        b8 wt[NT];
 #pragma unroll
-        for (int n = 0; n < NT; ++n)
-          w[n] = cat_bf16(*reinterpret_cast<const s4*>(wp + (ta * NT + n) * 16 * kPitch),
-                          *reinterpret_cast<const s4*>(wp + (tb * NT + n) * 16 * kPitch));
+        for (int n = 0; n < NT; ++n) wt[n] = cat_bf16(w[n][ta], w[n][tb]);
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const b8 xv = cat_bf16(
-              *reinterpret_cast<const s4*>(xp + ((r + ta / 3) * kCH + ta % 3) * kPitch),
-              *reinterpret_cast<const s4*>(xp + ((r + tb / 3) * kCH + tb % 3) * kPitch));
+        for (int r = 0; r < RW; ++r) {
+          const b8 xv = cat_bf16(X[r + ta / 3][ta % 3], X[r + tb / 3][tb % 3]);
 #pragma unroll
           for (int n = 0; n < NT; ++n)
-            acc[n][r] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[n], xv, acc[n][r], 0, 0, 0);
+            acc[n][r] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wt[n], xv, acc[n][r], 0, 0, 0);
         }
       }
-      {
-        constexpr int t9 = 8, dy = 2, dx = 2;  // halo coordinates of the ninth tap
-        s4 w[NT];
+#pragma unroll
+      for (int r = 0; r < RW; ++r)
 #pragma unroll
         for (int n = 0; n < NT; ++n)
-          w[n] = *reinterpret_cast<const s4*>(wp + (t9 * NT + n) * 16 * kPitch);
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const s4 xv = *reinterpret_cast<const s4*>(xp + ((r + dy) * kCH + dx) * kPitch);
-#pragma unroll
-          for (int n = 0; n < NT; ++n)
-            acc[n][r] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(w[n], xv, acc[n][r], 0, 0, 0);
-        }
-      }
+          acc[n][r] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(w[n][8], X[r + 2][2],
+                                                                acc[n][r], 0, 0, 0);
     }
   }
   // D[4 kq + j][m]: output channel co0 + 16 n + 4 kq + j of voxel x0 + m in
-  // row y0 + 4 wv + r
-  const int x = x0 + m;
-  if (x >= a.nx) return;
-  const bool vec = a.cout % 4 == 0 && a.ldy % 4 == 0 && a.ldf % 4 == 0 &&
+  // row y0 + wy + r of plane z0 + wz
+  const int x = x0 + m, z = z0 + wz;
+  if (x >= a.nx || z >= a.nz) return;
+  const bool vec = a.cout % 4 == 0 && a.ldy % 4 == 0 && a.ldf % 4 == 0 && a.ldm % 4 == 0 &&
                    (reinterpret_cast<uintptr_t>(a.Y) % 8) == 0 &&
+                   (reinterpret_cast<uintptr_t>(a.mask) % 8) == 0 &&
                    (reinterpret_cast<uintptr_t>(a.yf) % 16) == 0;
-  // voxel of row r: v0 + r nx (v0: this lane's voxel in row y0 + 4 wv)
-  const long long v0 = (long long)(z * a.ny + y0 + wv * 4) * a.nx + x;
+  // voxel of row r: v0 + r nx (v0: this lane's voxel in row y0 + wy)
+  const long long v0 = (long long)(z * a.ny + y0 + wy) * a.nx + x;
   uint16_t* const yrow = a.Y ? a.Y + v0 * a.ldy : nullptr;
   float* const frow = a.yf ? a.yf + v0 * a.ldf : nullptr;
-  const long long ystep = (long long)a.nx * a.ldy, fstep = (long long)a.nx * a.ldf;
+  const uint16_t* const mrow = a.mask ? a.mask + v0 * a.ldm : nullptr;
+  const long long ystep = (long long)a.nx * a.ldy, fstep = (long long)a.nx * a.ldf,
+                  mstep = (long long)a.nx * a.ldm;
 #pragma unroll
   for (int n = 0; n < NT; ++n) {
     const int cb = co0 + 16 * n + 4 * kq;
@@ -309,8 +362,8 @@ __global__ void __launch_bounds__(256) k_conv_tile(ConvArgs a) {
 #pragma unroll
     for (int j = 0; j < 4; ++j) bias[j] = (a.bias && cb + j < a.cout) ? a.bias[cb + j] : 0.0f;
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      if (y0 + wv * 4 + r >= a.ny) continue;
+    for (int r = 0; r < RW; ++r) {
+      if (y0 + wy + r >= a.ny) continue;
       float o[4];
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
@@ -318,6 +371,13 @@ __global__ void __launch_bounds__(256) k_conv_tile(ConvArgs a) {
         if (a.relu) o[j] = fmaxf(o[j], 0.0f);
       }
       if (vec) {
+        if (mrow) {
+          const uint2 q = *reinterpret_cast<const uint2*>(mrow + r * mstep + cb);
+          if (!(bf2f(static_cast<uint16_t>(q.x)) > 0.0f)) o[0] = 0.0f;
+          if (!(bf2f(static_cast<uint16_t>(q.x >> 16)) > 0.0f)) o[1] = 0.0f;
+          if (!(bf2f(static_cast<uint16_t>(q.y)) > 0.0f)) o[2] = 0.0f;
+          if (!(bf2f(static_cast<uint16_t>(q.y >> 16)) > 0.0f)) o[3] = 0.0f;
+        }
         if (yrow) {
           const bf2 lo = __builtin_convertvector(f2{o[0], o[1]}, bf2);
           const bf2 hi = __builtin_convertvector(f2{o[2], o[3]}, bf2);
@@ -329,6 +389,7 @@ __global__ void __launch_bounds__(256) k_conv_tile(ConvArgs a) {
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
           if (cb + j >= a.cout) continue;
+          if (mrow && !(bf2f(mrow[r * mstep + cb + j]) > 0.0f)) o[j] = 0.0f;
           if (yrow) yrow[r * ystep + cb + j] = f2bf(o[j]);
           if (frow) frow[r * fstep + cb + j] = o[j];
         }
@@ -802,6 +863,7 @@ __global__ void k_adam(float* __restrict__ p, float* __restrict__ m, float* __re
 
 __global__ void k_pack(const float* __restrict__ W, int cin, int cout, int cin_p,
                        int cout_p, uint16_t* __restrict__ Wf, uint16_t* __restrict__ Wb) {
+  const int nci = cin_p / 16, nco = cout_p / 16;
   const long long n = 27LL * cin_p * cout_p;
   for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < n;
        i += (long long)gridDim.x * blockDim.x) {
@@ -810,8 +872,14 @@ __global__ void k_pack(const float* __restrict__ W, int cin, int cout, int cin_p
     const int ci = r / cout_p, co = r % cout_p;
     const float w = (ci < cin && co < cout) ? W[((long long)t * cin + ci) * cout + co] : 0.0f;
     const uint16_t h = f2bf(w);
-    Wf[((long long)t * cout_p + co) * cin_p + ci] = h;
-    Wb[((long long)(26 - t) * cin_p + ci) * cout_p + co] = h;
+    // element of the operand: quad of the reduction channel, then the output
+    // channel, then the channel within the quad
+    const long long f = (((long long)(co / 16) * nci + ci / 16) * 27 + t) * 256 +
+                        (((ci % 16) / 4) * 16 + co % 16) * 4 + ci % 4;
+    const long long bk = (((long long)(ci / 16) * nco + co / 16) * 27 + (26 - t)) * 256 +
+                         (((co % 16) / 4) * 16 + ci % 16) * 4 + co % 4;
+    Wf[f] = h;
+    Wb[bk] = h;
   }
 }
 
@@ -841,22 +909,40 @@ long long wgrad_chunks(int cin_p, int cout_p, int nz, int ny, int nx) {
 
 }  // namespace
 
+namespace {
+
+template <int RW, int WZ>
+long long conv_tiles(const ConvArgs& a) {
+  constexpr int TY = RW * (4 / WZ);
+  return (long long)((a.nx + kCT - 1) / kCT) * ((a.ny + TY - 1) / TY) *
+         ((a.nz + WZ - 1) / WZ);
+}
+
+template <int NT, int RW, int WZ>
+hipError_t conv_tile(const ConvArgs& a, hipStream_t s) {
+  const dim3 grid(static_cast<unsigned>(conv_tiles<RW, WZ>(a) * (a.cout_p / (16 * NT))));
+  if (a.ldx % 8 || a.cin_valid % 8 || (reinterpret_cast<uintptr_t>(a.X) % 16))
+    hipLaunchKernelGGL((k_conv_tile<NT, RW, WZ, false>), grid, dim3(256), 0, s, a);
+  else
+    hipLaunchKernelGGL((k_conv_tile<NT, RW, WZ, true>), grid, dim3(256), 0, s, a);
+  return hipGetLastError();
+}
+
+}  // namespace
+
 hipError_t unet_conv(const ConvArgs& a, hipStream_t s) {
   const long long tile_bytes =
       ((long long)a.nz * a.ny * a.nx * a.ldx + ((a.cin_valid + 3) & ~3)) * 2;
   if (a.ldx % 4 == 0 && (reinterpret_cast<uintptr_t>(a.X) % 8) == 0 &&
       tile_bytes < static_cast<long long>(kFarOffset) - 16) {
-    // 32 output channels per block where the layer has them: each input
-    // operand read from LDS then feeds two MFMAs
-    const int nt = a.cout_p % 32 == 0 ? 2 : 1;
-    const long long nb = (long long)((a.nx + kCT - 1) / kCT) * ((a.ny + kCT - 1) / kCT) *
-                         a.nz * (a.cout_p / (16 * nt));
-    const dim3 grid(static_cast<unsigned>(nb));
-    if (nt == 2)
-      hipLaunchKernelGGL(k_conv_tile<2>, grid, dim3(256), 0, s, a);
-    else
-      hipLaunchKernelGGL(k_conv_tile<1>, grid, dim3(256), 0, s, a);
-    return hipGetLastError();
+    // 32 output channels per block where the layer has them and that still
+    // gives every compute unit a block: an input operand then feeds two
+    // MFMAs and the halo is staged half as often (40x48x56, 96 -> 32: 31 us,
+    // 36 us with 16); the coarser levels have too few tiles for it
+    // (20x24x28, 192 -> 64: 31 us, 24 us with 16).
+    if (a.cout_p % 32 == 0 && conv_tiles<4, 4>(a) * (a.cout_p / 32) >= device_cus())
+      return conv_tile<2, 4, 4>(a, s);
+    return conv_tile<1, 4, 4>(a, s);
   }
   dim3 grid((a.nx + 63) / 64, a.ny, a.nz * (a.cout_p / 16));
   const bool k32 = a.cin_p % 32 == 0 && a.ldx % 8 == 0 && a.cin_valid % 8 == 0 &&

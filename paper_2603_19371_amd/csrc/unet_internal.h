@@ -12,9 +12,12 @@ namespace lmr {
 //   X: input, element (v, c) at X[v*ldx + c]; channels [0, cin_valid) are used
 //      and the 4-channel group holding cin_valid-1 is read whole (the
 //      channels of that group past cin_valid must be finite).
-//   W: packed BF16 weights [27][cout_p][cin_p].
+//   W: packed BF16 weights (k_unet.hip), 27 cout_p cin_p elements.
 //   bias (FP32, may be NULL), relu: epilogue y = act(acc + bias).
 //   Y (BF16, may be NULL) and yf (FP32, may be NULL): outputs, stride ldy / ldf.
+//   mask (BF16, may be NULL), stride ldm: an output whose mask value is not
+//     positive is written as 0 (the gradient through the ReLU whose
+//     activations the mask holds).
 // Requirements (checked by the caller): ldx, and the element offset of X, are
 // multiples of 4; cin_p, cout_p multiples of 16.
 struct ConvArgs {
@@ -29,6 +32,8 @@ struct ConvArgs {
   int ldf;
   int nz, ny, nx;
   int relu;
+  const uint16_t* mask;
+  int ldm;
 };
 hipError_t unet_conv(const ConvArgs& a, hipStream_t s);
 
@@ -77,8 +82,8 @@ hipError_t unet_zero(uint16_t* p, long long n, hipStream_t s);
 hipError_t unet_adam(float* p, float* m, float* v, const float* g, long long n, float lr,
                      float b1, float b2, float eps, float c1, float c2, float gscale,
                      hipStream_t s);
-// W [27][cin][cout] FP32 -> Wf [27][cout_p][cin_p] and the tap-reversed,
-// transposed Wb [27][cin_p][cout_p] (BF16, zero padded).
+// W [27][cin][cout] FP32 -> the packs of the forward convolution and of the
+// gradient with respect to the input (BF16, zero padded, k_unet.hip).
 hipError_t unet_pack(const float* W, int cin, int cout, int cin_p, int cout_p,
                      uint16_t* Wf, uint16_t* Wb, hipStream_t s);
 
