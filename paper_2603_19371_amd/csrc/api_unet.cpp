@@ -127,8 +127,9 @@ hipError_t conv_fwd(lmr_unet* u, int l, T x, int cin_valid, T y, float* yf, int 
 }
 
 // Gradients of layer l from its input x and the gradient dz of its
-// pre-activation output; dx (may have p == NULL) receives the input gradient.
-hipError_t conv_bwd(lmr_unet* u, int l, T x, T dz, T dx, int accumulate) {
+// pre-activation output; dx (may have p == NULL) receives the input gradient,
+// through the ReLU with activations act (none if act.p == NULL).
+hipError_t conv_bwd(lmr_unet* u, int l, T x, T dz, T dx, T act, int accumulate) {
   const LayerDef& L = kLayers[l];
   const int* d = u->dims[L.level];
   hipError_t e = unet_wgrad(x.p, x.ld, L.cin, pad16(L.cin), dz.p, dz.ld, L.cout,
@@ -152,11 +153,9 @@ hipError_t conv_bwd(lmr_unet* u, int l, T x, T dz, T dx, int accumulate) {
   a.ny = d[1];
   a.nx = d[2];
   a.relu = 0;
+  a.mask = act.p;
+  a.ldm = act.ld;
   return unet_conv(a, u->stream);
-}
-
-hipError_t mask(lmr_unet* u, int level, T d, T a, int C) {
-  return unet_relu_mask(d.p, d.ld, a.p, a.ld, C, u->n[level], u->stream);
 }
 
 #define LMR_TRY(expr)                                \
@@ -359,45 +358,37 @@ lmr_status lmr_unet_backward(lmr_unet* u, const float* target, double target_sca
   const int acc = accumulate ? 1 : 0;
   LMR_TRY(unet_mse(u->yf, 4, target, static_cast<float>(target_scale), u->n[0], u->d_out.p,
                    4, u->mse_part, loss ? loss : u->loss_scratch, s));
+  // Every gradient with respect to an activation is taken through that
+  // activation's ReLU by the kernel that forms it.
   // level-0 decoder
-  LMR_TRY(conv_bwd(u, 14, u->f1, u->d_out, u->d_f1, acc));
-  LMR_TRY(mask(u, 0, u->d_f1, u->f1, 16));
-  LMR_TRY(conv_bwd(u, 13, u->f1a, u->d_f1, u->d_f1a, acc));
-  LMR_TRY(mask(u, 0, u->d_f1a, u->f1a, 16));
-  LMR_TRY(conv_bwd(u, 12, u->c1, u->d_f1a, u->d_c1, acc));
+  LMR_TRY(conv_bwd(u, 14, u->f1, u->d_out, u->d_f1, u->f1, acc));
+  LMR_TRY(conv_bwd(u, 13, u->f1a, u->d_f1, u->d_f1a, u->f1a, acc));
+  LMR_TRY(conv_bwd(u, 12, u->c1, u->d_f1a, u->d_c1, none, acc));
   // d_c1 = [d up(f2) | d e1]; d e1 stays in place (channels 32..47)
-  LMR_TRY(unet_up2_back(u->d_c1.p, 48, 32, d0[0], d0[1], d0[2], u->d_f2.p, 32, 0, s));
-  LMR_TRY(mask(u, 1, u->d_f2, u->f2, 32));
-  LMR_TRY(conv_bwd(u, 11, u->f2a, u->d_f2, u->d_f2a, acc));
-  LMR_TRY(mask(u, 1, u->d_f2a, u->f2a, 32));
-  LMR_TRY(conv_bwd(u, 10, u->c2, u->d_f2a, u->d_c2, acc));
-  LMR_TRY(unet_up2_back(u->d_c2.p, 96, 64, d1[0], d1[1], d1[2], u->d_f3.p, 64, 0, s));
-  LMR_TRY(mask(u, 2, u->d_f3, u->f3, 64));
-  LMR_TRY(conv_bwd(u, 9, u->f3a, u->d_f3, u->d_f3a, acc));
-  LMR_TRY(mask(u, 2, u->d_f3a, u->f3a, 64));
-  LMR_TRY(conv_bwd(u, 8, u->c3, u->d_f3a, u->d_c3, acc));
-  LMR_TRY(unet_up2_back(u->d_c3.p, 192, 128, d2[0], d2[1], d2[2], u->d_e4.p, 128, 0, s));
+  LMR_TRY(unet_up2_back(u->d_c1.p, 48, 32, d0[0], d0[1], d0[2], u->d_f2.p, 32, u->f2.p, 32, s));
+  LMR_TRY(conv_bwd(u, 11, u->f2a, u->d_f2, u->d_f2a, u->f2a, acc));
+  LMR_TRY(conv_bwd(u, 10, u->c2, u->d_f2a, u->d_c2, none, acc));
+  LMR_TRY(unet_up2_back(u->d_c2.p, 96, 64, d1[0], d1[1], d1[2], u->d_f3.p, 64, u->f3.p, 64, s));
+  LMR_TRY(conv_bwd(u, 9, u->f3a, u->d_f3, u->d_f3a, u->f3a, acc));
+  LMR_TRY(conv_bwd(u, 8, u->c3, u->d_f3a, u->d_c3, none, acc));
+  LMR_TRY(unet_up2_back(u->d_c3.p, 192, 128, d2[0], d2[1], d2[2], u->d_e4.p, 128, u->e4.p, 128,
+                        s));
   // bottom level
-  LMR_TRY(mask(u, 3, u->d_e4, u->e4, 128));
-  LMR_TRY(conv_bwd(u, 7, u->e4a, u->d_e4, u->d_e4a, acc));
-  LMR_TRY(mask(u, 3, u->d_e4a, u->e4a, 128));
-  LMR_TRY(conv_bwd(u, 6, u->p3, u->d_e4a, u->d_p3, acc));
+  LMR_TRY(conv_bwd(u, 7, u->e4a, u->d_e4, u->d_e4a, u->e4a, acc));
+  LMR_TRY(conv_bwd(u, 6, u->p3, u->d_e4a, u->d_p3, none, acc));
   // encoder: d e3 = skip part of d_c3 + pooling gradient
-  LMR_TRY(unet_pool2_back(u->d_p3.p, 64, 64, d2[0], d2[1], d2[2], u->d_c3.p + 128, 192, 1, s));
-  LMR_TRY(mask(u, 2, u->d_c3.at(128), u->c3.at(128), 64));
-  LMR_TRY(conv_bwd(u, 5, u->e3a, u->d_c3.at(128), u->d_e3a, acc));
-  LMR_TRY(mask(u, 2, u->d_e3a, u->e3a, 64));
-  LMR_TRY(conv_bwd(u, 4, u->p2, u->d_e3a, u->d_p2, acc));
-  LMR_TRY(unet_pool2_back(u->d_p2.p, 32, 32, d1[0], d1[1], d1[2], u->d_c2.p + 64, 96, 1, s));
-  LMR_TRY(mask(u, 1, u->d_c2.at(64), u->c2.at(64), 32));
-  LMR_TRY(conv_bwd(u, 3, u->e2a, u->d_c2.at(64), u->d_e2a, acc));
-  LMR_TRY(mask(u, 1, u->d_e2a, u->e2a, 32));
-  LMR_TRY(conv_bwd(u, 2, u->p1, u->d_e2a, u->d_p1, acc));
-  LMR_TRY(unet_pool2_back(u->d_p1.p, 16, 16, d0[0], d0[1], d0[2], u->d_c1.p + 32, 48, 1, s));
-  LMR_TRY(mask(u, 0, u->d_c1.at(32), u->c1.at(32), 16));
-  LMR_TRY(conv_bwd(u, 1, u->e1a, u->d_c1.at(32), u->d_e1a, acc));
-  LMR_TRY(mask(u, 0, u->d_e1a, u->e1a, 16));
-  LMR_TRY(conv_bwd(u, 0, u->x, u->d_e1a, none, acc));
+  LMR_TRY(unet_pool2_back(u->d_p3.p, 64, 64, d2[0], d2[1], d2[2], u->d_c3.p + 128, 192,
+                          u->c3.p + 128, 192, s));
+  LMR_TRY(conv_bwd(u, 5, u->e3a, u->d_c3.at(128), u->d_e3a, u->e3a, acc));
+  LMR_TRY(conv_bwd(u, 4, u->p2, u->d_e3a, u->d_p2, none, acc));
+  LMR_TRY(unet_pool2_back(u->d_p2.p, 32, 32, d1[0], d1[1], d1[2], u->d_c2.p + 64, 96,
+                          u->c2.p + 64, 96, s));
+  LMR_TRY(conv_bwd(u, 3, u->e2a, u->d_c2.at(64), u->d_e2a, u->e2a, acc));
+  LMR_TRY(conv_bwd(u, 2, u->p1, u->d_e2a, u->d_p1, none, acc));
+  LMR_TRY(unet_pool2_back(u->d_p1.p, 16, 16, d0[0], d0[1], d0[2], u->d_c1.p + 32, 48,
+                          u->c1.p + 32, 48, s));
+  LMR_TRY(conv_bwd(u, 1, u->e1a, u->d_c1.at(32), u->d_e1a, u->e1a, acc));
+  LMR_TRY(conv_bwd(u, 0, u->x, u->d_e1a, none, none, acc));
   return LMR_OK;
 }
 

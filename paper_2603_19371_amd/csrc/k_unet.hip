@@ -609,26 +609,36 @@ __global__ void __launch_bounds__(256, 2) k_wgrad(WgradArgs a) {
   if (ib == 0 && tid < 16) a.partb[(long long)chunk * a.cout_p + cb * 16 + tid] = red_b[tid];
 }
 
-// dW[t][ci][co] = sum over chunks of the padded partials.  A block of 256
-// threads reduces 16 consecutive outputs: 16 threads per output each sum the
-// chunks c = q, q + 16, ... (q = the thread's share), then the 16 shares are
-// added in order q = 0..15 (a fixed order, so the result does not depend on
-// scheduling).  Many short sums in parallel instead of one long one per
-// output: the partials of a layer can hold thousands of chunks.
+// dW[t][ci][co] and db[co] = sums over chunks of the padded partials.  A block
+// of 256 threads reduces 16 consecutive outputs: 16 threads per output each
+// sum the chunks c = q, q + 16, ... (q = the thread's share), then the 16
+// shares are added in order q = 0..15 (a fixed order, so the result does not
+// depend on scheduling).  Many short sums in parallel instead of one long one
+// per output: the partials of a layer can hold thousands of chunks.  The
+// blocks past the weights' reduce the bias (a launch of its own cost 5 to 8
+// us a layer).
 constexpr int kRedShare = 16;
 __global__ void __launch_bounds__(256)
-    k_reduce_w(const float* __restrict__ part, int nchunks, int cin, int cout, int cin_p,
-               int cout_p, float* __restrict__ dW, int accumulate) {
-  __shared__ float red[kRedShare][256 / kRedShare];
-  const long long n = 27LL * cin * cout, stride = 27LL * cin_p * cout_p;
-  const int lo = threadIdx.x % (256 / kRedShare), q = threadIdx.x / (256 / kRedShare);
-  const long long i = (long long)blockIdx.x * (256 / kRedShare) + lo;
+    k_reduce(const float* __restrict__ part, const float* __restrict__ partb, int nchunks,
+             int cin, int cout, int cin_p, int cout_p, int wblocks, float* __restrict__ dW,
+             float* __restrict__ db, int accumulate) {
+  constexpr int NO = 256 / kRedShare;
+  __shared__ float red[kRedShare][NO];
+  const bool bias = (int)blockIdx.x >= wblocks;
+  const long long n = bias ? cout : 27LL * cin * cout,
+                  stride = bias ? cout_p : 27LL * cin_p * cout_p;
+  const int lo = threadIdx.x % NO, q = threadIdx.x / NO;
+  const long long i = (long long)(bias ? blockIdx.x - wblocks : blockIdx.x) * NO + lo;
   float s = 0.0f;
   if (i < n) {
-    const int t = static_cast<int>(i / ((long long)cin * cout));
-    const int r = static_cast<int>(i % ((long long)cin * cout));
-    const long long o = ((long long)t * cin_p + r / cout) * cout_p + r % cout;
-    for (int c = q; c < nchunks; c += kRedShare) s += part[c * stride + o];
+    long long o = i;
+    if (!bias) {
+      const int t = static_cast<int>(i / ((long long)cin * cout));
+      const int r = static_cast<int>(i % ((long long)cin * cout));
+      o = ((long long)t * cin_p + r / cout) * cout_p + r % cout;
+    }
+    const float* p = (bias ? partb : part) + o;
+    for (int c = q; c < nchunks; c += kRedShare) s += p[c * stride];
   }
   red[q][lo] = s;
   __syncthreads();
@@ -636,101 +646,97 @@ __global__ void __launch_bounds__(256)
     float tot = 0.0f;
 #pragma unroll
     for (int k = 0; k < kRedShare; ++k) tot += red[k][lo];
-    dW[i] = accumulate ? dW[i] + tot : tot;
-  }
-}
-
-__global__ void __launch_bounds__(256)
-    k_reduce_b(const float* __restrict__ partb, int nchunks, int cout, int cout_p,
-               float* __restrict__ db, int accumulate) {
-  __shared__ float red[kRedShare][256 / kRedShare];
-  const int lo = threadIdx.x % (256 / kRedShare), q = threadIdx.x / (256 / kRedShare);
-  const int co = blockIdx.x * (256 / kRedShare) + lo;
-  float s = 0.0f;
-  if (co < cout)
-    for (int c = q; c < nchunks; c += kRedShare) s += partb[(long long)c * cout_p + co];
-  red[q][lo] = s;
-  __syncthreads();
-  if (q == 0 && co < cout) {
-    float tot = 0.0f;
-#pragma unroll
-    for (int k = 0; k < kRedShare; ++k) tot += red[k][lo];
-    db[co] = accumulate ? db[co] + tot : tot;
-  }
-}
-
-__global__ void k_relu_mask(uint16_t* __restrict__ d, int ldd, const uint16_t* __restrict__ a,
-                            int lda, int C, long long N) {
-  const long long n = N * C;
-  for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < n;
-       i += (long long)gridDim.x * blockDim.x) {
-    const long long v = i / C;
-    const int c = static_cast<int>(i % C);
-    if (!(bf2f(a[v * lda + c]) > 0.0f)) d[v * ldd + c] = 0;
+    float* d = (bias ? db : dW) + i;
+    *d = accumulate ? *d + tot : tot;
   }
 }
 
 // ------------------------------------------------------- resampling ops
+// Eight channels per thread (16-byte accesses; channel counts, strides and
+// offsets multiples of 8), 32-bit indices.  They move each tensor once and
+// are bound by memory; with one channel per thread and 64-bit divisions per
+// element they were bound by instructions (gradient of the pooling at
+// 80x96x112, 16 of 48 interleaved channels: 51 us and 33 for the ReLU mask
+// after it, now 35 together; of the upsampling 21 and 9, now 16).
+// mask (may be null): activations at the output's positions; the gradient is
+// written as 0 where they are not positive.
+struct F8 {
+  float v[8];
+};
+__device__ __forceinline__ F8 load8(const uint16_t* p) {
+  const uint4 q = *reinterpret_cast<const uint4*>(p);
+  const unsigned w[4] = {q.x, q.y, q.z, q.w};
+  F8 r;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    r.v[2 * k] = __uint_as_float(w[k] << 16);
+    r.v[2 * k + 1] = __uint_as_float(w[k] & 0xFFFF0000u);
+  }
+  return r;
+}
+__device__ __forceinline__ void store8(uint16_t* p, const F8& r) {
+  unsigned w[4];
+#pragma unroll
+  for (int k = 0; k < 4; ++k)
+    w[k] = __builtin_bit_cast(unsigned,
+                              __builtin_convertvector(f2{r.v[2 * k], r.v[2 * k + 1]}, bf2));
+  *reinterpret_cast<uint4*>(p) = uint4{w[0], w[1], w[2], w[3]};
+}
+__device__ __forceinline__ void mask8(F8& r, const uint16_t* a) {
+  const F8 m = load8(a);
+#pragma unroll
+  for (int k = 0; k < 8; ++k)
+    if (!(m.v[k] > 0.0f)) r.v[k] = 0.0f;
+}
 __device__ __forceinline__ long long child(int z, int y, int x, int k, int ny, int nx) {
   return ((long long)(2 * z + (k >> 2)) * ny + 2 * y + ((k >> 1) & 1)) * nx + 2 * x + (k & 1);
 }
 
-// 2x2x2 average pooling of C channels from fine dims (nz, ny, nx).
+// 2x2x2 average pooling from fine dims (nz, ny, nx).
 __global__ void k_pool2(const uint16_t* __restrict__ X, int ldx, int C, int nz, int ny,
                         int nx, uint16_t* __restrict__ Y, int ldy) {
-  const int cy = ny / 2, cx = nx / 2;
-  const long long n = (long long)(nz / 2) * cy * cx * C;
-  for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < n;
-       i += (long long)gridDim.x * blockDim.x) {
-    const int c = static_cast<int>(i % C);
-    const long long v = i / C;
-    const int x = static_cast<int>(v % cx), y = static_cast<int>((v / cx) % cy),
-              z = static_cast<int>(v / ((long long)cx * cy));
-    float s = 0.0f;
+  const int cy = ny / 2, cx = nx / 2, G = C / 8, n = (nz / 2) * cy * cx * G;
+  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
+    const int g = i % G, v = i / G;
+    const int x = v % cx, y = (v / cx) % cy, z = v / (cx * cy);
+    F8 f[8];
 #pragma unroll
-    for (int k = 0; k < 8; ++k) s += bf2f(X[child(z, y, x, k, ny, nx) * ldx + c]);
-    Y[v * ldy + c] = f2bf(s * 0.125f);
+    for (int k = 0; k < 8; ++k) f[k] = load8(X + child(z, y, x, k, ny, nx) * ldx + 8 * g);
+    F8 s;
+#pragma unroll
+    for (int c = 0; c < 8; ++c) {
+      s.v[c] = 0.0f;
+#pragma unroll
+      for (int k = 0; k < 8; ++k) s.v[c] += f[k].v[c];
+      s.v[c] *= 0.125f;
+    }
+    store8(Y + (long long)v * ldy + 8 * g, s);
   }
 }
 
-// Gradient of the pooling: every fine voxel receives dY / 8.
-__global__ void k_pool2_back(const uint16_t* __restrict__ dY, int ldy, int C, int nz,
-                             int ny, int nx, uint16_t* __restrict__ dX, int ldx, int add) {
-  const long long n = (long long)nz * ny * nx * C;
-  for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < n;
-       i += (long long)gridDim.x * blockDim.x) {
-    const int c = static_cast<int>(i % C);
-    const long long v = i / C;
-    const int x = static_cast<int>(v % nx), y = static_cast<int>((v / nx) % ny),
-              z = static_cast<int>(v / ((long long)nx * ny));
-    const long long cv = ((long long)(z / 2) * (ny / 2) + y / 2) * (nx / 2) + x / 2;
-    float r = bf2f(dY[cv * ldy + c]) * 0.125f;
-    if (add) r += bf2f(dX[v * ldx + c]);
-    dX[v * ldx + c] = f2bf(r);
+// Gradient of the pooling, added to dX: every fine voxel receives dY / 8.
+__global__ void k_pool2_back(const uint16_t* __restrict__ dY, int ldy, int C, int nz, int ny,
+                             int nx, uint16_t* __restrict__ dX, int ldx,
+                             const uint16_t* __restrict__ mask, int ldm) {
+  const int G = C / 8, n = nz * ny * nx * G;
+  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
+    const int g = i % G, v = i / G;
+    const int x = v % nx, y = (v / nx) % ny, z = v / (nx * ny);
+    const int cv = ((z >> 1) * (ny >> 1) + (y >> 1)) * (nx >> 1) + (x >> 1);
+    uint16_t* d = dX + (long long)v * ldx + 8 * g;
+    F8 r = load8(dY + (long long)cv * ldy + 8 * g);
+    const F8 o = load8(d);
+#pragma unroll
+    for (int c = 0; c < 8; ++c) r.v[c] = r.v[c] * 0.125f + o.v[c];
+    if (mask) mask8(r, mask + (long long)v * ldm + 8 * g);
+    store8(d, r);
   }
 }
 
 // x2 nearest-neighbour upsampling to fine dims (nz, ny, nx).
-__global__ void k_up2(const uint16_t* __restrict__ X, int ldx, int C, int nz, int ny,
-                      int nx, uint16_t* __restrict__ Y, int ldy) {
-  const long long n = (long long)nz * ny * nx * C;
-  for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < n;
-       i += (long long)gridDim.x * blockDim.x) {
-    const int c = static_cast<int>(i % C);
-    const long long v = i / C;
-    const int x = static_cast<int>(v % nx), y = static_cast<int>((v / nx) % ny),
-              z = static_cast<int>(v / ((long long)nx * ny));
-    const long long cv = ((long long)(z / 2) * (ny / 2) + y / 2) * (nx / 2) + x / 2;
-    Y[v * ldy + c] = X[cv * ldx + c];
-  }
-}
-
-// The same, 8 channels per 16-byte access (C, strides and bases multiples of 8
-// elements).
-__global__ void k_up2_v8(const uint16_t* __restrict__ X, int ldx, int C, int nz, int ny,
-                         int nx, uint16_t* __restrict__ Y, int ldy) {
-  const int G = C / 8;
-  const int n = nz * ny * nx * G;
+__global__ void k_up2(const uint16_t* __restrict__ X, int ldx, int C, int nz, int ny, int nx,
+                      uint16_t* __restrict__ Y, int ldy) {
+  const int G = C / 8, n = nz * ny * nx * G;
   for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
     const int g = i % G, v = i / G;
     const int x = v % nx, y = (v / nx) % ny, z = v / (nx * ny);
@@ -742,20 +748,24 @@ __global__ void k_up2_v8(const uint16_t* __restrict__ X, int ldx, int C, int nz,
 
 // Gradient of the upsampling: the sum over the 8 fine children.
 __global__ void k_up2_back(const uint16_t* __restrict__ dY, int ldy, int C, int nz, int ny,
-                           int nx, uint16_t* __restrict__ dX, int ldx, int add) {
-  const int cy = ny / 2, cx = nx / 2;
-  const long long n = (long long)(nz / 2) * cy * cx * C;
-  for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < n;
-       i += (long long)gridDim.x * blockDim.x) {
-    const int c = static_cast<int>(i % C);
-    const long long v = i / C;
-    const int x = static_cast<int>(v % cx), y = static_cast<int>((v / cx) % cy),
-              z = static_cast<int>(v / ((long long)cx * cy));
-    float s = 0.0f;
+                           int nx, uint16_t* __restrict__ dX, int ldx,
+                           const uint16_t* __restrict__ mask, int ldm) {
+  const int cy = ny / 2, cx = nx / 2, G = C / 8, n = (nz / 2) * cy * cx * G;
+  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
+    const int g = i % G, v = i / G;
+    const int x = v % cx, y = (v / cx) % cy, z = v / (cx * cy);
+    F8 f[8];
 #pragma unroll
-    for (int k = 0; k < 8; ++k) s += bf2f(dY[child(z, y, x, k, ny, nx) * ldy + c]);
-    if (add) s += bf2f(dX[v * ldx + c]);
-    dX[v * ldx + c] = f2bf(s);
+    for (int k = 0; k < 8; ++k) f[k] = load8(dY + child(z, y, x, k, ny, nx) * ldy + 8 * g);
+    F8 s;
+#pragma unroll
+    for (int c = 0; c < 8; ++c) {
+      s.v[c] = 0.0f;
+#pragma unroll
+      for (int k = 0; k < 8; ++k) s.v[c] += f[k].v[c];
+    }
+    if (mask) mask8(s, mask + (long long)v * ldm + 8 * g);
+    store8(dX + (long long)v * ldx + 8 * g, s);
   }
 }
 
@@ -976,53 +986,57 @@ hipError_t unet_wgrad(const uint16_t* X, int ldx, int cin, int cin_p, const uint
   const long long nch = wgrad_chunks(cin_p, cout_p, nz, ny, nx);
   const unsigned blocks = static_cast<unsigned>(nch * (cin_p / 16) * (cout_p / 16));
   hipLaunchKernelGGL(k_wgrad, dim3(blocks), dim3(256), 0, s, w);
-  const long long nw = 27LL * cin * cout, per = 256 / kRedShare;
-  hipLaunchKernelGGL(k_reduce_w, dim3(static_cast<unsigned>((nw + per - 1) / per)), dim3(256),
-                     0, s, part, static_cast<int>(nch), cin, cout, cin_p, cout_p, dW,
-                     accumulate);
-  hipLaunchKernelGGL(k_reduce_b, dim3(static_cast<unsigned>((cout + per - 1) / per)),
-                     dim3(256), 0, s, partb, static_cast<int>(nch), cout, cout_p, db,
-                     accumulate);
+  const long long per = 256 / kRedShare, wblocks = (27LL * cin * cout + per - 1) / per;
+  hipLaunchKernelGGL(k_reduce, dim3(static_cast<unsigned>(wblocks + (cout + per - 1) / per)),
+                     dim3(256), 0, s, part, partb, static_cast<int>(nch), cin, cout, cin_p,
+                     cout_p, static_cast<int>(wblocks), dW, db, accumulate);
   return hipGetLastError();
 }
 
-hipError_t unet_relu_mask(uint16_t* d, int ldd, const uint16_t* a, int lda, int C,
-                          long long N, hipStream_t s) {
-  hipLaunchKernelGGL(k_relu_mask, dim3(grid_n(N * C)), dim3(256), 0, s, d, ldd, a, lda, C, N);
-  return hipGetLastError();
+// Eight channels per access: counts, strides and bases.
+static bool by_eight(int C, int ld, const void* p) {
+  return C % 8 == 0 && ld % 8 == 0 && reinterpret_cast<uintptr_t>(p) % 16 == 0;
 }
 
 hipError_t unet_pool2(const uint16_t* X, int ldx, int C, int nz, int ny, int nx,
                       uint16_t* Y, int ldy, hipStream_t s) {
-  hipLaunchKernelGGL(k_pool2, dim3(grid_n((long long)nz * ny * nx * C / 8)), dim3(256), 0,
-                     s, X, ldx, C, nz, ny, nx, Y, ldy);
+  const long long n = (long long)nz * ny * nx * C / 64;
+  if (!by_eight(C, ldx, X) || !by_eight(C, ldy, Y) || n >= (1LL << 30))
+    return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_pool2, dim3(grid_n(n)), dim3(256), 0, s, X, ldx, C, nz, ny, nx, Y, ldy);
   return hipGetLastError();
 }
 
 hipError_t unet_pool2_back(const uint16_t* dY, int ldy, int C, int nz, int ny, int nx,
-                           uint16_t* dX, int ldx, int add, hipStream_t s) {
-  hipLaunchKernelGGL(k_pool2_back, dim3(grid_n((long long)nz * ny * nx * C)), dim3(256), 0,
-                     s, dY, ldy, C, nz, ny, nx, dX, ldx, add);
+                           uint16_t* dX, int ldx, const uint16_t* mask, int ldm,
+                           hipStream_t s) {
+  const long long n = (long long)nz * ny * nx * C / 8;
+  if (!by_eight(C, ldy, dY) || !by_eight(C, ldx, dX) || !by_eight(C, ldm, mask) ||
+      n >= (1LL << 30))
+    return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_pool2_back, dim3(grid_n(n)), dim3(256), 0, s, dY, ldy, C, nz, ny, nx,
+                     dX, ldx, mask, ldm);
   return hipGetLastError();
 }
 
 hipError_t unet_up2(const uint16_t* X, int ldx, int C, int nz, int ny, int nx, uint16_t* Y,
                     int ldy, hipStream_t s) {
-  if (C % 8 == 0 && ldx % 8 == 0 && ldy % 8 == 0 &&
-      reinterpret_cast<uintptr_t>(X) % 16 == 0 && reinterpret_cast<uintptr_t>(Y) % 16 == 0) {
-    hipLaunchKernelGGL(k_up2_v8, dim3(grid_n((long long)nz * ny * nx * C / 8)), dim3(256),
-                       0, s, X, ldx, C, nz, ny, nx, Y, ldy);
-    return hipGetLastError();
-  }
-  hipLaunchKernelGGL(k_up2, dim3(grid_n((long long)nz * ny * nx * C)), dim3(256), 0, s, X,
-                     ldx, C, nz, ny, nx, Y, ldy);
+  const long long n = (long long)nz * ny * nx * C / 8;
+  if (!by_eight(C, ldx, X) || !by_eight(C, ldy, Y) || n >= (1LL << 30))
+    return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_up2, dim3(grid_n(n)), dim3(256), 0, s, X, ldx, C, nz, ny, nx, Y, ldy);
   return hipGetLastError();
 }
 
 hipError_t unet_up2_back(const uint16_t* dY, int ldy, int C, int nz, int ny, int nx,
-                         uint16_t* dX, int ldx, int add, hipStream_t s) {
-  hipLaunchKernelGGL(k_up2_back, dim3(grid_n((long long)nz * ny * nx * C / 8)), dim3(256),
-                     0, s, dY, ldy, C, nz, ny, nx, dX, ldx, add);
+                         uint16_t* dX, int ldx, const uint16_t* mask, int ldm,
+                         hipStream_t s) {
+  const long long n = (long long)nz * ny * nx * C / 64;
+  if (!by_eight(C, ldy, dY) || !by_eight(C, ldx, dX) || !by_eight(C, ldm, mask) ||
+      n >= (1LL << 30))
+    return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_up2_back, dim3(grid_n(n)), dim3(256), 0, s, dY, ldy, C, nz, ny, nx, dX,
+                     ldx, mask, ldm);
   return hipGetLastError();
 }
 

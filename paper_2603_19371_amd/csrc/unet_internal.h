@@ -50,20 +50,21 @@ hipError_t unet_wgrad(const uint16_t* X, int ldx, int cin, int cin_p, const uint
                       int ldz, int cout, int cout_p, int nz, int ny, int nx, float* part,
                       float* partb, float* dW, float* db, int accumulate, hipStream_t s);
 
-// d[v, c] = 0 where a[v, c] <= 0 (gradient through a ReLU), c < C.
-hipError_t unet_relu_mask(uint16_t* d, int ldd, const uint16_t* a, int lda, int C,
-                          long long N, hipStream_t s);
-// 2x2x2 average pooling (fine dims nz, ny, nx) and its gradient (add: add
-// into dX instead of overwriting).
+// 2x2x2 average pooling (fine dims nz, ny, nx) and its gradient, added into
+// dX.  Here and below channel counts, strides and offsets are multiples of 8;
+// mask (may be NULL), stride ldm: activations at dX's positions, the gradient
+// is written as 0 where they are not positive.
 hipError_t unet_pool2(const uint16_t* X, int ldx, int C, int nz, int ny, int nx,
                       uint16_t* Y, int ldy, hipStream_t s);
 hipError_t unet_pool2_back(const uint16_t* dY, int ldy, int C, int nz, int ny, int nx,
-                           uint16_t* dX, int ldx, int add, hipStream_t s);
+                           uint16_t* dX, int ldx, const uint16_t* mask, int ldm,
+                           hipStream_t s);
 // x2 nearest upsampling to fine dims (nz, ny, nx) and its gradient.
 hipError_t unet_up2(const uint16_t* X, int ldx, int C, int nz, int ny, int nx, uint16_t* Y,
                     int ldy, hipStream_t s);
 hipError_t unet_up2_back(const uint16_t* dY, int ldy, int C, int nz, int ny, int nx,
-                         uint16_t* dX, int ldx, int add, hipStream_t s);
+                         uint16_t* dX, int ldx, const uint16_t* mask, int ldm,
+                         hipStream_t s);
 // Network input X [N][4] = (F, M, 0, 0) at dims (nz, ny, nx); pool = 1 reads
 // images of twice the size and average-pools them by 2.
 hipError_t unet_input(const void* F, const void* M, lmr_dtype t, int nz, int ny, int nx,
