@@ -402,23 +402,27 @@ __global__ void __launch_bounds__(256) k_conv_tile(ConvArgs a) {
 // of z planes.  A block of four waves takes one brick, one tile of 16 input
 // channels and one tile of 16 output channels; it marches through its planes
 // with the input planes z-1, z, z+1 (halo 18 x 18) and the output-gradient
-// plane z staged in LDS channel-major, so that a lane reads the four voxels
-// of its K slots for one channel at once:
+// plane z staged in LDS as they lie in memory, 16 channels per voxel:
 //   A[ci][k] = X[voxel k shifted by tap][ci],  B[k][co] = dZ[voxel k][co]
 // with K running over 16 voxels of a row (lane group g takes voxels 4g..4g+3).
-// Wave w owns rows 4w..4w+3 of the brick and keeps the 27 tap tiles in
-// registers.  For one (dz, dy) a lane reads 6 consecutive halo voxels, which
-// hold the operands of the three x taps (the shift by one voxel is a 16-bit
-// funnel shift of the dwords).  The next planes' loads are in flight during
-// the MFMAs of the current one.  At the end the four waves' tiles are added
-// in LDS in wave order (a fixed order) and the block writes one partial;
-// blocks of input tile 0 also sum dZ for the bias gradient.
-constexpr int kWgPX = 20;   // X^T row pitch (elements): 18 halo voxels + pad (40 bytes)
-constexpr int kWgPD = 20;   // dZ^T row pitch (elements): 16 voxels + pad (40 bytes)
-constexpr int kWgXItems = kCH * kCH * 4;          // 8-byte items per input plane
-constexpr int kWgXPer = (kWgXItems + 255) / 256;  // per thread
-constexpr int kWgDPer = 16 * 16 * 4 / 256;        // dZ items per thread
-constexpr int kWgSlot = kCH * 16 * kWgPX;         // elements per staged input plane
+// An operand is four voxels of one channel per lane, a transpose of what LDS
+// holds: gfx950's transposing read (ds_read_b64_tr_b16) gives it, where a
+// transposed copy in LDS takes 36 two-byte writes per thread and plane.  Wave
+// w owns rows 4w..4w+3 of the brick and keeps the 27 tap tiles in registers;
+// the 6 x 3 operands of a tap plane serve its four rows.  The next planes'
+// loads are in flight during the MFMAs of the current one, the first three
+// planes are requested together, and 168 registers leave room for a third
+// block per compute unit: the block's time is the latency of its planes.  At
+// the end the four waves' tiles are added in LDS in wave order (a fixed
+// order; lane after lane, since the tile's own layout is a 4-way bank
+// conflict) and the block writes one partial; blocks of input tile 0 also sum
+// dZ for the bias gradient.  With the reduction, 80x96x112: 16 -> 16 channels
+// 52 -> 37 us, 48 -> 16 105 -> 80, all 15 layers 701 -> 520 us.
+//
+// XV, DV: X and dZ are staged in 16-byte items (channel stride, offset and
+// count multiples of 8), else in 8-byte quads.
+constexpr int kWgPos = kCH * kCH;     // halo voxels of a plane
+constexpr int kWgSlot = kWgPos * 16;  // elements per staged input plane
 struct WgradArgs {
   const uint16_t* X;
   int ldx, cin, cin_p;
@@ -429,11 +433,77 @@ struct WgradArgs {
   float* part;
   float* partb;
 };
-__global__ void __launch_bounds__(256, 2) k_wgrad(WgradArgs a) {
-  __shared__ __attribute__((aligned(16))) uint16_t s_xt[3 * kWgSlot];  // [slot][hy][ci][hx]
-  __shared__ __attribute__((aligned(16))) uint16_t s_dt[16 * 16 * kWgPD];  // [y][co][x]
+
+// Staging of NPOS voxels x 16 channels by a block of 256 threads: 16-byte
+// halves of a voxel (V16) or its 8-byte quads.
+template <int NPOS, bool V16>
+struct WgStage {
+  static constexpr int ITEMS = V16 ? 2 * NPOS : NPOS, PER = (ITEMS + 255) / 256;
+  static constexpr int QN = V16 ? 1 : 4;
+  using Item = std::conditional_t<V16, uint4, uint2>;
+  int off[PER];  // element offset within a plane (-1: outside)
+  Item v[PER][QN];
+  // item j of this thread: voxel and first channel
+  __device__ static bool item(int j, int& pos, int& ch) {
+    const int it = threadIdx.x + 256 * j;
+    pos = V16 ? it >> 1 : it;
+    ch = V16 ? 8 * (it & 1) : 0;
+    return it < ITEMS;
+  }
+  // plane_off: element offset of the plane and channel tile; nc: channels of
+  // the tile that exist
+  __device__ void fetch(const RBuf& b, long long plane_off, bool zok, int nc) {
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+      int pos, ch;
+      item(j, pos, ch);
+      const bool ok = zok && off[j] >= 0;
+      const unsigned o = static_cast<unsigned>((plane_off + off[j]) * 2);
+      if constexpr (V16) {
+        const auto q =
+            __builtin_amdgcn_raw_buffer_load_b128(b.r, ok && ch < nc ? o : kFarOffset, 0, 0);
+        v[j][0] = uint4{static_cast<unsigned>(q[0]), static_cast<unsigned>(q[1]),
+                        static_cast<unsigned>(q[2]), static_cast<unsigned>(q[3])};
+      } else {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          v[j][k] = uint2{0, 0};
+          if (4 * k < nc) {
+            const auto q =
+                __builtin_amdgcn_raw_buffer_load_b64(b.r, ok ? o + 8 * k : kFarOffset, 0, 0);
+            v[j][k] = uint2{static_cast<unsigned>(q[0]), static_cast<unsigned>(q[1])};
+          }
+        }
+      }
+    }
+  }
+  __device__ void commit(uint16_t* d) const {
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+      int pos, ch;
+      if (!item(j, pos, ch)) continue;
+#pragma unroll
+      for (int k = 0; k < QN; ++k)
+        *reinterpret_cast<Item*>(d + pos * 16 + ch + 4 * k) = v[j][k];
+    }
+  }
+};
+
+// Operand of 16 consecutive voxels from LDS voxel p (16 channels each): lane l
+// receives voxels 4 (l / 16) .. + 3 of channel l % 16.
+__device__ __forceinline__ s4 read_tr(const uint16_t* p) {
+  const int l = threadIdx.x & 63;
+  uint16_t* q = const_cast<uint16_t*>(p) + (4 * (l >> 4) + ((l & 15) >> 2)) * 16 + (l & 3) * 4;
+  return __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+      (__attribute__((address_space(3))) s4*)q);
+}
+
+template <bool XV, bool DV>
+__global__ void __launch_bounds__(256, XV && DV ? 3 : 2) k_wgrad(WgradArgs a) {
+  __shared__ __attribute__((aligned(16))) uint16_t s_x[3 * kWgSlot];  // [slot][hy][hx][ci]
+  __shared__ __attribute__((aligned(16))) uint16_t s_d[16 * 16 * 16];  // [y][x][co]
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  const int m = lane & 15, kq = lane >> 4, q = tid & 3;
+  const int m = lane & 15, kq = lane >> 4;
   const int nci = a.cin_p / 16, nco = a.cout_p / 16;
   const int nbx = (a.nx + 15) / 16, nby = (a.ny + 15) / 16;
   int b = blockIdx.x;
@@ -453,137 +523,93 @@ __global__ void __launch_bounds__(256, 2) k_wgrad(WgradArgs a) {
       a.X, static_cast<unsigned>(((nvox - 1) * a.ldx + ((a.cin + 3) & ~3)) * 2));
   const RBuf rd = make_rbuf(
       a.dZ, static_cast<unsigned>(((nvox - 1) * a.ldz + ((a.cout + 3) & ~3)) * 2));
-  // input items of this thread: element offset within a plane (-1: reads 0)
-  // and LDS position (without the slot and channel-in-quad terms)
-  int xoff[kWgXPer], xl[kWgXPer];
-  const bool cin_ok = ib * 16 + 4 * q < a.cin;
+  WgStage<kWgPos, XV> px;
+  WgStage<256, DV> pd;
 #pragma unroll
-  for (int j = 0; j < kWgXPer; ++j) {
-    const int it = tid + 256 * j;
-    const int p = it >> 2, hy = p / kCH, hx = p % kCH;
-    const int gy = y0 - 1 + hy, gx = x0 - 1 + hx;
-    const bool ok = it < kWgXItems && cin_ok && (unsigned)gy < (unsigned)a.ny &&
-                    (unsigned)gx < (unsigned)a.nx;
-    xoff[j] = ok ? (gy * a.nx + gx) * a.ldx + ib * 16 + 4 * q : -1;
-    xl[j] = it < kWgXItems ? (hy * 16 + 4 * q) * kWgPX + hx : -1;
+  for (int j = 0; j < px.PER; ++j) {
+    int pos, ch;
+    const bool ok = px.item(j, pos, ch);
+    const int gy = y0 - 1 + pos / kCH, gx = x0 - 1 + pos % kCH;
+    px.off[j] = ok && (unsigned)gy < (unsigned)a.ny && (unsigned)gx < (unsigned)a.nx
+                    ? (gy * a.nx + gx) * a.ldx + ch
+                    : -1;
   }
-  // output-gradient items: voxel (x0 + dx_, y0 + dy_) with dy_ = tid / 64 + 4 j
-  const int dx_ = (tid >> 2) & 15;
-  const bool dcol_ok = x0 + dx_ < a.nx && cb * 16 + 4 * q < a.cout;
-  const long long plane_x = (long long)a.ny * a.nx * a.ldx;
-  uint2 px[kWgXPer], pd[kWgDPer];
-  auto fetch_x = [&](int gz) {
+#pragma unroll
+  for (int j = 0; j < pd.PER; ++j) {
+    int pos, ch;
+    pd.item(j, pos, ch);
+    const int gy = y0 + pos / 16, gx = x0 + pos % 16;
+    pd.off[j] = gy < a.ny && gx < a.nx ? (gy * a.nx + gx) * a.ldz + ch : -1;
+  }
+  const long long plane_x = (long long)a.ny * a.nx * a.ldx,
+                  plane_d = (long long)a.ny * a.nx * a.ldz;
+  auto fetch_x = [&](WgStage<kWgPos, XV>& st, int gz) {
     const bool zok = (unsigned)gz < (unsigned)a.nz;
-#pragma unroll
-    for (int j = 0; j < kWgXPer; ++j) {
-      const unsigned o = zok && xoff[j] >= 0
-                             ? static_cast<unsigned>((gz * plane_x + xoff[j]) * 2)
-                             : kFarOffset;
-      const auto v = __builtin_amdgcn_raw_buffer_load_b64(rx.r, o, 0, 0);
-      px[j] = uint2{static_cast<unsigned>(v[0]), static_cast<unsigned>(v[1])};
-    }
+    st.fetch(rx, (zok ? gz : 0) * plane_x + ib * 16, zok, a.cin - ib * 16);
   };
-  auto fetch_d = [&](int gz) {
-#pragma unroll
-    for (int j = 0; j < kWgDPer; ++j) {
-      const int gy = y0 + (tid >> 6) + 4 * j;
-      const bool ok = dcol_ok && gy < a.ny;
-      const long long e =
-          ((long long)(gz * a.ny + gy) * a.nx + x0 + dx_) * a.ldz + cb * 16 + 4 * q;
-      const unsigned o = ok ? static_cast<unsigned>(e * 2) : kFarOffset;
-      const auto v = __builtin_amdgcn_raw_buffer_load_b64(rd.r, o, 0, 0);
-      pd[j] = uint2{static_cast<unsigned>(v[0]), static_cast<unsigned>(v[1])};
-    }
-  };
-  // channel-major commits: 4 channels of one voxel go to 4 LDS rows
-  auto commit_x = [&](int slot) {
-    uint16_t* base = s_xt + slot * kWgSlot;
-#pragma unroll
-    for (int j = 0; j < kWgXPer; ++j) {
-      if (xl[j] < 0) continue;
-      uint16_t* d = base + xl[j];
-      d[0] = static_cast<uint16_t>(px[j].x);
-      d[kWgPX] = static_cast<uint16_t>(px[j].x >> 16);
-      d[2 * kWgPX] = static_cast<uint16_t>(px[j].y);
-      d[3 * kWgPX] = static_cast<uint16_t>(px[j].y >> 16);
-    }
-  };
-  auto commit_d = [&]() {
-#pragma unroll
-    for (int j = 0; j < kWgDPer; ++j) {
-      uint16_t* d = s_dt + (((tid >> 6) + 4 * j) * 16 + 4 * q) * kWgPD + dx_;
-      d[0] = static_cast<uint16_t>(pd[j].x);
-      d[kWgPD] = static_cast<uint16_t>(pd[j].x >> 16);
-      d[2 * kWgPD] = static_cast<uint16_t>(pd[j].y);
-      d[3 * kWgPD] = static_cast<uint16_t>(pd[j].y >> 16);
-    }
-  };
+  auto fetch_d = [&](int gz) { pd.fetch(rd, gz * plane_d + cb * 16, true, a.cout - cb * 16); };
   f4 acc[27];
 #pragma unroll
   for (int t = 0; t < 27; ++t) acc[t] = f4{0.f, 0.f, 0.f, 0.f};
   float bs = 0.0f;
-  // planes zb - 1 and zb, then the march
-  fetch_x(zb - 1);
-  commit_x((zb + 2) % 3);
-  fetch_x(zb);
-  commit_x(zb % 3);
-  fetch_x(zb + 1);
-  fetch_d(zb);
+  // planes zb - 1 and zb (requested together with the first step's), then
+  // the march
+  {
+    WgStage<kWgPos, XV> p0 = px, p1 = px;
+    fetch_x(p0, zb - 1);
+    fetch_x(p1, zb);
+    fetch_x(px, zb + 1);
+    fetch_d(zb);
+    p0.commit(s_x + ((zb + 2) % 3) * kWgSlot);
+    p1.commit(s_x + (zb % 3) * kWgSlot);
+  }
   for (int z = zb; z < ze; ++z) {
     __syncthreads();  // the plane z - 2 slot and the dZ plane are no longer read
-    commit_x((z + 1) % 3);
-    commit_d();
+    px.commit(s_x + ((z + 1) % 3) * kWgSlot);
+    pd.commit(s_d);
     __syncthreads();
     if (z + 1 < ze) {
-      fetch_x(z + 2);
+      fetch_x(px, z + 2);
       fetch_d(z + 1);
     }
-    const uint16_t* xs[3];
+    s4 dv[4];
 #pragma unroll
-    for (int dz = 0; dz < 3; ++dz) xs[dz] = s_xt + ((z + 2 + dz) % 3) * kWgSlot;
-    // rows 2p and 2p + 1 as one K = 32 product: each lane's eight K slots
-    // are its four voxels of the first row, then the same four of the second
+    for (int r = 0; r < 4; ++r) dv[r] = read_tr(s_d + (4 * wv + r) * 256);
+    if (ib == 0) {
 #pragma unroll
-    for (int rp = 0; rp < 2; ++rp) {
-      const int yl = 4 * wv + 2 * rp;
-      const s4 bv0 = *reinterpret_cast<const s4*>(&s_dt[(yl * 16 + m) * kWgPD + 4 * kq]);
-      const s4 bv1 = *reinterpret_cast<const s4*>(&s_dt[((yl + 1) * 16 + m) * kWgPD + 4 * kq]);
-      if (ib == 0) {
+      for (int r = 0; r < 4; ++r)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) bs += bf2f(static_cast<uint16_t>(bv0[i]));
+        for (int i = 0; i < 4; ++i) bs += bf2f(static_cast<uint16_t>(dv[r][i]));
+    }
 #pragma unroll
-        for (int i = 0; i < 4; ++i) bs += bf2f(static_cast<uint16_t>(bv1[i]));
-      }
-      const b8 bv = cat_bf16(bv0, bv1);
+    for (int dz = 0; dz < 3; ++dz) {
+      // halo rows 4 wv .. 4 wv + 5, x taps 0 .. 2
+      const uint16_t* xs = s_x + ((z + 2 + dz) % 3) * kWgSlot + 4 * wv * kCH * 16;
+      s4 X[6][3];
 #pragma unroll
-      for (int dz = 0; dz < 3; ++dz)
+      for (int r = 0; r < 6; ++r)
 #pragma unroll
-        for (int dy = 0; dy < 3; ++dy) {
-          // halo voxels 4 kq .. 4 kq + 5 of rows yl + dy and yl + 1 + dy,
-          // channel m; the three x taps are one-voxel shifts of them
-          s4 op[2][3];
+        for (int dx = 0; dx < 3; ++dx) X[r][dx] = read_tr(xs + (r * kCH + dx) * 16);
+      // rows 2p and 2p + 1 as one K = 32 product: each lane's eight K slots
+      // are its four voxels of the first row, then the same four of the second
 #pragma unroll
-          for (int h = 0; h < 2; ++h) {
-            const uint16_t* p = xs[dz] + ((yl + h + dy) * 16 + m) * kWgPX + 4 * kq;
-            const uint2 w01 = *reinterpret_cast<const uint2*>(p);
-            const unsigned w2 = *reinterpret_cast<const unsigned*>(p + 4);
-            const unsigned a0 = __builtin_amdgcn_alignbit(w01.y, w01.x, 16);
-            const unsigned a1 = __builtin_amdgcn_alignbit(w2, w01.y, 16);
-            op[h][0] = __builtin_bit_cast(s4, uint2{w01.x, w01.y});  // dx = -1
-            op[h][1] = __builtin_bit_cast(s4, uint2{a0, a1});        // dx = 0
-            op[h][2] = __builtin_bit_cast(s4, uint2{w01.y, w2});     // dx = +1
+      for (int rp = 0; rp < 2; ++rp) {
+        const b8 bv = cat_bf16(dv[2 * rp], dv[2 * rp + 1]);
+#pragma unroll
+        for (int dy = 0; dy < 3; ++dy)
+#pragma unroll
+          for (int dx = 0; dx < 3; ++dx) {
+            const int t = dz * 9 + dy * 3 + dx;
+            acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                cat_bf16(X[2 * rp + dy][dx], X[2 * rp + 1 + dy][dx]), bv, acc[t], 0, 0, 0);
           }
-          const int t = dz * 9 + dy * 3;
-#pragma unroll
-          for (int d = 0; d < 3; ++d)
-            acc[t + d] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(cat_bf16(op[0][d], op[1][d]),
-                                                                 bv, acc[t + d], 0, 0, 0);
-        }
+      }
     }
   }
-  // the four waves' tiles added in LDS in wave order: D[4 kq + j][m] is
-  // (input channel 4 kq + j, output channel m)
-  float* red = reinterpret_cast<float*>(s_xt);  // 27 x 16 x 16 floats
+  // the four waves' tiles added in LDS in wave order, lane after lane:
+  // element j of lane l of tap t at (4 t + j) 64 + l
+  static_assert(3 * kWgSlot * 2 >= 27 * 256 * 4, "the tap tiles fit the staged planes");
+  float* red = reinterpret_cast<float*>(s_x);
   __shared__ float red_b[16];
   bs += __shfl_xor(bs, 16);
   bs += __shfl_xor(bs, 32);
@@ -594,17 +620,19 @@ __global__ void __launch_bounds__(256, 2) k_wgrad(WgradArgs a) {
       for (int t = 0; t < 27; ++t)
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-          float* d = red + (t * 16 + 4 * kq + j) * 16 + m;
+          float* d = red + (4 * t + j) * 64 + lane;
           *d = (w == 0 ? 0.0f : *d) + acc[t][j];
         }
       if (kq == 0) red_b[m] = (w == 0 ? 0.0f : red_b[m]) + bs;
     }
   }
   __syncthreads();
+  // D[4 (l / 16) + j][l % 16] is (input channel, output channel)
   float* out = a.part + (long long)chunk * 27 * a.cin_p * a.cout_p;
   for (int e = tid; e < 27 * 256; e += 256) {
-    const int t = e >> 8, ci = (e >> 4) & 15, co = e & 15;
-    out[((long long)t * a.cin_p + ib * 16 + ci) * a.cout_p + cb * 16 + co] = red[e];
+    const int t = e >> 8, j = (e >> 6) & 3, l = e & 63;
+    out[((long long)t * a.cin_p + ib * 16 + 4 * (l >> 4) + j) * a.cout_p + cb * 16 + (l & 15)] =
+        red[e];
   }
   if (ib == 0 && tid < 16) a.partb[(long long)chunk * a.cout_p + cb * 16 + tid] = red_b[tid];
 }
@@ -985,7 +1013,11 @@ hipError_t unet_wgrad(const uint16_t* X, int ldx, int cin, int cin_p, const uint
   wgrad_split(cin_p, cout_p, nz, ny, nx, w.zper, w.nzp);
   const long long nch = wgrad_chunks(cin_p, cout_p, nz, ny, nx);
   const unsigned blocks = static_cast<unsigned>(nch * (cin_p / 16) * (cout_p / 16));
-  hipLaunchKernelGGL(k_wgrad, dim3(blocks), dim3(256), 0, s, w);
+  const bool xv = ldx % 8 == 0 && cin % 8 == 0 && reinterpret_cast<uintptr_t>(X) % 16 == 0;
+  const bool dv = ldz % 8 == 0 && cout % 8 == 0 && reinterpret_cast<uintptr_t>(dZ) % 16 == 0;
+  auto* kernel = xv ? (dv ? k_wgrad<true, true> : k_wgrad<true, false>)
+                    : (dv ? k_wgrad<false, true> : k_wgrad<false, false>);
+  hipLaunchKernelGGL(kernel, dim3(blocks), dim3(256), 0, s, w);
   const long long per = 256 / kRedShare, wblocks = (27LL * cin * cout + per - 1) / per;
   hipLaunchKernelGGL(k_reduce, dim3(static_cast<unsigned>(wblocks + (cout + per - 1) / per)),
                      dim3(256), 0, s, part, partb, static_cast<int>(nch), cin, cout, cin_p,
