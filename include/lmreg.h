@@ -108,11 +108,12 @@ typedef enum {
 
 /* How the three stencil passes (LNCC forward and backward, Gaussian) tile
  * the volume.  LMR_STENCIL_MARCH: 32 x 8 columns marching through chunks of
- * z planes (large volumes).  LMR_STENCIL_CUBE: 8^3 cubes of outputs, each
- * reduced along z, y and x in three steps (small volumes, where a march is
- * latency).  LMR_STENCIL_AUTO (default): cubes up to 2^20 voxels, else the
- * march.  The two forms sum the same terms in different orders (FP64 or
- * compensated sums either way). */
+ * z planes (large volumes).  LMR_STENCIL_CUBE: bricks of outputs 4 planes
+ * deep, 16 x 16 columns or, in the smallest volumes, 8 x 8, each reduced along
+ * z, y and x in three steps (small volumes, where a march is latency).
+ * LMR_STENCIL_AUTO (default): bricks up to 2^20 voxels, else the march.  The
+ * two forms sum the same terms in different orders (FP64 or compensated sums
+ * either way). */
 typedef enum {
   LMR_STENCIL_AUTO = 0,
   LMR_STENCIL_MARCH = 1,
@@ -316,8 +317,9 @@ typedef enum {
   LMR_K_FWD = 1,     /* LNCC forward (box sums, cc, adjoint maps, partials) */
   LMR_K_DECIDE = 2,  /* FP64 loss reduction and decision (LNCC levels with at most
                         1024 partials and a window of at most 7, marching or on
-                        4-plane bricks, take it inside the backward pass: this
-                        interval is then its event alone) */
+                        8 x 8 bricks, take it inside the backward pass, and
+                        mutual information where it is formed: this interval is
+                        then its event alone) */
   LMR_K_BWD = 3,     /* LNCC backward and warp backward */
   LMR_K_SMOOTH = 4,  /* Gaussian smoothing of the gradient */
   LMR_NUM_KERNELS = 5
@@ -376,8 +378,8 @@ void lmr_pyramid_destroy(lmr_pyramid* pyr);
  * replayed.  The batch owns a non-blocking stream; results of one pair are
  * read through lmr_batch_pair (borrowed context).  Box side 3..9 and
  * Gaussian radius ceil(3 sigma) <= 4 are supported (else LMR_EINVAL).  A pair
- * that a stand-alone context with p->stencil runs on 4-plane bricks runs on
- * the same bricks here; the others march (LMR_STENCIL_MARCH); either way a
+ * that a stand-alone context with p->stencil runs on 8 x 8 bricks runs on
+ * bricks here too; the others march (LMR_STENCIL_MARCH); either way a
  * pair follows the stand-alone context with that form bit for bit.
  *
  * Co-residency (persistent launches only).  The persistent launch needs all
@@ -420,8 +422,9 @@ lmr_ctx* lmr_batch_pair(lmr_batch* b, int i);
  * no persistent kernel, each phase of an attempt is one launch over the work
  * items of all pairs, the same items and results, 5 to 8 launches per
  * attempt, and no co-residency requirement; 0 = one persistent launch per
- * attempt with as many blocks as fit; n > 0 = n blocks per CU).  Pairs that a stand-alone context runs on 4-plane bricks run on
- * the same bricks here (either mode); the others march. */
+ * attempt with as many blocks as fit; n > 0 = n blocks per CU).  Pairs that a
+ * stand-alone context runs on 8 x 8 bricks run on bricks here (either mode);
+ * the others march. */
 lmr_status lmr_batch_set_config(lmr_batch* b, int target_tiles, int min_cz,
                                 int blocks_per_cu);
 lmr_status lmr_batch_get_config(lmr_batch* b, int cfg[3]);

@@ -37,7 +37,7 @@ struct lmr_batch {
   // target_tiles 0: each pair tiled as a stand-alone context's march tiles it;
   // blocks_per_cu -1: one launch per phase (no persistent kernel)
   int target_tiles = 0, min_cz = 16, blocks_per_cu = -1;
-  int n_update_items = 0, n_tiles = 0;
+  int n_update_items = 0, n_tiles = 0, n_wide = 0;
   unsigned long long timeout = 0;  // barrier timeout in wall-clock ticks
   unsigned long long start_timeout = 0;  // co-residency check, wall-clock ticks
   int missing = 0;                       // test hook (lmr_batch_test_residency)
@@ -56,7 +56,7 @@ void drop_graphs(lmr_batch* b) {
 
 // Rebuild the work lists for the current tiling knobs and upload the table.
 lmr_status layout(lmr_batch* b) {
-  int vox = 0, tiles = 0;
+  int vox = 0, tiles = 0, wide = 0;
   const int ty = batch_tile_rows();
   for (int i = 0; i < b->npairs; ++i) {
     BatchPair& P = b->host[i];
@@ -68,14 +68,17 @@ lmr_status layout(lmr_batch* b) {
     P.ucz = static_cast<int>(((long long)P.g.nz * ucols + kBatchUpdateItems - 1) /
                              kBatchUpdateItems);
     P.ucz = std::min(std::max(P.ucz, kBatchUpdateMinCz), kBatchUpdateMaxCz);
-    P.ntiles = P.bricks ? brick_count(P.g, kBatchBrickTZ) : P.t.tiles();
+    P.ntiles = P.bricks ? bricks_of(P.g, kT3, kBrickZ) : P.t.tiles();
     P.utile0 = vox;
     P.tile0 = tiles;
+    P.wide0 = wide;
+    if (P.bricks) wide += bricks_of(P.g, kWide, kBrickZ);
     vox += ucols * ((P.g.nz + P.ucz - 1) / P.ucz);
     tiles += P.ntiles;
   }
   b->n_update_items = vox;
   b->n_tiles = tiles;
+  b->n_wide = wide;
   LMR_HIP(hipMemcpyAsync(b->dev_pairs, b->host.data(), sizeof(BatchPair) * b->npairs,
                          hipMemcpyHostToDevice, b->stream));
   // the barrier counters count arrivals of one grid size: start them over
@@ -96,8 +99,8 @@ lmr_status enqueue_steps(lmr_batch* b, int n) {
     const int rb = b->p.window / 2, rg = gauss_r(b->p.grad_sigma);
     for (int i = 0; i < n; ++i)
       LMR_HIP(launch_batch_phases(b->img, static_cast<lmr_accum>(b->p.accum), rb, rg,
-                                  b->any_march, b->any_bricks, b->dev_pairs, b->npairs,
-                                  b->n_update_items, b->n_tiles, b->dp, b->stream));
+                                  b->any_march, b->dev_pairs, b->npairs, b->n_update_items,
+                                  b->n_tiles, b->n_wide, b->dp, b->stream));
     return LMR_OK;
   }
   const int grid = grid_of(b);
@@ -145,15 +148,15 @@ lmr_status lmr_batch_create(lmr_batch** out, int npairs, const int* shapes, lmr_
   if (p->tile != 1 || p->optimizer != LMR_OPT_LM || p->similarity != LMR_SIM_LNCC)
     return LMR_EINVAL;
   const int rb = p->window / 2, rg = gauss_r(p->grad_sigma);
-  // pair i runs its stencils on 4-plane bricks where a stand-alone context
-  // does (small pairs), else it marches; the pair's own begin uses that form
+  // pair i runs its stencils on bricks where a stand-alone context runs on
+  // small ones, else it marches; the pair's own begin uses that form
   std::vector<char> bricks(npairs, 0);
   bool any_bricks = false;
   for (int i = 0; i < npairs; ++i) {
     const int nz = shapes[3 * i], ny = shapes[3 * i + 1], nx = shapes[3 * i + 2];
     if (nz < 1 || ny < 1 || nx < 1) return LMR_EINVAL;
     const Geom gi{nz, ny, nx, (long long)nz * ny * nx};
-    bricks[i] = brick_depth(gi, *p) == kBatchBrickTZ;
+    bricks[i] = small_bricks(gi, *p);
     any_bricks = any_bricks || bricks[i];
   }
   const void* kernel =
@@ -217,7 +220,7 @@ lmr_status lmr_batch_create(lmr_batch** out, int npairs, const int* shapes, lmr_
     // 2), or the pair's bricks
     const int ty = batch_tile_rows();
     const size_t maxt =
-        bricks[i] ? (size_t)brick_count(gi, kBatchBrickTZ)
+        bricks[i] ? (size_t)bricks_of(gi, kT3, kBrickZ)
                : (size_t)((nx + kTX - 1) / kTX) * ((ny + ty - 1) / ty) * ((nz + 1) / 2);
     if (hipMalloc(&b->partials[i], sizeof(double) * maxt) != hipSuccess)
       return fail(LMR_ENOMEM);

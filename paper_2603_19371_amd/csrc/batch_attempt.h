@@ -5,7 +5,7 @@
 //
 //   P1 update     work items: staged-update tiles (32x8 columns over a z-chunk)
 //   P2 lncc_fwd   work items: stencil tiles of a pair (partial of cc per tile):
-//                 marching tiles, or 4-plane bricks for the pairs a stand-alone
+//                 marching tiles, or small bricks for the pairs a stand-alone
 //                 context runs on them
 //   P3 decide     work items: pairs (one block reduces a pair's partials)
 //   P4 lncc_bwd   stencil tiles of the pairs whose candidate was accepted
@@ -138,16 +138,6 @@ __device__ __forceinline__ int fresh(const int32_t* p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// origin of brick `b` of a pair (x fastest, then y, then z), as a stand-alone
-// context numbers its bricks
-__device__ __forceinline__ void brick_origin(const Geom& g, int b, int& x0, int& y0,
-                                             int& z0) {
-  const int cx = (g.nx + kT3 - 1) / kT3, cy = (g.ny + kT3 - 1) / kT3;
-  x0 = (b % cx) * kT3;
-  y0 = ((b / cx) % cy) * kT3;
-  z0 = (b / (cx * cy)) * kBatchBrickTZ;
-}
-
 // Pair owning work item `it` of a list whose per-pair offsets are first[p]:
 // one less than the number of offsets at or below it.  Every lane of a wave
 // compares one offset, so 64 pairs cost one memory round trip, where a walk
@@ -156,14 +146,12 @@ __device__ __forceinline__ void brick_origin(const Geom& g, int b, int& x0, int&
 // -> 81.9, smooth of accepted pairs 77.8 -> 67.8; a phase whose pairs all
 // rejected, which is this search alone, 32.7 -> 11.0 and 25.1 -> 6.6 us).
 __device__ __forceinline__ int owner(const BatchPair* __restrict__ pairs, int npairs,
-                                     int it, bool tiles) {
+                                     int it, int BatchPair::*first) {
   const int lane = threadIdx.x & 63;
   int n = 0;
   for (int k = 0; k < npairs; k += 64) {
     const int p = k + lane;
-    const bool at_or_below =
-        p < npairs && (tiles ? pairs[p].tile0 : pairs[p].utile0) <= it;
-    n += __popcll(__ballot(at_or_below));
+    n += __popcll(__ballot(p < npairs && pairs[p].*first <= it));
   }
   return __builtin_amdgcn_readfirstlane(n - 1);
 }
@@ -172,19 +160,19 @@ __device__ __forceinline__ int owner(const BatchPair* __restrict__ pairs, int np
 // brick path needs more registers, so pairs that all march keep a kernel
 // without it.
 template <int R, class P, int BR>
-using BrickLds = std::conditional_t<BR != 0, CubeLds<R, P, kBatchBrickTZ>, char>;
+using SmallLds = std::conditional_t<BR != 0, BrickLds<R, P, kT3>, char>;
 
 // One work item of each phase, shared by the persistent kernel (a grid-stride
 // loop per phase, grid barriers between them) and the per-phase kernels (one
-// item per block, k_batch_phases.hip).  FORM: 0 marching pairs only, 1
-// brick pairs only, 2 either; an item of a pair of the other form is skipped.
+// item per block, k_batch_phases.hip).  FORM: 0 marching pairs only (an item
+// of another pair is skipped), 2 marching pairs and pairs on small bricks.
 
 // P1: closed form, compositive integration, candidate warp (and its
 // derivative, which P4 reads), one staged tile per work item
 template <typename T>
 __device__ __forceinline__ void update_item(const BatchPair* __restrict__ pairs, int npairs,
                                             int it, StagedLds& lds) {
-  const BatchPair& P = pairs[owner(pairs, npairs, it, false)];
+  const BatchPair& P = pairs[owner(pairs, npairs, it, &BatchPair::utile0)];
   if (P.st->stalled) return;
   UpdateArgs a = update_args_from_state(P.st, P.U0, P.U1, P.G, P.Mw, P.eps, P.compositive);
   a.dMw = P.graw;
@@ -210,31 +198,26 @@ template <int R, int FORM, class Pol, class LM, class LB>
 __device__ __forceinline__ void stencil_item(const Pol& pol, const BatchPair& P, int local,
                                              typename Pol::Local& loc, LM& lm, LB& lb) {
   int x0, y0, z0;
-  if (FORM != 0 && P.bricks) {
-    if constexpr (FORM != 0) {
-      brick_origin(P.g, local, x0, y0, z0);
+  if (FORM == 2 && P.bricks) {
+    if constexpr (FORM == 2) {
+      brick_origin<kT3>(P.g, local, x0, y0, z0);
       __syncthreads();  // the previous brick's last LDS reads are done
-      stencil_cube<R, kBatchBrickTZ>(pol, P.g, x0, y0, z0, loc, lb);
+      stencil_cube<R>(pol, P.g, x0, y0, z0, loc, lb);
     }
   } else {
-    if constexpr (FORM != 1) {
-      tile_origin(P.t, local, kTY, x0, y0, z0);
-      stencil_tile<R, kTY>(pol, P.g, x0, y0, z0, min(z0 + P.t.cz, P.g.nz), loc, lm);
-    }
+    tile_origin(P.t, local, kTY, x0, y0, z0);
+    stencil_tile<R, kTY>(pol, P.g, x0, y0, z0, min(z0 + P.t.cz, P.g.nz), loc, lm);
   }
 }
 
 template <int FORM>
 __device__ __forceinline__ bool other_form(const BatchPair& P) {
-  return (FORM == 0 && P.bricks) || (FORM == 1 && !P.bricks);
+  return FORM == 0 && P.bricks;
 }
 
-// P2: LNCC forward, one partial of cc per tile
-template <int RB, typename T, typename Acc, int FORM, class LM, class LB>
-__device__ __forceinline__ void fwd_item(const BatchPair* __restrict__ pairs, int npairs,
-                                         int it, LM& lm, LB& lb) {
-  const BatchPair& P = pairs[owner(pairs, npairs, it, true)];
-  if (P.st->stalled || other_form<FORM>(P)) return;
+// The stencil policies of pair P.
+template <typename T, typename Acc>
+__device__ __forceinline__ FwdPol<T, kNT, Acc> fwd_policy(const BatchPair& P) {
   FwdPol<T, kNT, Acc> pol;
   pol.F = static_cast<const T*>(P.F);
   pol.Mw = P.Mw;
@@ -245,6 +228,38 @@ __device__ __forceinline__ void fwd_item(const BatchPair* __restrict__ pairs, in
   pol.N = static_cast<int>(P.g.N);
   pol.inv_n = P.inv_n;
   pol.eps = P.cc_eps;
+  return pol;
+}
+template <typename T, typename Acc>
+__device__ __forceinline__ BwdPol<T, Acc> bwd_policy(const BatchPair& P) {
+  BwdPol<T, Acc> pol;
+  pol.F = static_cast<const T*>(P.F);
+  pol.Mw = P.Mw;
+  pol.maps = P.maps;
+  pol.dMw = P.graw;  // stored there by P1 for the candidate
+  pol.graw = P.graw;
+  pol.g = P.g;
+  pol.inv_n = P.inv_n;
+  return pol;
+}
+template <int RG>
+__device__ __forceinline__ SmoothPol<RG> smooth_policy(const BatchPair& P) {
+  SmoothPol<RG> pol;
+  pol.in = P.graw;
+  pol.out = P.G;
+  pol.N = static_cast<int>(P.g.N);
+#pragma unroll
+  for (int k = 0; k <= 2 * RG; ++k) pol.w[k] = P.gw[k];
+  return pol;
+}
+
+// P2: LNCC forward, one partial of cc per tile
+template <int RB, typename T, typename Acc, int FORM, class LM, class LB>
+__device__ __forceinline__ void fwd_item(const BatchPair* __restrict__ pairs, int npairs,
+                                         int it, LM& lm, LB& lb) {
+  const BatchPair& P = pairs[owner(pairs, npairs, it, &BatchPair::tile0)];
+  if (P.st->stalled || other_form<FORM>(P)) return;
+  const auto pol = fwd_policy<T, Acc>(P);
   const int local = it - P.tile0;
   auto loc = pol.begin_block(P.st);
   stencil_item<RB, FORM>(pol, P, local, loc, lm, lb);
@@ -255,16 +270,9 @@ __device__ __forceinline__ void fwd_item(const BatchPair* __restrict__ pairs, in
 template <int RB, typename T, typename Acc, int FORM, class LM, class LB>
 __device__ __forceinline__ void bwd_item(const BatchPair* __restrict__ pairs, int npairs,
                                          int it, LM& lm, LB& lb) {
-  const BatchPair& P = pairs[owner(pairs, npairs, it, true)];
+  const BatchPair& P = pairs[owner(pairs, npairs, it, &BatchPair::tile0)];
   if (fresh(&P.st->stalled) || !fresh(&P.st->accepted) || other_form<FORM>(P)) return;
-  BwdPol<T, Acc> pol;
-  pol.F = static_cast<const T*>(P.F);
-  pol.Mw = P.Mw;
-  pol.maps = P.maps;
-  pol.dMw = P.graw;  // stored there by P1 for the candidate
-  pol.graw = P.graw;
-  pol.g = P.g;
-  pol.inv_n = P.inv_n;
+  const auto pol = bwd_policy<T, Acc>(P);
   auto loc = pol.begin_block(nullptr);
   stencil_item<RB, FORM>(pol, P, it - P.tile0, loc, lm, lb);
 }
@@ -273,14 +281,9 @@ __device__ __forceinline__ void bwd_item(const BatchPair* __restrict__ pairs, in
 template <int RG, int FORM, class LM, class LB>
 __device__ __forceinline__ void smooth_item(const BatchPair* __restrict__ pairs, int npairs,
                                             int it, LM& lm, LB& lb) {
-  const BatchPair& P = pairs[owner(pairs, npairs, it, true)];
+  const BatchPair& P = pairs[owner(pairs, npairs, it, &BatchPair::tile0)];
   if (fresh(&P.st->stalled) || !fresh(&P.st->accepted) || other_form<FORM>(P)) return;
-  SmoothPol<RG> pol;
-  pol.in = P.graw;
-  pol.out = P.G;
-  pol.N = static_cast<int>(P.g.N);
-#pragma unroll
-  for (int k = 0; k <= 2 * RG; ++k) pol.w[k] = P.gw[k];
+  const auto pol = smooth_policy<RG>(P);
   auto loc = pol.begin_block(P.st);
   stencil_item<RG, FORM>(pol, P, it - P.tile0, loc, lm, lb);
 }
@@ -299,9 +302,9 @@ __global__ void __launch_bounds__(kNT)
     StencilLds<RB, kTY, FwdPol<T, kNT, Acc>> fwd;
     StencilLds<RB, kTY, BwdPol<T, Acc>> bwd;
     StencilLds<RG, kTY, SmoothPol<RG>> smo;
-    BrickLds<RB, FwdPol<T, kNT, Acc>, BR> fwd_b;
-    BrickLds<RB, BwdPol<T, Acc>, BR> bwd_b;
-    BrickLds<RG, SmoothPol<RG>, BR> smo_b;
+    SmallLds<RB, FwdPol<T, kNT, Acc>, BR> fwd_b;
+    SmallLds<RB, BwdPol<T, Acc>, BR> bwd_b;
+    SmallLds<RG, SmoothPol<RG>, BR> smo_b;
   } lds;
   // after a barrier failure every later launch returns at once
   if (__hip_atomic_load(&ctl->error.v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) return;

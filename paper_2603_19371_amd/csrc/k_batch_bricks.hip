@@ -1,4 +1,4 @@
-// Batched persistent form, FP64 box sums, with 4-plane bricks for the pairs
+// Batched persistent form, FP64 box sums, with small bricks for the pairs
 // that run on them (a set of its own: it needs more registers).
 #include "batch_attempt.h"
 

@@ -1,4 +1,4 @@
-// Batched persistent form, compensated FP32 box sums, with 4-plane bricks for
+// Batched persistent form, compensated FP32 box sums, with small bricks for
 // the pairs that run on them.
 #include "batch_attempt.h"
 

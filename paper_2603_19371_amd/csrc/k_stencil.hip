@@ -98,21 +98,36 @@ __global__ void __launch_bounds__(kTX* TY)
   pol.end_tile(loc, tile);  // partials in tile order, as in the batched form
 }
 
-// The same stencil on TZ x kT3 x kT3 bricks (small volumes; stencil.h).
-template <int R, class P, int TZ, bool DEC>
+// The same stencil on small bricks (stencil.h).
+template <int R, class P, bool DEC>
 __global__ void __launch_bounds__(kCubeThreads)
     __attribute__((amdgpu_waves_per_eu(DEC ? 4 : 1)))
-    k_cube(const P pol, Geom g, int cubes_x, int cubes_y, const DevState* st, int need,
-           PassDecision pd) {
+    k_cube(const P pol, Geom g, const DevState* st, int need, PassDecision pd) {
   const DevState* rs;
   if (!pass_state<kCubeThreads, DEC>(st, need, pd, rs)) return;
-  __shared__ CubeLds<R, P, TZ> sm;
+  __shared__ BrickLds<R, P, kT3> sm;
   const int b = xcd_remap(blockIdx.x, gridDim.x);
-  const int x0 = (b % cubes_x) * kT3, y0 = ((b / cubes_x) % cubes_y) * kT3;
-  const int z0 = (b / (cubes_x * cubes_y)) * TZ;
+  int x0, y0, z0;
+  brick_origin<kT3>(g, b, x0, y0, z0);
   typename P::Local loc = pol.begin_block(rs);
-  stencil_cube<R, TZ>(pol, g, x0, y0, z0, loc, sm);
+  stencil_cube<R>(pol, g, x0, y0, z0, loc, sm);
   pol.end_tile(loc, b);
+}
+
+// And on wide bricks.
+template <int R, class P>
+__global__ void __launch_bounds__(kWideThreads)
+    k_wide(const P pol, Geom g, const DevState* st, int need, PassDecision pd) {
+  const DevState* rs;
+  if (!pass_state<kWideThreads, false>(st, need, pd, rs)) return;
+  __shared__ BrickLds<R, P, kWide> sm;
+  const int b = xcd_remap(blockIdx.x, gridDim.x);
+  int x0, y0, z0;
+  brick_origin<kWide>(g, b, x0, y0, z0);
+  typename P::Local loc = pol.begin_block(rs);
+  WideFetch<R, P> f;
+  wide_fetch<R>(pol, g, x0, y0, z0, loc, f);
+  stencil_wide<R>(pol, g, x0, y0, z0, loc, f, sm, false, b);
 }
 
 }  // namespace
@@ -163,21 +178,12 @@ bool use_cubes(const Geom& g, const lmr_params& p) {
          (p.stencil == LMR_STENCIL_AUTO && g.N <= kCubeMaxVoxels);
 }
 
-// Bricks are 8 planes deep, or 4 where 8-plane bricks would give fewer than
-// kCubeSplitBelow blocks (the quarter-resolution level): there each block's
-// own latency is the launch's, and halving its work halves that.
-constexpr int kCubeSplitBelow = 512;
+// Small bricks where the volume gives fewer than kWideFrom wide ones.
+constexpr int kWideFrom = 256;
 
-int cube_columns(const Geom& g) { return ((g.nx + kT3 - 1) / kT3) * ((g.ny + kT3 - 1) / kT3); }
+bool use_wide(const Geom& g) { return bricks_of(g, kWide, kBrickZ) >= kWideFrom; }
 
-int cube_tz(const Geom& g) {
-  return cube_columns(g) * ((g.nz + 7) / 8) < kCubeSplitBelow ? 4 : 8;
-}
-
-int cube_count(const Geom& g) {
-  const int tz = cube_tz(g);
-  return cube_columns(g) * ((g.nz + tz - 1) / tz);
-}
+int brick_blocks(const Geom& g) { return bricks_of(g, use_wide(g) ? kWide : kT3, kBrickZ); }
 
 template <class P, int R, bool DEC = false>
 hipError_t run(const P& pol, const Geom& g, bool cubes, const DevState* st, int need,
@@ -186,15 +192,14 @@ hipError_t run(const P& pol, const Geom& g, bool cubes, const DevState* st, int 
     return hipErrorInvalidValue;  // wider windows keep the decision kernel
   } else {
     if (cubes) {
-      const int cx = (g.nx + kT3 - 1) / kT3, cy = (g.ny + kT3 - 1) / kT3;
-      if (cube_tz(g) == 4)
-        hipLaunchKernelGGL((k_cube<R, P, 4, DEC>), dim3(cube_count(g)), dim3(kCubeThreads),
-                           0, s, pol, g, cx, cy, st, need, pd);
+      if (!use_wide(g))
+        hipLaunchKernelGGL((k_cube<R, P, DEC>), dim3(brick_blocks(g)), dim3(kCubeThreads), 0, s,
+                           pol, g, st, need, pd);
       else if constexpr (DEC)
-        return hipErrorInvalidValue;  // 8-plane bricks keep the decision kernel
+        return hipErrorInvalidValue;  // wide bricks keep the decision kernel
       else
-        hipLaunchKernelGGL((k_cube<R, P, 8, false>), dim3(cube_count(g)),
-                           dim3(kCubeThreads), 0, s, pol, g, cx, cy, st, need, pd);
+        hipLaunchKernelGGL((k_wide<R, P>), dim3(brick_blocks(g)), dim3(kWideThreads), 0, s, pol,
+                           g, st, need, pd);
       return hipGetLastError();
     }
     const Tiling t = march_tiling(g, R);
@@ -276,14 +281,12 @@ hipError_t smooth_r(const float* in, float* out, const Geom& g, const lmr_params
 
 }  // namespace
 
-int brick_depth(const Geom& g, const lmr_params& p) {
-  return use_cubes(g, p) ? cube_tz(g) : 0;
+bool small_bricks(const Geom& g, const lmr_params& p) {
+  return use_cubes(g, p) && !use_wide(g);
 }
 
-int brick_count(const Geom& g, int tz) { return cube_columns(g) * ((g.nz + tz - 1) / tz); }
-
 int fwd_num_blocks(const Geom& g, const lmr_params& p) {
-  return use_cubes(g, p) ? cube_count(g) : march_tiling(g, p.window / 2).tiles();
+  return use_cubes(g, p) ? brick_blocks(g) : march_tiling(g, p.window / 2).tiles();
 }
 
 int gauss_radius(double sigma) {
@@ -353,7 +356,7 @@ hipError_t launch_smooth(const float* graw, const Geom& g, const lmr_params& p,
 
 bool bwd_takes_decision(const Geom& g, const lmr_params& p, int nparts) {
   return nparts <= kPassDecisionMaxParts && p.window / 2 <= kPassDecisionMaxRadius &&
-         !(use_cubes(g, p) && cube_tz(g) == 8);
+         !(use_cubes(g, p) && use_wide(g));
 }
 
 hipError_t launch_bwd_decide(const void* F, lmr_dtype t, const float* Mw, const float* maps,

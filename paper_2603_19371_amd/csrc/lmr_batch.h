@@ -21,11 +21,12 @@ struct BatchPair {
   double* partials;  // one slot per stencil tile of this pair
   DevState* st;
   Tiling t;          // stencil tiling of this pair (marching form)
-  int bricks;        // 1: the stencil work items are kBatchBrickTZ x 8 x 8 bricks
-  int ntiles;        // stencil work items (and cc partials) of this pair
+  int bricks;        // 1: the stencil work items are bricks
+  int ntiles;        // cc partials of this pair: its marching tiles or small bricks
   int utile0;        // first update work item of this pair
   int ucz;           // planes per update work item of this pair
-  int tile0;         // first stencil work item of this pair
+  int tile0;         // first stencil work item of this pair (marching tiles, small bricks)
+  int wide0;         // first wide brick of this pair (marching pairs have none)
   float eps;
   int compositive;
   double inv_n, cc_eps;
@@ -43,10 +44,11 @@ struct BatchPair {
 // it is at, and no plain store to a counter has to be ordered against the
 // atomics of blocks on other chiplets.
 constexpr int kBarGroups = 8;
-// Depth of the bricks of the pairs the batched kernel runs on bricks: those
-// a stand-alone context also runs on 4-plane bricks (brick_depth), so that
-// such a pair's run is the stand-alone run bit for bit.
-constexpr int kBatchBrickTZ = 4;
+// The pairs that a stand-alone context runs on small bricks run on bricks
+// here too, and their run is the stand-alone run bit for bit: an output does
+// not depend on its brick, and a cc partial is a small brick's in both.  The
+// persistent kernel keeps the small bricks; one launch per phase, where the
+// pairs fill the GPU together, runs wide ones.
 // update work item: a 32 x 8 column (the staged update's tile) over ucz
 // planes: about kBatchUpdateItems items per pair, 2..32 planes each (long
 // marches for large pairs, short ones where a pair has few columns)
@@ -78,11 +80,12 @@ const void* batch_kernel_bricks(lmr_dtype t, int box_radius, int gauss_radius);
 const void* batch_kernel_bricks_f32c(lmr_dtype t, int box_radius, int gauss_radius);
 // One attempt of every pair as one launch per phase (no persistent kernel):
 // update, forward, decision, backward, smoothing; the stencil phases once
-// for the marching pairs and once for the brick pairs, as present.
+// for the marching pairs (if any: march; n_tiles items) and once for the brick
+// pairs (n_wide wide bricks).
 hipError_t launch_batch_phases(lmr_dtype t, lmr_accum accum, int box_radius,
-                               int gauss_radius, bool march, bool bricks,
-                               const BatchPair* pairs, int npairs, int n_update_items,
-                               int n_tiles, const DecideParams& dp, hipStream_t s);
+                               int gauss_radius, bool march, const BatchPair* pairs,
+                               int npairs, int n_update_items, int n_tiles, int n_wide,
+                               const DecideParams& dp, hipStream_t s);
 // timeout: ticks of a barrier wait; start_timeout: ticks after which a
 // block waiting at the first barrier of a launch gives up if some block of
 // the grid has not started; missing: 0, or 1 to make block 0 of every launch

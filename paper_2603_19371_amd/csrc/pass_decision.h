@@ -31,7 +31,9 @@ struct PassDecision {
 
 // Whether the backward pass of this level takes the decision: at most
 // kPassDecisionMaxParts partials, a window of at most 7, on the march or on
-// 4-plane bricks (the 8-plane brick pass would spill registers with it).
+// small bricks.  The wide bricks' pass has so many blocks for its work that
+// the reductions cost more than the launch they save (80x96x112, 840 blocks:
+// a rejected attempt 15 us, decision kernel and returning blocks 7).
 bool bwd_takes_decision(const Geom& g, const lmr_params& p, int nparts);
 // P4 with the decision: st is the pair state before the attempt (read only).
 hipError_t launch_bwd_decide(const void* F, lmr_dtype t, const float* Mw, const float* maps,

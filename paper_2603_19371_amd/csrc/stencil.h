@@ -114,11 +114,13 @@ __host__ __device__ inline Tiling make_tiling(int nz, int ny, int nx, int ty,
   return t;
 }
 
-// The depth of the bricks the stencil passes of a stand-alone context run on
-// (4 or 8 planes), or 0 where they march (k_stencil.hip); and the number of
-// bricks of depth tz.
-int brick_depth(const Geom& g, const lmr_params& p);
-int brick_count(const Geom& g, int tz);
+// Whether the stencil passes of a stand-alone context run on small bricks
+// (kT3 x kT3 columns, the smallest volumes; else on wide bricks or marching,
+// k_stencil.hip), and the number of small and of wide bricks of a volume.
+bool small_bricks(const Geom& g, const lmr_params& p);
+__host__ __device__ inline int bricks_of(const Geom& g, int side, int depth) {
+  return ((g.nx + side - 1) / side) * ((g.ny + side - 1) / side) * ((g.nz + depth - 1) / depth);
+}
 
 // The march's tiling of a volume for stencil radius R on the current device
 // (k_stencil.hip): every pass of a per-pair attempt, and by default each pair
@@ -299,142 +301,294 @@ __device__ __forceinline__ void stencil_tile(const P& pol, const Geom& g, int x0
 // ------------------------------------------------------------- 3D tiles
 // Small volumes (coarse pyramid levels) have too few 32 x TY columns to fill
 // the GPU, and the plane-serial march of a short chunk is their latency.
-// There a block owns a whole TZ x kT3 x kT3 brick of outputs instead: each
-// thread reads one (y, x) column of the (kT3 + 2R)^2 halo straight from
-// memory (all its loads in flight at once) and reduces along z, expanding the
-// raw inputs into the accumulated channels; then the block reduces along y
-// and along x in LDS and emits.  Three steps instead of a march.
-constexpr int kT3 = 8;
-constexpr int kCubeThreads = 256;
+// There a block owns a brick of kBrickZ planes instead: each thread reads one
+// (y, x) column of the halo straight from memory (all its loads in flight at
+// once, in wide bricks the operands of its outputs with them) and reduces
+// along z; then the block reduces along y and along x in LDS and emits.  Three
+// steps instead of a march.
+//
+// Two sizes.  Small bricks, kT3 x kT3 columns, where few blocks are the
+// limit (40x48x56: 420 of them).  Wide bricks, kWide x kWide columns, for
+// larger volumes: what bounds a pass there is the cache lines its halo rows
+// touch (loads and stores alone take 14 of the forward pass's 18 us on 8 x 8
+// x 8 bricks at 80x96x112, whose 14-voxel rows use 56 bytes of one or two
+// 128-byte lines), and a 22-voxel row serves twice the outputs (15 us; the
+// backward pass 23 -> 19, the Gaussian 13.6 -> 11).
+//
+// Every output is the sum of its terms in ascending z, then y, then x, so it
+// does not depend on the brick that computes it.
+constexpr int kT3 = 8, kWide = 16, kBrickZ = 4;
+constexpr int kCubeThreads = 256, kWideThreads = 512;
 
-// The z sums of the halo columns.  The y pass reads them, keeps its own
-// (fewer) results in registers and, after a barrier, writes them over the z
-// sums, so one array serves both passes and more blocks fit on a CU.
-template <int R, class P, int TZ>
-struct CubeLds {
+// The z sums of the halo columns of a brick of SIDE x SIDE columns.  The y
+// pass reads them, keeps its own (fewer) results in registers and, after a
+// barrier, writes them over the z sums, so one array serves both passes and
+// more blocks fit on a CU.
+template <int R, class P, int SIDE>
+struct BrickLds {
   using A = typename P::Acc;
-  static constexpr int L = kT3 + 2 * R;
-  A z[P::NCH][TZ][L][L];
-  __device__ __forceinline__ A (&y())[P::NCH][TZ][kT3][L] {
-    return *reinterpret_cast<A(*)[P::NCH][TZ][kT3][L]>(&z[0][0][0][0]);
+  static constexpr int L = SIDE + 2 * R;
+  A z[P::NCH][kBrickZ][L][L];
+  __device__ __forceinline__ A (&y())[P::NCH][kBrickZ][SIDE][L] {
+    return *reinterpret_cast<A(*)[P::NCH][kBrickZ][SIDE][L]>(&z[0][0][0][0]);
   }
 };
 
-template <int R, int TZ, class P>
-__device__ __forceinline__ void stencil_cube(const P& pol, const Geom& g, int x0, int y0,
-                                             int z0, typename P::Local& loc,
-                                             CubeLds<R, P, TZ>& sm) {
+// KO consecutive outputs of one channel along an axis from the KO + 2R values
+// they share, each summed in order.
+template <int R, int KO, class P>
+__device__ __forceinline__ void window_outputs(const P& pol,
+                                               const typename P::Acc (&v)[KO + 2 * R],
+                                               typename P::Acc (&o)[KO]) {
   using A = typename P::Acc;
-  constexpr int NR = P::NRAW, NC = P::NCH, W = 2 * R + 1, L = kT3 + 2 * R;
-  constexpr int NT = kCubeThreads;
-  // z: one (y, x) column of the halo per thread
-  for (int col = threadIdx.x; col < L * L; col += NT) {
-    const int yy = col / L, xx = col - yy * L;
-    const int gy = y0 - R + yy, gx = x0 - R + xx;
-    const bool in = (unsigned)gy < (unsigned)g.ny && (unsigned)gx < (unsigned)g.nx;
-    float r[TZ + 2 * R][NR];
 #pragma unroll
-    for (int k = 0; k < TZ + 2 * R; ++k) {
-      const int gz = z0 - R + k;
-      const unsigned i = (in && (unsigned)gz < (unsigned)g.nz)
-                             ? static_cast<unsigned>((gz * g.ny + gy) * g.nx + gx)
-                             : kFarIndex;
-      pol.load(loc, i, r[k]);
-    }
-    if constexpr (P::kBox) {
-      // running sum down the column: the entering position's terms are
-      // added, the leaving position's (formed again) subtracted
-      A a[NC];
+  for (int j = 0; j < KO; ++j) {
+    o[j] = A();
 #pragma unroll
-      for (int c = 0; c < NC; ++c) a[c] = A();
-#pragma unroll
-      for (int k = 0; k < W; ++k) pol.accum(a, r[k], k);
-#pragma unroll
-      for (int oz = 0; oz < TZ; ++oz) {
-#pragma unroll
-        for (int c = 0; c < NC; ++c) sm.z[c][oz][yy][xx] = a[c];
-        if (oz + 1 < TZ) {
-          A in_[NC], out_[NC];
-#pragma unroll
-          for (int c = 0; c < NC; ++c) in_[c] = out_[c] = A();
-          pol.accum(in_, r[oz + W], 0);
-          pol.accum(out_, r[oz], 0);
-#pragma unroll
-          for (int c = 0; c < NC; ++c) a[c] += in_[c] - out_[c];
-        }
-      }
-    } else {
-#pragma unroll
-      for (int oz = 0; oz < TZ; ++oz) {
-        A a[NC];
-#pragma unroll
-        for (int c = 0; c < NC; ++c) a[c] = A();
-#pragma unroll
-        for (int k = 0; k < W; ++k) pol.accum(a, r[oz + k], k);
-#pragma unroll
-        for (int c = 0; c < NC; ++c) sm.z[c][oz][yy][xx] = a[c];
-      }
+    for (int k = 0; k <= 2 * R; ++k) {
+      if constexpr (P::kBox)
+        o[j] += v[j + k];
+      else
+        o[j] = fma(A(pol.wt(k)), v[j + k], o[j]);
     }
   }
-  __syncthreads();
-  // y, into registers first
-  constexpr int NY = TZ * kT3 * L, KY = (NY + NT - 1) / NT;
-  A ay[KY][NC];
+}
+
+// Halo column `col` of the brick at (x0, y0, z0).
+template <int R, int SIDE, class P>
+__device__ __forceinline__ void brick_column(const P& pol, const Geom& g, int x0, int y0,
+                                             int z0, const typename P::Local& loc, int col,
+                                             float (&r)[kBrickZ + 2 * R][P::NRAW]) {
+  constexpr int L = SIDE + 2 * R;
+  const int yy = col / L, xx = col - yy * L;
+  const int gy = y0 - R + yy, gx = x0 - R + xx;
+  const bool in = (unsigned)gy < (unsigned)g.ny && (unsigned)gx < (unsigned)g.nx;
 #pragma unroll
-  for (int j = 0; j < KY; ++j) {
+  for (int k = 0; k < kBrickZ + 2 * R; ++k) {
+    const int gz = z0 - R + k;
+    const unsigned i = (in && (unsigned)gz < (unsigned)g.nz)
+                           ? static_cast<unsigned>((gz * g.ny + gy) * g.nx + gx)
+                           : kFarIndex;
+    pol.load(loc, i, r[k]);
+  }
+}
+
+// Its z sums into LDS, the raw inputs expanded into the accumulated channels.
+template <int R, int SIDE, class P>
+__device__ __forceinline__ void brick_zsum(const P& pol,
+                                           const float (&r)[kBrickZ + 2 * R][P::NRAW], int col,
+                                           BrickLds<R, P, SIDE>& sm) {
+  using A = typename P::Acc;
+  constexpr int NC = P::NCH, L = SIDE + 2 * R;
+  const int yy = col / L, xx = col - yy * L;
+#pragma unroll
+  for (int oz = 0; oz < kBrickZ; ++oz) {
+    A a[NC];
+#pragma unroll
+    for (int c = 0; c < NC; ++c) a[c] = A();
+#pragma unroll
+    for (int k = 0; k <= 2 * R; ++k) pol.accum(a, r[oz + k], k);
+#pragma unroll
+    for (int c = 0; c < NC; ++c) sm.z[c][oz][yy][xx] = a[c];
+  }
+}
+
+// The y pass of a brick by NT threads, KY outputs per item.
+template <int R, int SIDE, int NT, int KY, class P>
+__device__ __forceinline__ void brick_ypass(const P& pol, BrickLds<R, P, SIDE>& sm) {
+  using A = typename P::Acc;
+  constexpr int NC = P::NCH, L = SIDE + 2 * R, NY = kBrickZ * (SIDE / KY) * L,
+                PY = (NY + NT - 1) / NT;
+  A ay[PY][NC][KY];
+#pragma unroll
+  for (int j = 0; j < PY; ++j) {
     const int it = threadIdx.x + j * NT;
     if (NY % NT == 0 || it < NY) {
-      const int oz = it / (kT3 * L), rem = it - oz * (kT3 * L);
-      const int oy = rem / L, xx = rem - oy * L;
+      const int xx = it % L, row = it / L;
+      const int oy = (row % (SIDE / KY)) * KY, oz = row / (SIDE / KY);
 #pragma unroll
-      for (int c = 0; c < NC; ++c) ay[j][c] = A();
+      for (int c = 0; c < NC; ++c) {
+        A v[KY + 2 * R];
 #pragma unroll
-      for (int k = 0; k < W; ++k)
-#pragma unroll
-        for (int c = 0; c < NC; ++c) {
-          if constexpr (P::kBox)
-            ay[j][c] += sm.z[c][oz][oy + k][xx];
-          else
-            ay[j][c] = fma(A(pol.wt(k)), sm.z[c][oz][oy + k][xx], ay[j][c]);
-        }
+        for (int k = 0; k < KY + 2 * R; ++k) v[k] = sm.z[c][oz][oy + k][xx];
+        window_outputs<R, KY>(pol, v, ay[j][c]);
+      }
     }
   }
   __syncthreads();
   auto& sy = sm.y();
 #pragma unroll
-  for (int j = 0; j < KY; ++j) {
+  for (int j = 0; j < PY; ++j) {
     const int it = threadIdx.x + j * NT;
     if (NY % NT == 0 || it < NY) {
-      const int oz = it / (kT3 * L), rem = it - oz * (kT3 * L);
-      const int oy = rem / L, xx = rem - oy * L;
+      const int xx = it % L, row = it / L;
+      const int oy = (row % (SIDE / KY)) * KY, oz = row / (SIDE / KY);
 #pragma unroll
-      for (int c = 0; c < NC; ++c) sy[c][oz][oy][xx] = ay[j][c];
+      for (int c = 0; c < NC; ++c)
+#pragma unroll
+        for (int k = 0; k < KY; ++k) sy[c][oz][oy + k][xx] = ay[j][c][k];
     }
+  }
+}
+
+// A small brick by kCubeThreads threads, one output each.
+template <int R, class P>
+__device__ __forceinline__ void stencil_cube(const P& pol, const Geom& g, int x0, int y0,
+                                             int z0, typename P::Local& loc,
+                                             BrickLds<R, P, kT3>& sm) {
+  using A = typename P::Acc;
+  constexpr int NC = P::NCH, L = kT3 + 2 * R, NT = kCubeThreads;
+  static_assert(kBrickZ * kT3 * kT3 == NT, "one output per thread");
+  for (int col = threadIdx.x; col < L * L; col += NT) {
+    float r[kBrickZ + 2 * R][P::NRAW];
+    brick_column<R, kT3>(pol, g, x0, y0, z0, loc, col, r);
+    brick_zsum<R, kT3>(pol, r, col, sm);
   }
   __syncthreads();
-  // x, and the outputs
-  for (int it = threadIdx.x; it < TZ * kT3 * kT3; it += NT) {
-    const int oz = it / (kT3 * kT3), oy = (it / kT3) % kT3, ox = it % kT3;
-    A a[NC];
+  brick_ypass<R, kT3, NT, 1>(pol, sm);
+  __syncthreads();
+  auto& sy = sm.y();
+  const int oz = threadIdx.x / (kT3 * kT3), oy = (threadIdx.x / kT3) % kT3,
+            ox = threadIdx.x % kT3;
+  A a[NC];
 #pragma unroll
-    for (int c = 0; c < NC; ++c) a[c] = A();
+  for (int c = 0; c < NC; ++c) {
+    A v[1 + 2 * R], o[1];
 #pragma unroll
-    for (int k = 0; k < W; ++k)
+    for (int k = 0; k <= 2 * R; ++k) v[k] = sy[c][oz][oy][ox + k];
+    window_outputs<R, 1>(pol, v, o);
+    a[c] = o[0];
+  }
+  const int gx = x0 + ox, gy = y0 + oy, gz = z0 + oz;
+  if (gx < g.nx && gy < g.ny && gz < g.nz) {
+    const int i = (gz * g.ny + gy) * g.nx + gx;
+    typename P::Pre q;
+    pol.pre(i, q);
+    pol.emit(loc, i, q, a);
+  }
+}
+
+// ---- wide bricks: kWideThreads threads, two outputs adjacent in x each
+template <int R, class P>
+struct WideFetch {
+  float r[kBrickZ + 2 * R][P::NRAW];  // the thread's halo column
+  typename P::Pre q[2];               // the operands of its outputs
+  int i;                              // its first output
+  bool ok0, ok1;                      // which of them exist
+};
+
+template <int R, class P>
+__device__ __forceinline__ void wide_fetch(const P& pol, const Geom& g, int x0, int y0, int z0,
+                                           const typename P::Local& loc, WideFetch<R, P>& f) {
+  constexpr int L = kWide + 2 * R;
+  static_assert(kBrickZ * kWide * kWide == 2 * kWideThreads, "two outputs per thread");
+  if (L * L >= kWideThreads || threadIdx.x < L * L)
+    brick_column<R, kWide>(pol, g, x0, y0, z0, loc, threadIdx.x, f.r);
+  const int gx = x0 + (threadIdx.x % 8) * 2, gy = y0 + (threadIdx.x / 8) % 16,
+            gz = z0 + threadIdx.x / 128;
+  f.ok0 = gx < g.nx && gy < g.ny && gz < g.nz;
+  f.ok1 = f.ok0 && gx + 1 < g.nx;
+  f.i = (gz * g.ny + gy) * g.nx + gx;
+  if (f.ok0) pol.pre(f.i, f.q[0]);
+  if (f.ok1) pol.pre(f.i + 1, f.q[1]);
+}
+
+// The passes over a fetched brick.  cc (summing policies): what each of the
+// thread's outputs added to loc.sum.
+template <int R, class P>
+__device__ __forceinline__ void wide_passes(const P& pol, const Geom& g, int x0, int y0, int z0,
+                                            typename P::Local& loc, WideFetch<R, P>& f,
+                                            BrickLds<R, P, kWide>& sm, double (&cc)[2]) {
+  using A = typename P::Acc;
+  constexpr int NC = P::NCH, L = kWide + 2 * R, NT = kWideThreads;
+  if (L * L >= NT || threadIdx.x < L * L) brick_zsum<R, kWide>(pol, f.r, threadIdx.x, sm);
+  for (int col = threadIdx.x + NT; col < L * L; col += NT) {  // R > 3
+    float r[kBrickZ + 2 * R][P::NRAW];
+    brick_column<R, kWide>(pol, g, x0, y0, z0, loc, col, r);
+    brick_zsum<R, kWide>(pol, r, col, sm);
+  }
+  __syncthreads();
+  brick_ypass<R, kWide, NT, 4>(pol, sm);
+  __syncthreads();
+  auto& sy = sm.y();
+  cc[0] = cc[1] = 0.0;
+  if (!f.ok0) return;
+  const int ox = (threadIdx.x % 8) * 2, oy = (threadIdx.x / 8) % 16, oz = threadIdx.x / 128;
+  A a[2][NC];
 #pragma unroll
-      for (int c = 0; c < NC; ++c) {
-        if constexpr (P::kBox)
-          a[c] += sy[c][oz][oy][ox + k];
-        else
-          a[c] = fma(A(pol.wt(k)), sy[c][oz][oy][ox + k], a[c]);
-      }
-    const int gx = x0 + ox, gy = y0 + oy, gz = z0 + oz;
-    if (gx < g.nx && gy < g.ny && gz < g.nz) {
-      const int i = (gz * g.ny + gy) * g.nx + gx;
-      typename P::Pre q;
-      pol.pre(i, q);
-      pol.emit(loc, i, q, a);
+  for (int c = 0; c < NC; ++c) {
+    A v[2 + 2 * R], o[2];
+#pragma unroll
+    for (int k = 0; k < 2 + 2 * R; ++k) v[k] = sy[c][oz][oy][ox + k];
+    window_outputs<R, 2>(pol, v, o);
+    a[0][c] = o[0];
+    a[1][c] = o[1];
+  }
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    if (j == 1 && !f.ok1) break;
+    pol.emit(loc, f.i + j, f.q[j], a[j]);
+    if constexpr (P::kSum) {
+      cc[j] = loc.sum;
+      loc.sum = 0.0;
     }
   }
+}
+
+// The partial sums of a wide brick.  Its 2 x 2 small bricks are summed in the
+// order of block_sum_to over a small brick's block (there lane 8 oy + ox of
+// wave oz; here the outputs 2 j and 2 j + 1 of a row share a lane, so the last
+// step of the tree is inside it).  sub: one partial per small brick, at its
+// number in the volume, else their sum to partials[slot].
+__device__ __forceinline__ void wide_partials(const double (&cc)[2], const Geom& g, int x0,
+                                              int y0, int z0, bool sub, int slot,
+                                              double* partials) {
+  __shared__ double red[kBrickZ][2][2];  // plane, half along y, half along x
+  __shared__ double quad[4];
+  double e = cc[0], o = cc[1];
+#pragma unroll
+  for (int off : {32, 16, 8, 2, 1}) {
+    e += __shfl_xor(e, off, 64);
+    o += __shfl_xor(o, off, 64);
+  }
+  const int lane = threadIdx.x & 63;
+  if ((lane & ~4) == 0) red[threadIdx.x / 128][(threadIdx.x / 64) % 2][lane / 4] = e + o;
+  __syncthreads();
+  if (threadIdx.x < 4) {
+    const int px = threadIdx.x & 1, py = threadIdx.x >> 1;
+    double s = 0.0;
+#pragma unroll
+    for (int k = 0; k < kBrickZ; ++k) s += red[k][py][px];
+    if (sub) {
+      const int cx = (g.nx + kT3 - 1) / kT3, cy = (g.ny + kT3 - 1) / kT3;
+      const int bx = x0 / kT3 + px, by = y0 / kT3 + py;
+      if (bx < cx && by < cy) partials[((z0 / kBrickZ) * cy + by) * cx + bx] = s;
+    } else {
+      quad[threadIdx.x] = s;
+    }
+  }
+  if (sub) return;
+  __syncthreads();
+  if (threadIdx.x == 0) partials[slot] = ((quad[0] + quad[1]) + quad[2]) + quad[3];
+}
+
+// A wide brick from fetch to partials.
+template <int R, class P>
+__device__ __forceinline__ void stencil_wide(const P& pol, const Geom& g, int x0, int y0, int z0,
+                                             typename P::Local& loc, WideFetch<R, P>& f,
+                                             BrickLds<R, P, kWide>& sm, bool sub, int slot) {
+  double cc[2];
+  wide_passes<R>(pol, g, x0, y0, z0, loc, f, sm, cc);
+  if constexpr (P::kSum) wide_partials(cc, g, x0, y0, z0, sub, slot, pol.partials);
+}
+
+// Origin of brick b of a volume (x fastest, then y, then z).
+template <int SIDE>
+__device__ __forceinline__ void brick_origin(const Geom& g, int b, int& x0, int& y0, int& z0) {
+  const int cx = (g.nx + SIDE - 1) / SIDE, cy = (g.ny + SIDE - 1) / SIDE;
+  x0 = (b % cx) * SIDE;
+  y0 = ((b / cx) % cy) * SIDE;
+  z0 = (b / (cx * cy)) * kBrickZ;
 }
 
 // Block sum of one double per thread; thread 0 writes it to *out.
@@ -463,7 +617,7 @@ template <typename T, typename AccT = double>
 struct FStatPol {
   using Acc = AccT;
   static constexpr int NRAW = 1, NCH = 2;
-  static constexpr bool kBox = true, kSeparateLds = false;
+  static constexpr bool kBox = true, kSeparateLds = false, kSum = false;
   const T* __restrict__ F;
   double* __restrict__ fstat;  // [2][N]: mu_F, sigma_FF
   int N;
@@ -502,7 +656,7 @@ template <typename T, int NT, typename AccT = double>
 struct FwdPol {
   using Acc = AccT;
   static constexpr int NRAW = 2, NCH = 3;
-  static constexpr bool kBox = true, kSeparateLds = false;
+  static constexpr bool kBox = true, kSeparateLds = false, kSum = true;
   const T* __restrict__ F;
   const float* __restrict__ Mw;
   const double* __restrict__ fstat;
@@ -571,7 +725,7 @@ template <typename T, typename AccT = double>
 struct BwdPol {
   using Acc = AccT;
   static constexpr int NRAW = 4, NCH = 4;
-  static constexpr bool kBox = true, kSeparateLds = true;
+  static constexpr bool kBox = true, kSeparateLds = true, kSum = false;
   const T* __restrict__ F;
   const float* __restrict__ Mw;
   const float* __restrict__ maps;
@@ -636,7 +790,7 @@ template <int R>
 struct SmoothPol {
   using Acc = float;
   static constexpr int NRAW = 3, NCH = 3;
-  static constexpr bool kBox = false, kSeparateLds = false;
+  static constexpr bool kBox = false, kSeparateLds = false, kSum = false;
   const float* __restrict__ in;
   float* __restrict__ out;
   int N;
