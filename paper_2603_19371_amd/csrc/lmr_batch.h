@@ -51,8 +51,13 @@ constexpr int kBarGroups = 8;
 // pairs fill the GPU together, runs wide ones.
 // update work item: a 32 x 8 column (the staged update's tile) over ucz
 // planes: about kBatchUpdateItems items per pair, 2..32 planes each (long
-// marches for large pairs, short ones where a pair has few columns)
+// marches for large pairs, short ones where a pair has few columns), but no
+// more than kBatchUpdateTotal per compute unit over all pairs: an item stages
+// two planes more than it updates, one after another before its first step
+// (32 pairs of 48^3, update phase: 4 per unit 104 us, 8: 87, 16: 87; without
+// the limit, 32 per unit there, 93)
 constexpr int kBatchUpdateTX = 32, kBatchUpdateTY = 8, kBatchUpdateItems = 256;
+constexpr int kBatchUpdateTotal = 8;
 constexpr int kBatchUpdateMinCz = 2, kBatchUpdateMaxCz = 32;
 struct BatchCtl {
   struct alignas(128) Line {
