@@ -20,12 +20,15 @@ __device__ __forceinline__ double clamp_d(double v, double lo, double hi) {
   return v < lo ? lo : (v > hi ? hi : v);
 }
 
-// The sum of the partials in a fixed order, by all NT threads of one block
-// (sh: NT doubles of LDS); the result is valid in thread 0.
-template <int NT>
+// The sum of the partials in a fixed order, by the first NT of the NB threads
+// of one block, all of which call it (sh: NT doubles of LDS); the result is
+// valid in thread 0.
+template <int NT, int NB = NT>
 __device__ double reduce_partials(const double* __restrict__ partials, int nparts,
                                   double* sh) {
-  static_assert(NT >= 64 && (NT & (NT - 1)) == 0, "power-of-two block of whole waves");
+  static_assert(NT >= 64 && (NT & (NT - 1)) == 0 && NB >= NT,
+                "power-of-two block of whole waves");
+  if (NB > NT && threadIdx.x >= NT) nparts = 0;
   // each thread sums partials t, t + NT, t + 2 NT, ... in that order; the
   // first kLoads of them are all requested before the first add, so a level
   // with up to kLoads * NT partials waits for one memory round trip, not one
@@ -42,7 +45,7 @@ __device__ double reduce_partials(const double* __restrict__ partials, int npart
   for (int j = 0; j < kLoads; ++j)
     if (threadIdx.x + j * NT < nparts) s += v[j];
   for (int k = threadIdx.x + kLoads * NT; k < nparts; k += NT) s += partials[k];
-  sh[threadIdx.x] = s;
+  if (NB == NT || threadIdx.x < NT) sh[threadIdx.x] = s;
   __syncthreads();
   // the fixed tree sh[t] += sh[t + w], w = NT/2 ... 1: the steps across waves
   // in LDS, the last six inside wave 0 with the same operands and order

@@ -1,6 +1,6 @@
 // Per-pair launches of the three stencils of an LM attempt (stencil.h):
 // LNCC forward (P2), LNCC + warp backward (P4) and Gaussian smoothing (P5).
-// One block per tile; block ids are remapped so that each XCD receives a
+// One block per pair of tiles or brick; block ids are remapped so that each XCD receives a
 // contiguous range of tiles and shares their halos in its L2.
 #include <algorithm>
 
@@ -12,38 +12,26 @@ namespace lmr {
 
 namespace {
 
-constexpr int kTY = 8;
-
-// Waves per SIMD a stencil instantiation must leave register room for
-// (measured choices; the others keep the compiler's own):
-// * forward pass, BF16 images, compensated FP32 sums: 130 VGPRs left alone,
-//   two above the 128 that allow four waves; asked for four, the compiler
-//   fits it in 128 without spilling (200 -> 151 us at 160x192x224);
-// * backward pass, BF16 images, FP64 sums: 156 VGPRs left alone; at four
-//   waves nine VGPRs spill to scratch, and the attempt is still 5 % faster.
-template <class P>
-struct StencilWaves {
-  static constexpr int value = 1;
-};
-template <int NT>
-struct StencilWaves<FwdPol<uint16_t, NT, F32C>> {
-  static constexpr int value = 4;
-};
-template <>
-struct StencilWaves<BwdPol<uint16_t, double>> {
-  static constexpr int value = 4;
-};
+// The tiling (and with it the chunks, and the partial sums of the forward
+// pass) is in 32 x kTY tiles, as in the batched form; a block runs two of
+// them, one above the other, on two waves per SIMD, and two blocks share a CU
+// (at most 128 VGPRs a thread).  Launches with fewer blocks than CUs (small
+// volumes asked to march) have none to share: there a block runs one tile
+// (attempt at 33x40x45: 28 us, 31 with two tiles; at 64x64x64: 36, 39).
+constexpr int kTY = 8, kMarchTY = 2 * kTY;
+__host__ __device__ inline int march_rows(const Tiling& t) { return (t.tiles_y + 1) / 2; }
 
 // The decision of the attempt inside a pass of NT threads (pass_decision.h):
 // every block reduces the partials and decides on the pair state st; block 0
 // stores the result in pd.next.  Returns the decided state, in LDS.
 template <int NT>
 __device__ const DevState* decide_in_pass(const DevState* st, const PassDecision& pd) {
-  __shared__ double sh[NT];
+  constexpr int kSumThreads = 256;  // the decision kernel's order of the sum
+  __shared__ double sh[kSumThreads];
   __shared__ DevState s_next;
   DevState cur;
   if (threadIdx.x == 0) cur = *st;
-  const double S = reduce_partials<NT>(pd.partials, pd.nparts, sh);
+  const double S = reduce_partials<kSumThreads, NT>(pd.partials, pd.nparts, sh);
   if (threadIdx.x == 0) {
     const DevState n = decide_next(cur, -S / static_cast<double>(pd.N), pd.dp, pd.force);
     if (blockIdx.x == 0) *pd.next = n;
@@ -74,28 +62,52 @@ __device__ __forceinline__ bool pass_state(const DevState* st, int need,
   }
 }
 
-// A marching pass that takes the decision is held to the waves per SIMD the
-// pass has without it (left alone, the compiler gives the decision's registers
-// to the stencil and loses a wave): four with FP64 sums, three with
-// compensated FP32 sums (which spill at four).
-template <class P>
-struct DecidingWaves {
-  static constexpr int value = std::is_same<typename P::Acc, F32C>::value ? 3 : 4;
-};
+// Sums of one double per thread over the halves of a block of NT threads, each
+// in the order of block_sum_to over a block of NT / 2.
+template <int NT>
+__device__ __forceinline__ void half_sums_to(double v, double* lower, double* upper) {
+  constexpr int kWaves = NT / 64;
+  __shared__ double red[kWaves];
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
+  __syncthreads();
+  if (threadIdx.x % (NT / 2) == 0) {
+    const int w0 = threadIdx.x >> 6;
+    double s = 0.0;
+#pragma unroll
+    for (int k = 0; k < kWaves / 2; ++k) s += red[w0 + k];
+    double* out = threadIdx.x == 0 ? lower : upper;
+    if (out) *out = s;
+  }
+}
 
 template <int R, int TY, class P, bool DEC>
 __global__ void __launch_bounds__(kTX* TY)
-    __attribute__((amdgpu_waves_per_eu(DEC ? DecidingWaves<P>::value
-                                           : StencilWaves<P>::value)))
+    __attribute__((amdgpu_waves_per_eu(TY == kMarchTY ? 4 : 2)))
     k_stencil(const P pol, Geom g, Tiling t, const DevState* st, int need, PassDecision pd) {
   const DevState* rs;
   if (!pass_state<kTX * TY, DEC>(st, need, pd, rs)) return;
-  const int tile = xcd_remap(blockIdx.x, gridDim.x);
-  int x0, y0, z0;
-  tile_origin(t, tile, TY, x0, y0, z0);
+  __shared__ StencilLds<R, TY, P> sm[TY == kMarchTY ? 2 : 1];
+  const int b = xcd_remap(blockIdx.x, gridDim.x);
+  const int rows = TY == kMarchTY ? march_rows(t) : t.tiles_y;
+  const int tx = b % t.tiles_x, row = (b / t.tiles_x) % rows, chunk = b / (t.tiles_x * rows);
+  const int z0 = chunk * t.cz;
   typename P::Local loc = pol.begin_block(rs);
-  stencil_tile<R, TY>(pol, g, x0, y0, z0, min(z0 + t.cz, g.nz), loc);
-  pol.end_tile(loc, tile);  // partials in tile order, as in the batched form
+  const int z1 = min(z0 + t.cz, g.nz);
+  // partials in tile order, as in the batched form
+  if constexpr (TY == kTY) {
+    stencil_tile<R, TY>(pol, g, tx * kTX, row * TY, z0, z1, loc, sm[0]);
+    pol.end_tile(loc, b);
+    return;
+  } else {
+    stencil_march<R, TY>(pol, g, tx * kTX, row * TY, z0, z1, loc, sm);
+  }
+  if constexpr (TY == kMarchTY && P::kSum) {
+    double* lower = pol.partials + (chunk * t.tiles_y + 2 * row) * t.tiles_x + tx;
+    half_sums_to<kTX * TY>(loc.sum, lower,
+                                2 * row + 1 < t.tiles_y ? lower + t.tiles_x : nullptr);
+  }
 }
 
 // The same stencil on small bricks (stencil.h).
@@ -132,21 +144,20 @@ __global__ void __launch_bounds__(kWideThreads)
 
 }  // namespace
 
-// Chunk length of the march.  A launch runs its blocks in rounds of
-// 4 x CUs co-resident ones (the forward and backward passes' occupancy with
-// FP64 sums and window 7; the smoothing pass holds 8 per CU but is bound by
-// memory and runs fastest on the same chunks), and each block of a round
-// marches its chunk plus the 2R halo planes, so a launch lasts about
-// ceil(tiles / (4 CUs)) x (cz + 2R) plane steps.  Among the chunk lengths
-// not below make_tiling's floor, take the one that minimises this (the longer
-// chunk on a tie).  It does not depend on the kernel: a box sum's rounding
-// depends on where its chunk starts, and the batched form reproduces a pair's
-// run by using the same tiling for all passes.
+// Chunk length of the march.  A launch runs its blocks in rounds of 2 x CUs
+// co-resident ones, and each block of a round marches its chunk plus the 2R
+// halo planes, so a launch lasts about ceil(blocks / (2 CUs)) x (cz + 2R) plane
+// steps.  Among the chunk lengths not below make_tiling's floor, take the one
+// that minimises this (the longer chunk on a tie).  It does not depend on the
+// kernel: a box sum's rounding depends on where its chunk starts, and the
+// batched form (blocks of one tile, four per CU) reproduces a pair's run by
+// using the same tiling for all passes.
 Tiling march_tiling(const Geom& g, int R) {
   Tiling t = make_tiling(g.nz, g.ny, g.nx, kTY);
-  const long long cols = (long long)t.tiles_x * t.tiles_y;
-  const long long cap = 4LL * device_cus();
-  const int floor_cz = std::min(march_floor_cz(cols, g.nz), g.nz);
+  const long long cols = (long long)t.tiles_x * march_rows(t);
+  const long long cap = 2LL * device_cus();
+  const int floor_cz =
+      std::min(march_floor_cz((long long)t.tiles_x * t.tiles_y, g.nz), g.nz);
   long long best = -1;
   for (int n = 1; n <= g.nz; ++n) {
     const int cz = (g.nz + n - 1) / n;
@@ -203,8 +214,13 @@ hipError_t run(const P& pol, const Geom& g, bool cubes, const DevState* st, int 
       return hipGetLastError();
     }
     const Tiling t = march_tiling(g, R);
-    hipLaunchKernelGGL((k_stencil<R, kTY, P, DEC>), dim3(t.tiles()), dim3(kTX * kTY), 0, s,
-                       pol, g, t, st, need, pd);
+    const int blocks = t.tiles_x * march_rows(t) * t.nchunks;
+    if (blocks < device_cus())
+      hipLaunchKernelGGL((k_stencil<R, kTY, P, DEC>), dim3(t.tiles()), dim3(kTX * kTY), 0, s,
+                         pol, g, t, st, need, pd);
+    else
+      hipLaunchKernelGGL((k_stencil<R, kMarchTY, P, DEC>), dim3(blocks), dim3(kTX * kMarchTY),
+                         0, s, pol, g, t, st, need, pd);
     return hipGetLastError();
   }
 }

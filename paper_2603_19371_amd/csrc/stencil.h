@@ -134,167 +134,232 @@ struct StencilLds {
   typename P::Acc y[P::NCH][TY][kTX + 2 * R];
 };
 
-// Runs the stencil over tile (x0, y0, z0..z1) with the whole block, in the
-// LDS arrays s_in (staged raw inputs) and s_y (y-pass sums).
+// The march of a tile (x0, y0, z0..z1) by a block of kTX x TY threads.  No
+// vector memory operation of a step sits in a branch: a position outside the
+// volume, a plane past the chunk and an output that does not exist use
+// kFarIndex, which loads 0 and stores nothing.  The compiler then knows how
+// many operations follow a load and waits for just that load; with branches it
+// waits for everything in flight, stores included (160x192x224, window 7, BF16
+// images: forward pass 96 -> 77 us; FP32 images: forward 81 -> 79, backward
+// 108 -> 104).
 template <int R, int TY, class P>
-__device__ __forceinline__ void stencil_tile_in(
-    const P& pol, const Geom& g, int x0, int y0, int z0, int z1, typename P::Local& loc,
-    float (&s_in)[P::NRAW][TY + 2 * R][kTX + 2 * R],
-    typename P::Acc (&s_y)[P::NCH][TY][kTX + 2 * R]) {
+struct March {
   using A = typename P::Acc;
-  constexpr int NR = P::NRAW, NC = P::NCH;
-  constexpr int W = 2 * R + 1, LX = kTX + 2 * R, LY = TY + 2 * R, NT = kTX * TY;
-  constexpr int NPOS = LX * LY, PER = (NPOS + NT - 1) / NT;
-  constexpr bool kEarly = !std::is_same<A, F32C>::value;
+  static constexpr int NR = P::NRAW, NC = P::NCH, W = 2 * R + 1;
+  static constexpr int LX = kTX + 2 * R, LY = TY + 2 * R, NT = kTX * TY;
+  static constexpr int NPOS = LX * LY, PER = (NPOS + NT - 1) / NT;
 
-  const int lx = threadIdx.x % kTX, ly = threadIdx.x / kTX;
-  const int gx = x0 + lx, gy = y0 + ly;
-  const bool own = gx < g.nx && gy < g.ny;
-  const int plane = g.ny * g.nx;
-
-  // positions of the halo tile this thread stages
-  int pidx[PER];
+  const P& pol;
+  const Geom& g;
+  const int z0, zend, plane, lx, ly, col;
+  const bool own;
+  int pidx[PER];  // positions of the halo tile this thread stages
   bool pin[PER];
+  float pre[PER][NR];  // the plane in flight
+  A ring[W][NC], run[NC];
+
+  __device__ __forceinline__ March(const P& p, const Geom& geom, int x0, int y0, int z0_, int z1)
+      : pol(p), g(geom), z0(z0_), zend(z1 + R), plane(geom.ny * geom.nx),
+        lx(threadIdx.x % kTX), ly(threadIdx.x / kTX), col((y0 + ly) * geom.nx + x0 + lx),
+        own(x0 + lx < geom.nx && y0 + ly < geom.ny) {
 #pragma unroll
-  for (int p = 0; p < PER; ++p) {
-    const int i = threadIdx.x + p * NT;
-    const int yy = i / LX, xx = i - yy * LX;
-    const int gyy = y0 - R + yy, gxx = x0 - R + xx;
-    pin[p] = i < NPOS && (unsigned)gyy < (unsigned)g.ny && (unsigned)gxx < (unsigned)g.nx;
-    pidx[p] = pin[p] ? gyy * g.nx + gxx : 0;
+    for (int q = 0; q < PER; ++q) {
+      const int i = threadIdx.x + q * NT;
+      const int yy = i / LX, xx = i - yy * LX;
+      const int gyy = y0 - R + yy, gxx = x0 - R + xx;
+      pin[q] = i < NPOS && (unsigned)gyy < (unsigned)g.ny && (unsigned)gxx < (unsigned)g.nx;
+      pidx[q] = pin[q] ? gyy * g.nx + gxx : 0;
+    }
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+      run[c] = A();
+#pragma unroll
+      for (int k = 0; k < W; ++k) ring[k][c] = A();
+    }
   }
-  // Branch-free staging: a padding position (outside the volume in x, y or z)
-  // reads kFarIndex, whose offset lies beyond the buffer and reads 0.
-  float pre[PER][NR];
-  auto fetch = [&](int zi) {
-    const bool zin = (unsigned)zi < (unsigned)g.nz;
+  __device__ __forceinline__ void fetch(const typename P::Local& loc, int zi) {
+    const bool zin = (unsigned)zi < (unsigned)g.nz && zi < zend;
     const unsigned zoff = zin ? static_cast<unsigned>(zi * plane) : 0u;
 #pragma unroll
-    for (int p = 0; p < PER; ++p)
-      pol.load(loc, (zin && pin[p]) ? zoff + static_cast<unsigned>(pidx[p]) : kFarIndex,
-               pre[p]);
-  };
-  auto commit = [&]() {
+    for (int q = 0; q < PER; ++q)
+      pol.load(loc, (zin && pin[q]) ? zoff + static_cast<unsigned>(pidx[q]) : kFarIndex,
+               pre[q]);
+  }
+  __device__ __forceinline__ void commit(StencilLds<R, TY, P>& sm) const {
 #pragma unroll
-    for (int p = 0; p < PER; ++p) {
-      const int i = threadIdx.x + p * NT;
+    for (int q = 0; q < PER; ++q) {
+      const int i = threadIdx.x + q * NT;
       if (i < NPOS) {
         const int yy = i / LX, xx = i - yy * LX;
 #pragma unroll
-        for (int c = 0; c < NR; ++c) s_in[c][yy][xx] = pre[p][c];
+        for (int c = 0; c < NR; ++c) sm.in[c][yy][xx] = pre[q][c];
       }
     }
-  };
-
-  A ring[W][NC], run[NC];
-#pragma unroll
-  for (int c = 0; c < NC; ++c) {
-    run[c] = A();
-#pragma unroll
-    for (int k = 0; k < W; ++k) ring[k][c] = A();
   }
-
-  const int zend = z1 + R;
-  int zi = z0 - R;
-  fetch(zi);
-  while (zi < zend) {
+  // kFarIndex where the plane zo holds no output of this thread
+  __device__ __forceinline__ unsigned out_index(int zo) const {
+    return zo >= z0 && own ? static_cast<unsigned>(zo * plane + col) : kFarIndex;
+  }
+  __device__ __forceinline__ void operands(unsigned io, typename P::Pre& q) const {
+    pol.pre(io != kFarIndex ? io : 0u, q);
+  }
+  // fence > 0: at most that many taps of the window in flight (see below)
+  template <int FENCE>
+  __device__ __forceinline__ void ypass(StencilLds<R, TY, P>& sm) const {
+    for (int i = threadIdx.x; i < TY * LX; i += NT) {
+      const int yy = i / LX, xx = i - yy * LX;
+      A a[NC];
 #pragma unroll
-    for (int s = 0; s < W; ++s) {
-      if (zi < zend) {
-        commit();
-        // with FP64 sums the operands of this step's output are requested
-        // before the next plane, so that they arrive during the y pass (read
-        // at their use, a block waits a memory round trip per plane; forward
-        // pass at 160x192x224, w 7: 90.5 -> 85.5 us).  The compensated sums
-        // have no registers to hold them (121x145x119, w 9: 346 -> 351 us).
-        const int zo = zi - R;
-        const bool out = zo >= z0 && own;
-        const int io = zo * plane + gy * g.nx + gx;
-        typename P::Pre q;
-        if (kEarly && out) pol.pre(io, q);
-        if (zi + 1 < zend) fetch(zi + 1);
-        __syncthreads();
-        for (int i = threadIdx.x; i < TY * LX; i += NT) {
-          const int yy = i / LX, xx = i - yy * LX;
-          A a[NC];
+      for (int c = 0; c < NC; ++c) a[c] = A();
 #pragma unroll
-          for (int c = 0; c < NC; ++c) a[c] = A();
+      for (int k = 0; k < W; ++k) {
+        float r[NR];
 #pragma unroll
-          for (int k = 0; k < W; ++k) {
-            float r[NR];
-#pragma unroll
-            for (int c = 0; c < NR; ++c) r[c] = s_in[c][yy + k][xx];
-            pol.accum(a, r, k);
-          }
-#pragma unroll
-          for (int c = 0; c < NC; ++c) s_y[c][yy][xx] = a[c];
-        }
-        __syncthreads();
-        A pl[NC];
-#pragma unroll
-        for (int c = 0; c < NC; ++c) pl[c] = A();
-#pragma unroll
-        for (int k = 0; k < W; ++k)
-#pragma unroll
-          for (int c = 0; c < NC; ++c) {
-            if constexpr (P::kBox)
-              pl[c] += s_y[c][ly][lx + k];
-            else
-              pl[c] = fma(A(pol.wt(k)), s_y[c][ly][lx + k], pl[c]);
-          }
-        A sm[NC];
-        if constexpr (P::kBox) {
-          // ring[s] holds the plane that entered W steps ago
-#pragma unroll
-          for (int c = 0; c < NC; ++c) {
-            run[c] += pl[c] - ring[s][c];
-            ring[s][c] = pl[c];
-            sm[c] = run[c];
-          }
-        } else {
-#pragma unroll
-          for (int c = 0; c < NC; ++c) {
-            ring[s][c] = pl[c];
-            sm[c] = A(0);
-          }
-          // planes zi-2R .. zi sit in slots s+1 .. s+W (mod W)
-#pragma unroll
-          for (int k = 0; k < W; ++k)
-#pragma unroll
-            for (int c = 0; c < NC; ++c)
-              sm[c] = fma(A(pol.wt(k)), ring[(s + 1 + k) % W][c], sm[c]);
-        }
-        if (out) {
-          if (!kEarly) pol.pre(io, q);
-          pol.emit(loc, io, q, sm);
-        }
+        for (int c = 0; c < NR; ++c) r[c] = sm.in[c][yy + k][xx];
+        pol.accum(a, r, k);
+        if constexpr (FENCE > 0)
+          if (k % FENCE == FENCE - 1) __builtin_amdgcn_sched_barrier(0);
       }
-      ++zi;
+#pragma unroll
+      for (int c = 0; c < NC; ++c) sm.y[c][yy][xx] = a[c];
     }
+  }
+  // the window sums of the plane whose y pass is in sm; S: its ring slot
+  template <int S, int FENCE>
+  __device__ __forceinline__ void xpass(const StencilLds<R, TY, P>& sm, A (&o)[NC]) {
+    A pl[NC];
+#pragma unroll
+    for (int c = 0; c < NC; ++c) pl[c] = A();
+#pragma unroll
+    for (int k = 0; k < W; ++k) {
+#pragma unroll
+      for (int c = 0; c < NC; ++c) {
+        if constexpr (P::kBox)
+          pl[c] += sm.y[c][ly][lx + k];
+        else
+          pl[c] = fma(A(pol.wt(k)), sm.y[c][ly][lx + k], pl[c]);
+      }
+      if constexpr (FENCE > 0)
+        if (k % FENCE == FENCE - 1) __builtin_amdgcn_sched_barrier(0);
+    }
+    if constexpr (P::kBox) {
+      // ring[S] holds the plane that entered W steps ago
+#pragma unroll
+      for (int c = 0; c < NC; ++c) {
+        run[c] += pl[c] - ring[S][c];
+        ring[S][c] = pl[c];
+        o[c] = run[c];
+      }
+    } else {
+#pragma unroll
+      for (int c = 0; c < NC; ++c) {
+        ring[S][c] = pl[c];
+        o[c] = A(0);
+      }
+      // planes zi-2R .. zi sit in slots S+1 .. S+W (mod W)
+#pragma unroll
+      for (int k = 0; k < W; ++k)
+#pragma unroll
+        for (int c = 0; c < NC; ++c)
+          o[c] = fma(A(pol.wt(k)), ring[(S + 1 + k) % W][c], o[c]);
+    }
+  }
+};
+
+// One step of stencil_tile: plane zi, in ring slot S.
+template <int S, int R, int TY, class P>
+__device__ __forceinline__ void tile_step(March<R, TY, P>& m, int zi, typename P::Local& loc,
+                                          StencilLds<R, TY, P>& sm) {
+  // with FP64 sums the operands of this step's output are requested before the
+  // next plane, so that they arrive during the y pass (read at their use, a
+  // block waits a memory round trip per plane; forward pass at 160x192x224,
+  // w 7: 90.5 -> 85.5 us).  The compensated sums have no registers to hold
+  // them (121x145x119, w 9: 346 -> 351 us).
+  constexpr bool kEarly = !std::is_same<typename P::Acc, F32C>::value;
+  m.commit(sm);
+  const unsigned io = m.out_index(zi - R);
+  typename P::Pre q;
+  if (kEarly) m.operands(io, q);
+  m.fetch(loc, zi + 1);
+  __syncthreads();
+  m.template ypass<0>(sm);
+  __syncthreads();
+  typename P::Acc o[P::NCH];
+  m.template xpass<S, 0>(sm, o);
+  if (!kEarly) m.operands(io, q);
+  m.pol.emit(loc, io, q, o);
+}
+
+// Calls f(slot) for the slots 0 .. W-1 in turn, until it returns true.
+template <int S, int W, class F>
+__device__ __forceinline__ bool each_slot(F&& f) {
+  if constexpr (S < W) {
+    if (f(std::integral_constant<int, S>{})) return true;
+    return each_slot<S + 1, W>(f);
+  } else {
+    return false;
   }
 }
 
-// In the LDS `sm` (a kernel that runs several phases overlays their LDS).
+// The stencil over a tile, two barriers per plane, in the LDS `sm` (the
+// batched kernels, whose phases overlay their LDS and fill the GPU with blocks
+// of one size).
 template <int R, int TY, class P>
 __device__ __forceinline__ void stencil_tile(const P& pol, const Geom& g, int x0, int y0,
                                              int z0, int z1, typename P::Local& loc,
                                              StencilLds<R, TY, P>& sm) {
-  stencil_tile_in<R, TY>(pol, g, x0, y0, z0, z1, loc, sm.in, sm.y);
+  March<R, TY, P> m(pol, g, x0, y0, z0, z1);
+  int zi = z0 - R;
+  m.fetch(loc, zi);
+  while (!each_slot<0, 2 * R + 1>([&](auto s) {
+    tile_step<decltype(s)::value>(m, zi, loc, sm);
+    return ++zi == m.zend;
+  })) {
+  }
 }
 
-// In LDS of its own.  Both forms give the same results; the compiler
-// schedules them differently, and the backward pass runs faster with two
-// separate arrays, the others with one struct (measured).
+// The stencil over a tile with one barrier per plane, on two copies of the
+// LDS: after the barrier of plane zi a block runs the y pass of that plane,
+// stages the next one into the other copy and runs the x pass of plane zi - 1
+// from there, so the LDS reads of one overlap the sums of the other.  With
+// 32 x 16 tiles two blocks share a CU and a plane's halo rows are read 22 times
+// for 16 rows of outputs, not 14 for 8 (what bounds the passes is how fast
+// halo lines come from the caches: loads and stores alone take 90 of the
+// backward pass's 104 us on 32 x 8 tiles, 81 on 32 x 16).  kFence keeps the
+// compiler from requesting all taps of a window at once, whose registers it
+// would spill: 160x192x224, window 7, FP64 sums, forward 73 us either way,
+// backward 102 -> 89 (window 9: 190 -> 127).  The smoothing pass has the
+// registers (57 us; 61 with fences).  Against the two-barrier form on 32 x 8
+// tiles: forward 79 -> 72 us, backward 104 -> 89, smoothing 62 -> 57; with
+// compensated FP32 sums and window 9 forward 223 -> 147, backward 256 -> 190.
 template <int R, int TY, class P>
-__device__ __forceinline__ void stencil_tile(const P& pol, const Geom& g, int x0, int y0,
-                                             int z0, int z1, typename P::Local& loc) {
-  if constexpr (P::kSeparateLds) {
-    __shared__ float s_in[P::NRAW][TY + 2 * R][kTX + 2 * R];
-    __shared__ typename P::Acc s_y[P::NCH][TY][kTX + 2 * R];
-    stencil_tile_in<R, TY>(pol, g, x0, y0, z0, z1, loc, s_in, s_y);
-  } else {
-    __shared__ StencilLds<R, TY, P> sm;
-    stencil_tile_in<R, TY>(pol, g, x0, y0, z0, z1, loc, sm.in, sm.y);
+__device__ __forceinline__ void stencil_march(const P& pol, const Geom& g, int x0, int y0,
+                                              int z0, int z1, typename P::Local& loc,
+                                              StencilLds<R, TY, P> (&sm)[2]) {
+  constexpr int kFenceY = P::kBox ? 4 : 0, kFenceX = P::kBox ? 1 : 0;
+  March<R, TY, P> m(pol, g, x0, y0, z0, z1);
+  int zi = z0 - R, b = 1;
+  m.fetch(loc, zi);
+  m.commit(sm[0]);
+  m.fetch(loc, zi + 1);
+  __syncthreads();
+  m.template ypass<kFenceY>(sm[0]);
+  m.commit(sm[1]);
+  m.fetch(loc, zi + 2);
+  while (!each_slot<0, 2 * R + 1>([&](auto s) {
+    __syncthreads();
+    const unsigned io = m.out_index(zi - R);
+    typename P::Pre q;
+    m.operands(io, q);
+    m.template ypass<kFenceY>(sm[b]);  // plane zi + 1
+    m.commit(sm[b ^ 1]);               // plane zi + 2: sm[b ^ 1].in was read a step ago
+    m.fetch(loc, zi + 3);
+    typename P::Acc o[P::NCH];
+    m.template xpass<decltype(s)::value, kFenceX>(sm[b ^ 1], o);
+    pol.emit(loc, io, q, o);
+    b ^= 1;
+    return ++zi == m.zend;
+  })) {
   }
 }
 
@@ -617,7 +682,7 @@ template <typename T, typename AccT = double>
 struct FStatPol {
   using Acc = AccT;
   static constexpr int NRAW = 1, NCH = 2;
-  static constexpr bool kBox = true, kSeparateLds = false, kSum = false;
+  static constexpr bool kBox = true, kSum = false;
   const T* __restrict__ F;
   double* __restrict__ fstat;  // [2][N]: mu_F, sigma_FF
   int N;
@@ -640,8 +705,9 @@ struct FStatPol {
       a[1] = fma(f, f, a[1]);
     }
   }
-  __device__ void pre(int, Pre&) const {}
-  __device__ void emit(Local&, int i, const Pre&, const Acc S[2]) const {
+  __device__ void pre(unsigned, Pre&) const {}
+  __device__ void emit(Local&, unsigned i, const Pre&, const Acc S[2]) const {
+    if (i == kFarIndex) return;
     const double muF = to_f64(S[0]) * inv_n;
     fstat[i] = muF;
     fstat[N + i] = to_f64(S[1]) * inv_n - muF * muF;
@@ -656,7 +722,7 @@ template <typename T, int NT, typename AccT = double>
 struct FwdPol {
   using Acc = AccT;
   static constexpr int NRAW = 2, NCH = 3;
-  static constexpr bool kBox = true, kSeparateLds = false, kSum = true;
+  static constexpr bool kBox = true, kSum = true;
   const T* __restrict__ F;
   const float* __restrict__ Mw;
   const double* __restrict__ fstat;
@@ -667,7 +733,7 @@ struct FwdPol {
   double inv_n, eps;
   struct Local {
     double sum;
-    RBuf bF, bM;
+    RBuf bF, bM, out[4];
   };
   struct Pre {
     double muF, sff;
@@ -675,7 +741,10 @@ struct FwdPol {
 
   __device__ static constexpr double wt(int) { return 1.0; }
   __device__ Local begin_block(const DevState*) const {
-    return Local{0.0, make_rbuf_n(F, N), make_rbuf_n(Mw, N)};
+    Local l{0.0, make_rbuf_n(F, N), make_rbuf_n(Mw, N), {}};
+#pragma unroll
+    for (int c = 0; c < 4; ++c) l.out[c] = make_rbuf_n(maps + (size_t)c * N, N);
+    return l;
   }
   __device__ void load(const Local& l, unsigned i, float v[2]) const {
     v[0] = bld<T>(l.bF, i);
@@ -693,11 +762,11 @@ struct FwdPol {
       a[2] = fma(f, m, a[2]);
     }
   }
-  __device__ void pre(int i, Pre& q) const {
+  __device__ void pre(unsigned i, Pre& q) const {
     q.muF = fstat[i];
     q.sff = fstat[N + i];
   }
-  __device__ void emit(Local& loc, int i, const Pre& q, const Acc S[3]) const {
+  __device__ void emit(Local& loc, unsigned i, const Pre& q, const Acc S[3]) const {
     const double muF = q.muF, sff = q.sff;
     const double muM = to_f64(S[0]) * inv_n;
     const double sfm = to_f64(S[2]) * inv_n - muF * muM;
@@ -706,12 +775,12 @@ struct FwdPol {
     const double c = sfm * sfm * iD;
     const double alpha = 2.0 * sfm * iD;
     const double beta = -c * sff * iD;
-    maps[i] = static_cast<float>(alpha);
-    maps[N + i] = static_cast<float>(alpha * muF);
-    maps[2 * N + i] = static_cast<float>(beta);
-    maps[3 * N + i] = static_cast<float>(beta * muM);
-    if (cc) cc[i] = static_cast<float>(c);
-    loc.sum += c;
+    bst(loc.out[0], i, static_cast<float>(alpha));
+    bst(loc.out[1], i, static_cast<float>(alpha * muF));
+    bst(loc.out[2], i, static_cast<float>(beta));
+    bst(loc.out[3], i, static_cast<float>(beta * muM));
+    if (cc && i != kFarIndex) cc[i] = static_cast<float>(c);
+    loc.sum += i != kFarIndex ? c : 0.0;
   }
   // partial sum of cc of the tile just processed, to partials[slot]
   __device__ void end_tile(Local& loc, int slot) const {
@@ -725,7 +794,7 @@ template <typename T, typename AccT = double>
 struct BwdPol {
   using Acc = AccT;
   static constexpr int NRAW = 4, NCH = 4;
-  static constexpr bool kBox = true, kSeparateLds = true, kSum = false;
+  static constexpr bool kBox = true, kSum = false;
   const T* __restrict__ F;
   const float* __restrict__ Mw;
   const float* __restrict__ maps;
@@ -739,7 +808,7 @@ struct BwdPol {
   Geom g;
   double inv_n;
   struct Local {
-    RBuf bmap[4];
+    RBuf bmap[4], out[3];
   };
   struct Pre {
     float f, m, d[3];
@@ -751,6 +820,8 @@ struct BwdPol {
     Local l;
 #pragma unroll
     for (int c = 0; c < 4; ++c) l.bmap[c] = make_rbuf_n(maps + c * N, N);
+#pragma unroll
+    for (int c = 0; c < 3; ++c) l.out[c] = make_rbuf_n(graw + c * N, N);
     return l;
   }
   __device__ void load(const Local& l, unsigned i, float v[4]) const {
@@ -766,21 +837,20 @@ struct BwdPol {
         a[c] += static_cast<double>(r[c]);
     }
   }
-  __device__ void pre(int i, Pre& q) const {
+  __device__ void pre(unsigned i, Pre& q) const {
     const int N = static_cast<int>(g.N);
     q.f = ldf(F, i);
     q.m = Mw[i];
 #pragma unroll
     for (int c = 0; c < 3; ++c) q.d[c] = dMw[c * N + i];
   }
-  __device__ void emit(const Local&, int i, const Pre& q, const Acc Bs[4]) const {
-    const int N = static_cast<int>(g.N);
+  __device__ void emit(const Local& l, unsigned i, const Pre& q, const Acc Bs[4]) const {
     const double fj = q.f, mj = q.m;
     const double B[4] = {to_f64(Bs[0]), to_f64(Bs[1]), to_f64(Bs[2]), to_f64(Bs[3])};
     const double dS = (fj * B[0] - B[1] + 2.0 * mj * B[2] - 2.0 * B[3]) * inv_n;
     const float d = static_cast<float>(dS);
 #pragma unroll
-    for (int c = 0; c < 3; ++c) graw[c * N + i] = -d * q.d[c];
+    for (int c = 0; c < 3; ++c) bst(l.out[c], i, -d * q.d[c]);
   }
   __device__ void end_tile(Local&, int) const {}
 };
@@ -790,19 +860,25 @@ template <int R>
 struct SmoothPol {
   using Acc = float;
   static constexpr int NRAW = 3, NCH = 3;
-  static constexpr bool kBox = false, kSeparateLds = false, kSum = false;
+  static constexpr bool kBox = false, kSum = false;
   const float* __restrict__ in;
   float* __restrict__ out;
   int N;
   float w[2 * R + 1];
   struct Local {
-    RBuf b[3];
+    RBuf b[3], out[3];
   };
   struct Pre {};
 
   __device__ float wt(int k) const { return w[k]; }
   __device__ Local begin_block(const DevState*) const {
-    return Local{{make_rbuf_n(in, N), make_rbuf_n(in + N, N), make_rbuf_n(in + 2 * N, N)}};
+    Local l;
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      l.b[c] = make_rbuf_n(in + (size_t)c * N, N);
+      l.out[c] = make_rbuf_n(out + (size_t)c * N, N);
+    }
+    return l;
   }
   __device__ void load(const Local& l, unsigned i, float v[3]) const {
 #pragma unroll
@@ -812,11 +888,10 @@ struct SmoothPol {
 #pragma unroll
     for (int c = 0; c < 3; ++c) a[c] = fmaf(w[k], r[c], a[c]);
   }
-  __device__ void pre(int, Pre&) const {}
-  __device__ void emit(Local&, int i, const Pre&, const float S[3]) const {
-    out[i] = S[0];
-    out[N + i] = S[1];
-    out[2 * N + i] = S[2];
+  __device__ void pre(unsigned, Pre&) const {}
+  __device__ void emit(Local& l, unsigned i, const Pre&, const float S[3]) const {
+#pragma unroll
+    for (int c = 0; c < 3; ++c) bst(l.out[c], i, S[c]);
   }
   __device__ void end_tile(Local&, int) const {}
 };
