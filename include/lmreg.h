@@ -378,9 +378,9 @@ void lmr_pyramid_destroy(lmr_pyramid* pyr);
  * replayed.  The batch owns a non-blocking stream; results of one pair are
  * read through lmr_batch_pair (borrowed context).  Box side 3..9 and
  * Gaussian radius ceil(3 sigma) <= 4 are supported (else LMR_EINVAL).  A pair
- * that a stand-alone context with p->stencil runs on 8 x 8 bricks runs on
- * bricks here too; the others march (LMR_STENCIL_MARCH); either way a
- * pair follows the stand-alone context with that form bit for bit.
+ * of at most 2^19 voxels that a stand-alone context with p->stencil runs on
+ * bricks runs on bricks here too; the others march (LMR_STENCIL_MARCH); either
+ * way a pair follows the stand-alone context with that form bit for bit.
  *
  * Co-residency (persistent launches only).  The persistent launch needs all
  * its blocks on the GPU at once; the caller must not run other kernels at

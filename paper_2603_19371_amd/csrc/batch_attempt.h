@@ -162,6 +162,29 @@ __device__ __forceinline__ int owner(const BatchPair* __restrict__ pairs, int np
 template <int R, class P, int BR>
 using SmallLds = std::conditional_t<BR != 0, BrickLds<R, P, kT3>, char>;
 
+// The decision of pair P, or its begin, by one block.  The partials are in
+// the order of a stand-alone context's: a wide brick's is the sum of its
+// small bricks', row by row (those outside the volume count as 0).
+__device__ __forceinline__ void decide_pair(const BatchPair& P, const DecideParams& dp,
+                                            int mode) {
+  if (P.nwide == 0) {
+    decide_block<kNT>(P.st, [&](int k) { return P.partials[k]; }, P.ntiles, P.g.N, dp, mode,
+                      -1, P.lambda0, nullptr);
+    return;
+  }
+  const int cx = (P.g.nx + kT3 - 1) / kT3, cy = (P.g.ny + kT3 - 1) / kT3;
+  const int wx = (P.g.nx + kWide - 1) / kWide, wy = (P.g.ny + kWide - 1) / kWide;
+  auto part = [&](int k) {
+    const int bx = 2 * (k % wx), by = 2 * ((k / wx) % wy), bz = k / (wx * wy);
+    const double* row = P.partials + ((long long)bz * cy + by) * cx + bx;
+    const bool x1 = bx + 1 < cx, y1 = by + 1 < cy;
+    const double q0 = row[0], q1 = x1 ? row[1] : 0.0;
+    const double q2 = y1 ? row[cx] : 0.0, q3 = x1 && y1 ? row[cx + 1] : 0.0;
+    return ((q0 + q1) + q2) + q3;
+  };
+  decide_block<kNT>(P.st, part, P.nwide, P.g.N, dp, mode, -1, P.lambda0, nullptr);
+}
+
 // One work item of each phase, shared by the persistent kernel (a grid-stride
 // loop per phase, grid barriers between them) and the per-phase kernels (one
 // item per block, k_batch_phases.hip).  FORM: 0 marching pairs only (an item
@@ -324,8 +347,7 @@ __global__ void __launch_bounds__(kNT)
   if (!grid_sync(ctl, nb, timeout)) return;
   // P3: per-pair FP64 reduction and decision
   for (int p = blockIdx.x; p < npairs; p += nb) {
-    const BatchPair& P = pairs[p];
-    decide_block<kNT>(P.st, P.partials, P.ntiles, P.g.N, dp, 0, -1, 0.0, nullptr);
+    decide_pair(pairs[p], dp, 0);
   }
   if (!grid_sync(ctl, nb, timeout)) return;
   for (int it = blockIdx.x; it < n_tiles; it += nb)

@@ -22,10 +22,9 @@ __device__ __forceinline__ double clamp_d(double v, double lo, double hi) {
 
 // The sum of the partials in a fixed order, by the first NT of the NB threads
 // of one block, all of which call it (sh: NT doubles of LDS); the result is
-// valid in thread 0.
-template <int NT, int NB = NT>
-__device__ double reduce_partials(const double* __restrict__ partials, int nparts,
-                                  double* sh) {
+// valid in thread 0.  part(k): the k-th partial, k < nparts.
+template <int NT, int NB = NT, class Part>
+__device__ double reduce_partials(const Part& part, int nparts, double* sh) {
   static_assert(NT >= 64 && (NT & (NT - 1)) == 0 && NB >= NT,
                 "power-of-two block of whole waves");
   if (NB > NT && threadIdx.x >= NT) nparts = 0;
@@ -38,13 +37,13 @@ __device__ double reduce_partials(const double* __restrict__ partials, int npart
 #pragma unroll
   for (int j = 0; j < kLoads; ++j) {
     const int k = threadIdx.x + j * NT;
-    v[j] = k < nparts ? partials[k] : 0.0;
+    v[j] = k < nparts ? part(k) : 0.0;
   }
   double s = 0.0;
 #pragma unroll
   for (int j = 0; j < kLoads; ++j)
     if (threadIdx.x + j * NT < nparts) s += v[j];
-  for (int k = threadIdx.x + kLoads * NT; k < nparts; k += NT) s += partials[k];
+  for (int k = threadIdx.x + kLoads * NT; k < nparts; k += NT) s += part(k);
   if (NB == NT || threadIdx.x < NT) sh[threadIdx.x] = s;
   __syncthreads();
   // the fixed tree sh[t] += sh[t + w], w = NT/2 ... 1: the steps across waves
@@ -135,15 +134,15 @@ __device__ inline void decide_write(DevState* st, const DevState& cur, double L,
 
 // The same from the partials, by all NT threads of one block; uses NT doubles
 // of LDS.
-template <int NT>
-__device__ void decide_block(DevState* st, const double* __restrict__ partials,
-                             int nparts, long long N, const DecideParams& dp, int mode,
-                             int force, double lambda0, double* probe) {
+template <int NT, class Part>
+__device__ void decide_block(DevState* st, const Part& part, int nparts, long long N,
+                             const DecideParams& dp, int mode, int force, double lambda0,
+                             double* probe) {
   __shared__ double sh[NT];
   // thread 0 fetches the state while the partials are being loaded
   DevState cur_st;
   if (threadIdx.x == 0) cur_st = *st;
-  const double S = reduce_partials<NT>(partials, nparts, sh);
+  const double S = reduce_partials<NT>(part, nparts, sh);
   if (threadIdx.x == 0)
     decide_write(st, cur_st, -S / static_cast<double>(N), dp, mode, force, lambda0, probe);
   __syncthreads();

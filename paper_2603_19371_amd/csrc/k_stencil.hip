@@ -31,7 +31,8 @@ __device__ const DevState* decide_in_pass(const DevState* st, const PassDecision
   __shared__ DevState s_next;
   DevState cur;
   if (threadIdx.x == 0) cur = *st;
-  const double S = reduce_partials<kSumThreads, NT>(pd.partials, pd.nparts, sh);
+  const double S = reduce_partials<kSumThreads, NT>([&](int k) { return pd.partials[k]; },
+                                                    pd.nparts, sh);
   if (threadIdx.x == 0) {
     const DevState n = decide_next(cur, -S / static_cast<double>(pd.N), pd.dp, pd.force);
     if (blockIdx.x == 0) *pd.next = n;
@@ -297,9 +298,11 @@ hipError_t smooth_r(const float* in, float* out, const Geom& g, const lmr_params
 
 }  // namespace
 
-bool small_bricks(const Geom& g, const lmr_params& p) {
-  return use_cubes(g, p) && !use_wide(g);
+bool batch_bricks(const Geom& g, const lmr_params& p) {
+  return use_cubes(g, p) && g.N <= kBatchBrickMaxVoxels;
 }
+
+bool wide_partials_of(const Geom& g) { return use_wide(g); }
 
 int fwd_num_blocks(const Geom& g, const lmr_params& p) {
   return use_cubes(g, p) ? brick_blocks(g) : march_tiling(g, p.window / 2).tiles();

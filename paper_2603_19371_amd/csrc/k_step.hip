@@ -210,7 +210,8 @@ __global__ void __launch_bounds__(kDecideThreads)
     k_decide(DevState* st, const double* __restrict__ partials, int nparts,
              long long N, DecideParams dp, int mode, int force, double lambda0,
              double* probe) {
-  decide_block<kDecideThreads>(st, partials, nparts, N, dp, mode, force, lambda0, probe);
+  decide_block<kDecideThreads>(st, [=](int k) { return partials[k]; }, nparts, N, dp, mode,
+                               force, lambda0, probe);
 }
 
 __global__ void k_copy_cur(const DevState* __restrict__ st, const float* U0,

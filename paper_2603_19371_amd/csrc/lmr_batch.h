@@ -17,12 +17,13 @@ struct BatchPair {
   float* graw;
   float* maps;
   float* Mw;
-  const double* fstat;  // window mean and variance of F (the pair context's)
+  double* fstat;     // window mean and variance of F (the pair context's)
   double* partials;  // one slot per stencil tile of this pair
   DevState* st;
   Tiling t;          // stencil tiling of this pair (marching form)
   int bricks;        // 1: the stencil work items are bricks
   int ntiles;        // cc partials of this pair: its marching tiles or small bricks
+  int nwide;         // > 0: its loss sums them by wide bricks, of which there are so many
   int utile0;        // first update work item of this pair
   int ucz;           // planes per update work item of this pair
   int tile0;         // first stencil work item of this pair (marching tiles, small bricks)
@@ -30,6 +31,7 @@ struct BatchPair {
   float eps;
   int compositive;
   double inv_n, cc_eps;
+  double lambda0;    // of the last begin
   float gw[16];      // Gaussian taps, 2R+1 <= 9 used
 };
 
@@ -44,11 +46,12 @@ struct BatchPair {
 // it is at, and no plain store to a counter has to be ordered against the
 // atomics of blocks on other chiplets.
 constexpr int kBarGroups = 8;
-// The pairs that a stand-alone context runs on small bricks run on bricks
-// here too, and their run is the stand-alone run bit for bit: an output does
-// not depend on its brick, and a cc partial is a small brick's in both.  The
-// persistent kernel keeps the small bricks; one launch per phase, where the
-// pairs fill the GPU together, runs wide ones.
+// The pairs that a stand-alone context runs on bricks run on bricks here too,
+// and their run is the stand-alone run bit for bit: an output does not depend
+// on its brick, a cc partial here is a small brick's, and the decision first
+// sums those of a wide brick where the context's partials are wide ones.  The
+// persistent kernel runs small bricks; one launch per phase, where the pairs
+// fill the GPU together, wide ones.
 // update work item: a 32 x 8 column (the staged update's tile) over ucz
 // planes: about kBatchUpdateItems items per pair, 2..32 planes each (long
 // marches for large pairs, short ones where a pair has few columns), but no
@@ -91,6 +94,11 @@ hipError_t launch_batch_phases(lmr_dtype t, lmr_accum accum, int box_radius,
                                int gauss_radius, bool march, const BatchPair* pairs,
                                int npairs, int n_update_items, int n_tiles, int n_wide,
                                const DecideParams& dp, hipStream_t s);
+// The begin of every pair on bricks from the identity, one launch per phase.
+hipError_t launch_batch_begin(lmr_dtype t, lmr_accum accum, int box_radius, int gauss_radius,
+                              const BatchPair* pairs, int npairs, int n_update_items,
+                              int n_tiles, int n_wide, const DecideParams& dp,
+                              hipStream_t s);
 // timeout: ticks of a barrier wait; start_timeout: ticks after which a
 // block waiting at the first barrier of a launch gives up if some block of
 // the grid has not started; missing: 0, or 1 to make block 0 of every launch

@@ -114,10 +114,15 @@ __host__ __device__ inline Tiling make_tiling(int nz, int ny, int nx, int ty,
   return t;
 }
 
-// Whether the stencil passes of a stand-alone context run on small bricks
-// (kT3 x kT3 columns, the smallest volumes; else on wide bricks or marching,
-// k_stencil.hip), and the number of small and of wide bricks of a volume.
-bool small_bricks(const Geom& g, const lmr_params& p);
+// Whether a pair of a batch runs on bricks: where a stand-alone context does,
+// up to kBatchBrickMaxVoxels (larger pairs fill the GPU together and march as
+// fast: 16 of 64x64x72 on bricks 303 us per attempt, marching 360; 4 of
+// 96x96x96 198 and 180); whether that context's bricks are wide ones, so
+// that its partial sums of cc are (k_stencil.hip); and the number of small and
+// of wide bricks of a volume.
+constexpr long long kBatchBrickMaxVoxels = 1LL << 19;
+bool batch_bricks(const Geom& g, const lmr_params& p);
+bool wide_partials_of(const Geom& g);
 __host__ __device__ inline int bricks_of(const Geom& g, int side, int depth) {
   return ((g.nx + side - 1) / side) * ((g.ny + side - 1) / side) * ((g.nz + depth - 1) / depth);
 }
