@@ -331,26 +331,28 @@ lmr_status lmr_begin(lmr_ctx* c, const void* F, const void* M, const float* fiel
   if (!c || !F || !M || !(lambda0 > 0.0)) return LMR_EINVAL;
   hipStream_t s = c->stream;
   const size_t bytes = sizeof(float) * 3 * c->g.N;
-  if (!field)
-    LMR_HIP(launch_fill(c->U[0], 3 * c->g.N, 0.0f, s));
-  else if (field != c->U[0])  // a field already in place is kept as it is
+  if (field && field != c->U[0])  // a field already in place is kept as it is
     LMR_HIP(hipMemcpyAsync(c->U[0], field, bytes, hipMemcpyDeviceToDevice, s));
+  auto warp = [&] {
+    return field ? launch_warp(M, c->img, c->U[0], c->g, c->Mw, c->graw, s)
+                 : launch_warp_identity(M, c->img, c->U[0], c->g, c->Mw, c->graw, s);
+  };
   const int sim = c->p.similarity;
   if (sim == LMR_SIM_LNCC) {
     LMR_HIP(launch_fstat(F, c->img, c->g, c->p, c->fstat, s));
     c->fstat_of = F;
-    LMR_HIP(launch_warp(M, c->img, c->U[0], c->g, c->Mw, c->graw, s));
+    LMR_HIP(warp());
     LMR_HIP(launch_fwd(F, c->img, c->Mw, c->fstat, c->g, c->p, nullptr, c->maps,
                        c->partials, c->nparts, nullptr, s));
   } else if (sim == LMR_SIM_MI) {
     LMR_HIP(launch_mi_range(F, M, c->img, c->g, c->p.mi_bins, c->mi_rpart, c->mi_map, s));
     c->mi_of[0] = F;
     c->mi_of[1] = M;
-    LMR_HIP(launch_warp(M, c->img, c->U[0], c->g, c->Mw, c->graw, s));
+    LMR_HIP(warp());
     LMR_HIP(launch_mi_fwd(F, c->img, c->Mw, c->g, c->p.mi_bins, c->mi_map, c->mi_hpart,
                           c->mi_tab, c->st, MiDecision{c->dp, 1, -1, lambda0, nullptr}, s));
   } else {
-    LMR_HIP(launch_warp(M, c->img, c->U[0], c->g, c->Mw, c->graw, s));
+    LMR_HIP(warp());
     LMR_HIP(launch_mse_fwd(F, c->img, c->Mw, c->g, c->nparts, c->partials, nullptr, nullptr,
                            s));
   }

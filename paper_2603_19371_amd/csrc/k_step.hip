@@ -32,15 +32,27 @@ __device__ __forceinline__ bool voxel(const Geom& g, int& x, int& y, int& z, int
   return true;
 }
 
-template <typename T>
+// ZERO: the identity, u is written (zeros), not read.  Bound by memory: 32
+// bytes a voxel either way, and the 12 of a fill before it saved (begin at
+// 160x192x224, filled and then warped 73 us, in one pass 59; 384^3, BF16: 463,
+// 429).
+template <typename T, bool ZERO>
 __global__ void __launch_bounds__(kBX* kBY)
-    k_warp(const T* __restrict__ M, const float* __restrict__ u, Geom g,
-           float* __restrict__ Mw, float* __restrict__ dMw) {
+    k_warp(const T* __restrict__ M, float* __restrict__ u, Geom g, float* __restrict__ Mw,
+           float* __restrict__ dMw) {
   int x, y, z, i;
   if (!voxel(g, x, y, z, i)) return;
   const int N = static_cast<int>(g.N);
   const RBuf bm = make_rbuf_n(M, N);
-  const BCell c = make_bcell(g, x, y, z, u[i], u[N + i], u[2 * N + i]);
+  float d0[3] = {0.0f, 0.0f, 0.0f};
+#pragma unroll
+  for (int c = 0; c < 3; ++c) {
+    if constexpr (ZERO)
+      u[c * N + i] = 0.0f;
+    else
+      d0[c] = u[c * N + i];
+  }
+  const BCell c = make_bcell(g, x, y, z, d0[0], d0[1], d0[2]);
   float v[8], d[3];
   bcorners<T>(bm, g, c, v);
   Mw[i] = binterp(c, v, dMw ? d : nullptr);
@@ -246,16 +258,31 @@ unsigned flat_grid(long long n) {
 
 }  // namespace
 
-hipError_t launch_warp(const void* M, lmr_dtype t, const float* u, const Geom& g,
-                       float* Mw, float* dMw, hipStream_t s) {
+namespace {
+
+template <bool ZERO>
+hipError_t warp_t(const void* M, lmr_dtype t, float* u, const Geom& g, float* Mw, float* dMw,
+                  hipStream_t s) {
   dim3 blk(kBX, kBY);
   if (t == LMR_BF16)
-    hipLaunchKernelGGL(k_warp<uint16_t>, vox_grid(g), blk, 0, s,
+    hipLaunchKernelGGL((k_warp<uint16_t, ZERO>), vox_grid(g), blk, 0, s,
                        static_cast<const uint16_t*>(M), u, g, Mw, dMw);
   else
-    hipLaunchKernelGGL(k_warp<float>, vox_grid(g), blk, 0, s,
+    hipLaunchKernelGGL((k_warp<float, ZERO>), vox_grid(g), blk, 0, s,
                        static_cast<const float*>(M), u, g, Mw, dMw);
   return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t launch_warp(const void* M, lmr_dtype t, const float* u, const Geom& g,
+                       float* Mw, float* dMw, hipStream_t s) {
+  return warp_t<false>(M, t, const_cast<float*>(u), g, Mw, dMw, s);
+}
+
+hipError_t launch_warp_identity(const void* M, lmr_dtype t, float* u, const Geom& g,
+                                float* Mw, float* dMw, hipStream_t s) {
+  return warp_t<true>(M, t, u, g, Mw, dMw, s);
 }
 
 // compute units of the current device, cached per device (a tiling

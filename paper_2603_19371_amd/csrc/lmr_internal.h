@@ -387,6 +387,9 @@ int gauss_radius(double sigma);
 
 hipError_t launch_warp(const void* M, lmr_dtype t, const float* u, const Geom& g,
                        float* Mw, float* dMw, hipStream_t s);
+// The same at the identity, which is written to u.
+hipError_t launch_warp_identity(const void* M, lmr_dtype t, float* u, const Geom& g,
+                                float* Mw, float* dMw, hipStream_t s);
 // P1: closed form + compositive integration + warp of M at the candidate.
 // Explicit mode (st == null): reads u_in, g_smooth, r, lambda, writes u_out.
 // In state mode dMw (may be null) receives the derivative of the warped image
