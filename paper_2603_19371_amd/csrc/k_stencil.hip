@@ -190,12 +190,24 @@ bool use_cubes(const Geom& g, const lmr_params& p) {
          (p.stencil == LMR_STENCIL_AUTO && g.N <= kCubeMaxVoxels);
 }
 
-// Small bricks where the volume gives fewer than kWideFrom wide ones.
-constexpr int kWideFrom = 256;
+// Wide bricks where the volume gives more small ones than the backward pass
+// takes the decision on (67x51x57, 952 small or 272 wide bricks, window 7: an
+// attempt 25.8 us small, 29.2 wide; 57x63x85, 1320 or 360: 33.0, 32.1;
+// 80x96x112: 56.9, 50.0).  With radii up to 2 the rows of a small brick's halo
+// are short of a cache line by less, and the larger padding of wide bricks
+// counts: they have to be the more, the more they are padded (window 3, wide
+// bricks and their area over the small ones': 840, 1.00: 45.0 us small, 43.7
+// wide; 456, 1.00: 32.9, 32.0; 720, 1.21: 40.2, 40.3; 450, 1.21: 29.8, 31.3;
+// 624, 1.25: 33.7, 36.1).
+bool use_wide(const Geom& g, int R) {
+  const long long wide = bricks_of(g, kWide, kBrickZ), small = bricks_of(g, kT3, kBrickZ);
+  if (small <= kPassDecisionMaxParts) return false;
+  return R > 2 || small * (wide + 800) >= 4800 * wide;
+}
 
-bool use_wide(const Geom& g) { return bricks_of(g, kWide, kBrickZ) >= kWideFrom; }
-
-int brick_blocks(const Geom& g) { return bricks_of(g, use_wide(g) ? kWide : kT3, kBrickZ); }
+int brick_blocks(const Geom& g, int R) {
+  return bricks_of(g, use_wide(g, R) ? kWide : kT3, kBrickZ);
+}
 
 template <class P, int R, bool DEC = false>
 hipError_t run(const P& pol, const Geom& g, bool cubes, const DevState* st, int need,
@@ -204,13 +216,13 @@ hipError_t run(const P& pol, const Geom& g, bool cubes, const DevState* st, int 
     return hipErrorInvalidValue;  // wider windows keep the decision kernel
   } else {
     if (cubes) {
-      if (!use_wide(g))
-        hipLaunchKernelGGL((k_cube<R, P, DEC>), dim3(brick_blocks(g)), dim3(kCubeThreads), 0, s,
+      if (!use_wide(g, R))
+        hipLaunchKernelGGL((k_cube<R, P, DEC>), dim3(brick_blocks(g, R)), dim3(kCubeThreads), 0, s,
                            pol, g, st, need, pd);
       else if constexpr (DEC)
         return hipErrorInvalidValue;  // wide bricks keep the decision kernel
       else
-        hipLaunchKernelGGL((k_wide<R, P>), dim3(brick_blocks(g)), dim3(kWideThreads), 0, s, pol,
+        hipLaunchKernelGGL((k_wide<R, P>), dim3(brick_blocks(g, R)), dim3(kWideThreads), 0, s, pol,
                            g, st, need, pd);
       return hipGetLastError();
     }
@@ -302,10 +314,13 @@ bool batch_bricks(const Geom& g, const lmr_params& p) {
   return use_cubes(g, p) && g.N <= kBatchBrickMaxVoxels;
 }
 
-bool wide_partials_of(const Geom& g) { return use_wide(g); }
+bool wide_partials_of(const Geom& g, const lmr_params& p) {
+  return use_wide(g, p.window / 2);
+}
 
 int fwd_num_blocks(const Geom& g, const lmr_params& p) {
-  return use_cubes(g, p) ? brick_blocks(g) : march_tiling(g, p.window / 2).tiles();
+  return use_cubes(g, p) ? brick_blocks(g, p.window / 2)
+                         : march_tiling(g, p.window / 2).tiles();
 }
 
 int gauss_radius(double sigma) {
@@ -375,7 +390,7 @@ hipError_t launch_smooth(const float* graw, const Geom& g, const lmr_params& p,
 
 bool bwd_takes_decision(const Geom& g, const lmr_params& p, int nparts) {
   return nparts <= kPassDecisionMaxParts && p.window / 2 <= kPassDecisionMaxRadius &&
-         !(use_cubes(g, p) && use_wide(g));
+         !(use_cubes(g, p) && use_wide(g, p.window / 2));
 }
 
 hipError_t launch_bwd_decide(const void* F, lmr_dtype t, const float* Mw, const float* maps,

@@ -122,7 +122,7 @@ __host__ __device__ inline Tiling make_tiling(int nz, int ny, int nx, int ty,
 // of wide bricks of a volume.
 constexpr long long kBatchBrickMaxVoxels = 1LL << 19;
 bool batch_bricks(const Geom& g, const lmr_params& p);
-bool wide_partials_of(const Geom& g);
+bool wide_partials_of(const Geom& g, const lmr_params& p);
 __host__ __device__ inline int bricks_of(const Geom& g, int side, int depth) {
   return ((g.nx + side - 1) / side) * ((g.ny + side - 1) / side) * ((g.nz + depth - 1) / depth);
 }

@@ -9,8 +9,10 @@ import pytest
 
 pytestmark = pytest.mark.gpu
 
-# wide bricks: 6 + 8; 330 (83 columns: 11 small bricks, 6 wide ones) + 6 + march
-BATCHES = [[(7, 19, 30), (15, 9, 23)], [(41, 75, 83), (7, 19, 30), (40, 64, 420)]]
+# wide bricks: 6 + 8; 330 (83 columns: 11 small bricks, 6 wide ones) + 6 + march;
+# 400 + 6 (partial sums per wide brick with every window; above from window 7 on)
+BATCHES = [[(7, 19, 30), (15, 9, 23)], [(41, 75, 83), (7, 19, 30), (40, 64, 420)],
+           [(100, 64, 64), (7, 19, 30)]]
 
 
 @pytest.fixture(scope="module")
