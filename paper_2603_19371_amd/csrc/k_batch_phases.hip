@@ -281,8 +281,8 @@ hipError_t launch_batch_begin(lmr_dtype t, lmr_accum accum, int box_radius, int 
                               const BatchPair* pairs, int npairs, int n_update_items,
                               int n_tiles, int n_wide, const DecideParams& dp,
                               hipStream_t s) {
-  return phases<true>(PhaseLaunch{pairs, npairs, n_update_items, n_tiles, n_wide, false, s}, t, accum,
-                      box_radius, gauss_radius, dp);
+  return phases<true>(PhaseLaunch{pairs, npairs, n_update_items, n_tiles, n_wide, false, s}, t,
+                      accum, box_radius, gauss_radius, dp);
 }
 
 }  // namespace lmr
