@@ -221,10 +221,12 @@ template <int R, int FORM, class Pol, class LM, class LB>
 __device__ __forceinline__ void stencil_item(const Pol& pol, const BatchPair& P, int local,
                                              typename Pol::Local& loc, LM& lm, LB& lb) {
   int x0, y0, z0;
+  // a brick ends with reads of its LDS, which the next item, a brick or a
+  // marching tile (whose LDS overlays it), writes
+  if constexpr (FORM == 2) __syncthreads();
   if (FORM == 2 && P.bricks) {
     if constexpr (FORM == 2) {
       brick_origin<kT3>(P.g, local, x0, y0, z0);
-      __syncthreads();  // the previous brick's last LDS reads are done
       stencil_cube<R>(pol, P.g, x0, y0, z0, loc, lb);
     }
   } else {
