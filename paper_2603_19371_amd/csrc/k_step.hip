@@ -42,7 +42,7 @@ __global__ void __launch_bounds__(kBX* kBY)
            float* __restrict__ dMw) {
   int x, y, z, i;
   if (!voxel(g, x, y, z, i)) return;
-  const int N = static_cast<int>(g.N);
+  const long long N = g.N;
   const RBuf bm = make_rbuf_n(M, N);
   float d0[3] = {0.0f, 0.0f, 0.0f};
 #pragma unroll
@@ -195,7 +195,7 @@ __global__ void __launch_bounds__(256)
   }
   const int t = blockIdx.x * blockDim.x + threadIdx.x;
   if (t >= ntiles) return;
-  const int N = static_cast<int>(g.N);
+  const long long N = g.N;
   const int bx = t % tx, by = (t / tx) % ty, bz = t / (tx * ty);
   double h[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
   int cnt = 0;

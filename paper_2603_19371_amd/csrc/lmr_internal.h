@@ -68,8 +68,8 @@ struct Geom {
 };
 
 // ---------------------------------------------------------------- helpers
-// Voxel counts are below 2^31 (checked at context creation), so indices
-// within one channel are 32-bit.
+// Voxel counts are below 2^30 (checked at context creation), so indices
+// within one channel are 32-bit; an element of channel c, at c N + i, is not.
 __device__ __forceinline__ float ldf(const float* p, int i) { return p[i]; }
 __device__ __forceinline__ float ldf(const uint16_t* p, int i) {
   return __uint_as_float(static_cast<uint32_t>(p[i]) << 16);

@@ -821,7 +821,7 @@ struct BwdPol {
 
   __device__ static constexpr double wt(int) { return 1.0; }
   __device__ Local begin_block(const DevState*) const {
-    const int N = static_cast<int>(g.N);
+    const long long N = g.N;
     Local l;
 #pragma unroll
     for (int c = 0; c < 4; ++c) l.bmap[c] = make_rbuf_n(maps + c * N, N);
@@ -843,11 +843,11 @@ struct BwdPol {
     }
   }
   __device__ void pre(unsigned i, Pre& q) const {
-    const int N = static_cast<int>(g.N);
+    const long long N = g.N;
     q.f = ldf(F, i);
     q.m = Mw[i];
 #pragma unroll
-    for (int c = 0; c < 3; ++c) q.d[c] = dMw[c * N + i];
+    for (int c = 0; c < 3; ++c) q.d[c] = (dMw + c * N)[i];
   }
   __device__ void emit(const Local& l, unsigned i, const Pre& q, const Acc Bs[4]) const {
     const double fj = q.f, mj = q.m;

@@ -63,7 +63,7 @@ struct TileStep {
     for (int c = 0; c < 3; ++c) q.g[c] = bld<float>(make_rbuf_n(G + c * N, N), i);
   }
   __device__ void apply(const Regs& q, int, int x, int y, int z, float e[3]) const {
-    const double* h = H + 6 * (((z / k) * ty + y / k) * tx + x / k);
+    const double* h = H + 6LL * (((z / k) * ty + y / k) * tx + x / k);
     const double a = h[0] + lam, b = h[1] + lam, c = h[2] + lam;
     const double d = h[3], f = h[4], o = h[5];  // xy, xz, yz
     const double c00 = b * c - o * o, c01 = f * o - d * c, c02 = d * o - b * f;
@@ -102,8 +102,8 @@ struct AdamStep {
     for (int c = 0; c < 3; ++c) {
       const float mn = b1 * q.m[c] + ob1 * q.g[c];
       const float vn = b2 * q.v[c] + ob2 * (q.g[c] * q.g[c]);
-      m[c * N + i] = mn;
-      v[c * N + i] = vn;
+      bst(make_rbuf_n(m + c * N, N), i, mn);
+      bst(make_rbuf_n(v + c * N, N), i, vn);
       const float d = -lr * (mn / c1) / (sqrtf(vn / c2) + aeps);
       e[c] = eps * d;
     }
@@ -130,7 +130,7 @@ struct GivenStep {
 template <typename T>
 __device__ __forceinline__ void update_voxel(const T* __restrict__ M, const Geom& g,
                                              const UpdateArgs& a, int x, int y, int z) {
-  const int N = static_cast<int>(g.N);
+  const long long N = g.N;
   const int i = (z * g.ny + y) * g.nx + x;
   const float g0 = a.G[i], g1 = a.G[N + i], g2 = a.G[2 * N + i];
   const float s = -a.r / fmaf(g2, g2, fmaf(g1, g1, fmaf(g0, g0, a.lam)));
@@ -177,7 +177,7 @@ template <typename T, int V, class S>
 __device__ __forceinline__ void update_voxels(const T* __restrict__ M, const Geom& g,
                                               const UpdateArgs& a, const S& step, int x,
                                               int y, int z0) {
-  const int N = static_cast<int>(g.N);
+  const long long N = g.N;
   int idx[V];
   bool ok[V];
   float e[V][3], n[V][3], mw[V], dm[V][3];
@@ -275,7 +275,8 @@ __device__ __forceinline__ void staged_update_tile(const T* __restrict__ M, cons
   // a block that runs tiles back to back: every thread is done with the
   // previous tile's slots before they are overwritten
   __syncthreads();
-  const int N = static_cast<int>(g.N), plane = g.nx * g.ny;
+  const long long N = g.N;
+  const int plane = g.nx * g.ny;
   const int lx = threadIdx.x % kSX, ly = threadIdx.x / kSX;
   const int x = bx + lx, y = by + ly;
   const bool own = x < g.nx && y < g.ny;
