@@ -172,14 +172,22 @@ __global__ void __launch_bounds__(256) k_conv(ConvArgs a) {
 // V16: the input is staged in 16-byte items (channel stride, offset and
 // count multiples of 8); otherwise in 8-byte quads, those past cin_valid
 // written as zeros without a read (the 2-channel input: 36 -> 25 us).
+// MFMAs keep the order in which they are written; anything else may move.  A
+// 16x16x16 and a 16x16x32 product in a row on one accumulator, either way
+// round, need five wait states that the compiler does not insert: the second
+// reads the accumulator as it was before the first (measured with integer
+// operands: half of all sums wrong with up to four wait states, none with
+// five or with any other MFMA in between).
+__device__ __forceinline__ void keep_product_order() {
+  __builtin_amdgcn_sched_barrier(0x7F6);  // all kinds but MFMA
+}
+
 constexpr int kCT = 16;            // tile edge along x
 constexpr int kCH = kCT + 2;       // halo tile edge
 constexpr int kPitch = 20;         // LDS row pitch, uint16 elements (40 bytes)
 template <int NT, int RW, int WZ, bool V16>
 __global__ void __launch_bounds__(256) k_conv_tile(ConvArgs a) {
-  // MFMAs on the same accumulator lie at least four apart: with fewer, the
-  // K = 16 product after a K = 32 product gave wrong sums
-  static_assert(NT * RW >= 4, "independent accumulators between dependent products");
+  static_assert(NT * RW >= 2, "another accumulator's product between dependent ones");
   constexpr int TY = RW * (4 / WZ);                        // rows of the tile
   constexpr int HY = TY + 2, P = (WZ + 2) * HY * kCH;      // halo rows, positions
   // staged items per thread: 16-byte halves of a voxel's 16 channels, or whole
@@ -327,16 +335,20 @@ __global__ void __launch_bounds__(256) k_conv_tile(ConvArgs a) {
         for (int r = 0; r < RW; ++r) {
           const b8 xv = cat_bf16(X[r + ta / 3][ta % 3], X[r + tb / 3][tb % 3]);
 #pragma unroll
-          for (int n = 0; n < NT; ++n)
+          for (int n = 0; n < NT; ++n) {
             acc[n][r] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wt[n], xv, acc[n][r], 0, 0, 0);
+            keep_product_order();
+          }
         }
       }
 #pragma unroll
       for (int r = 0; r < RW; ++r)
 #pragma unroll
-        for (int n = 0; n < NT; ++n)
+        for (int n = 0; n < NT; ++n) {
           acc[n][r] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(w[n][8], X[r + 2][2],
                                                                 acc[n][r], 0, 0, 0);
+          keep_product_order();
+        }
     }
   }
   // D[4 kq + j][m]: output channel co0 + 16 n + 4 kq + j of voxel x0 + m in
