@@ -258,6 +258,10 @@ lmr_status lmr_batch_create(lmr_batch** out, int npairs, const int* shapes, lmr_
 lmr_status lmr_batch_begin(lmr_batch* b, const void* const* fixed,
                            const void* const* moving, const double* lambda0) {
   if (!b || !fixed || !moving) return LMR_EINVAL;
+  // nothing changes for a call that is refused (the table of the pairs is
+  // uploaded again by later calls, and its images are the last begin's)
+  for (int i = 0; i < b->npairs; ++i)
+    if (!fixed[i] || !moving[i] || (lambda0 && !(lambda0[i] > 0.0))) return LMR_EINVAL;
   // the pairs on bricks begin together: one after another their launches are
   // smaller than the GPU (begin and one attempt, 32 pairs of 48^3: 1350 us one
   // after another, 550 together; 4 pairs: 233, 157; one pair: 120, 121).  A
@@ -268,8 +272,6 @@ lmr_status lmr_batch_begin(lmr_batch* b, const void* const* fixed,
     if (!P.bricks) {
       lmr_status st = lmr_begin(b->ctx[i], fixed[i], moving[i], nullptr, l0);
       if (st != LMR_OK) return st;
-    } else if (!fixed[i] || !moving[i] || !(l0 > 0.0)) {
-      return LMR_EINVAL;
     }
     P.F = fixed[i];
     P.M = moving[i];
