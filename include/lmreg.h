@@ -430,8 +430,9 @@ lmr_status lmr_batch_set_config(lmr_batch* b, int target_tiles, int min_cz,
 lmr_status lmr_batch_get_config(lmr_batch* b, int cfg[3]);
 /* Autotuner: times iters_per_trial iterations for every candidate
  * configuration on the given images and keeps the fastest; with cache_path
- * the choice is read from / appended to that text file, keyed by the GPU,
- * image type, window, sigma and the pair shapes.  best_ms (may be NULL)
+ * the choice is read from / appended to that text file, keyed by the GPU, the
+ * version of the kernels, image type, accumulator, window, sigma, stencil form,
+ * composition and the pair shapes.  best_ms (may be NULL)
  * receives the time of one iteration.  The trials overwrite the pair states:
  * call lmr_batch_begin afterwards. */
 lmr_status lmr_batch_tune(lmr_batch* b, const void* const* fixed,

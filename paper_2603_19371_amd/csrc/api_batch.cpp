@@ -112,10 +112,12 @@ lmr_status enqueue_steps(lmr_batch* b, int n) {
   return LMR_OK;
 }
 
+// What the time of an attempt depends on.  v: raised when the kernels or the
+// work items change, so that choices timed on others are not taken.
 std::string cache_key(const lmr_batch* b) {
   char buf[128];
-  snprintf(buf, sizeof buf, "gfx950|v2|img%d|acc%d|w%d|s%.3f|", (int)b->img, b->p.accum,
-           b->p.window, b->p.grad_sigma);
+  snprintf(buf, sizeof buf, "gfx950|v3|img%d|acc%d|w%d|s%.3f|st%d|c%d|", (int)b->img,
+           b->p.accum, b->p.window, b->p.grad_sigma, b->p.stencil, b->p.compositive);
   std::string k = buf;
   for (const auto& P : b->host) {
     snprintf(buf, sizeof buf, "%dx%dx%d,", P.g.nz, P.g.ny, P.g.nx);
