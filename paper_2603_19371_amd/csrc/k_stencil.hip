@@ -13,13 +13,13 @@ namespace lmr {
 namespace {
 
 // The tiling (and with it the chunks, and the partial sums of the forward
-// pass) is in 32 x kTY tiles, as in the batched form; a block runs two of
-// them, one above the other, on two waves per SIMD, and two blocks share a CU
-// (at most 128 VGPRs a thread).  Launches with fewer blocks than CUs (small
-// volumes asked to march) have none to share: there a block runs one tile
-// (attempt at 33x40x45: 28 us, 31 with two tiles; at 64x64x64: 36, 39).
+// pass) is in 32 x kTY tiles, as in the batched form; a block runs one, or two
+// of them, one above the other, on two waves per SIMD, and two such blocks
+// share a CU (at most 128 VGPRs a thread).
 constexpr int kTY = 8, kMarchTY = 2 * kTY;
-__host__ __device__ inline int march_rows(const Tiling& t) { return (t.tiles_y + 1) / 2; }
+__host__ __device__ inline int march_rows(const Tiling& t) {
+  return t.pairs ? (t.tiles_y + 1) / 2 : t.tiles_y;
+}
 
 // The decision of the attempt inside a pass of NT threads (pass_decision.h):
 // every block reduces the partials and decides on the pair state st; block 0
@@ -91,7 +91,7 @@ __global__ void __launch_bounds__(kTX* TY)
   if (!pass_state<kTX * TY, DEC>(st, need, pd, rs)) return;
   __shared__ StencilLds<R, TY, P> sm[TY == kMarchTY ? 2 : 1];
   const int b = xcd_remap(blockIdx.x, gridDim.x);
-  const int rows = TY == kMarchTY ? march_rows(t) : t.tiles_y;
+  const int rows = march_rows(t);
   const int tx = b % t.tiles_x, row = (b / t.tiles_x) % rows, chunk = b / (t.tiles_x * rows);
   const int z0 = chunk * t.cz;
   typename P::Local loc = pol.begin_block(rs);
@@ -107,7 +107,7 @@ __global__ void __launch_bounds__(kTX* TY)
   if constexpr (TY == kMarchTY && P::kSum) {
     double* lower = pol.partials + (chunk * t.tiles_y + 2 * row) * t.tiles_x + tx;
     half_sums_to<kTX * TY>(loc.sum, lower,
-                                2 * row + 1 < t.tiles_y ? lower + t.tiles_x : nullptr);
+                           2 * row + 1 < t.tiles_y ? lower + t.tiles_x : nullptr);
   }
 }
 
@@ -145,18 +145,18 @@ __global__ void __launch_bounds__(kWideThreads)
 
 }  // namespace
 
-// Chunk length of the march.  A launch runs its blocks in rounds of 2 x CUs
-// co-resident ones, and each block of a round marches its chunk plus the 2R
-// halo planes, so a launch lasts about ceil(blocks / (2 CUs)) x (cz + 2R) plane
-// steps.  Among the chunk lengths not below make_tiling's floor, take the one
-// that minimises this (the longer chunk on a tie).  It does not depend on the
-// kernel: a box sum's rounding depends on where its chunk starts, and the
-// batched form (blocks of one tile, four per CU) reproduces a pair's run by
-// using the same tiling for all passes.
-Tiling march_tiling(const Geom& g, int R) {
-  Tiling t = make_tiling(g.nz, g.ny, g.nx, kTY);
+namespace {
+
+// Chunk length of the march for tiling t.  A launch runs its blocks in rounds
+// of as many as are co-resident (two per CU that run two tiles, four that run
+// one), and each block of a round marches its chunk plus the 2R halo planes,
+// so a launch lasts about rounds x (cz + 2R) plane steps.  Among the chunk
+// lengths not below make_tiling's floor, take the one that minimises this (the
+// longer chunk on a tie).  Returns the planes that the fullest CU marches,
+// counted in tiles.
+long long set_chunks(Tiling& t, const Geom& g, int R) {
   const long long cols = (long long)t.tiles_x * march_rows(t);
-  const long long cap = 2LL * device_cus();
+  const long long cus = device_cus(), cap = (t.pairs ? 2 : 4) * cus;
   const int floor_cz =
       std::min(march_floor_cz((long long)t.tiles_x * t.tiles_y, g.nz), g.nz);
   long long best = -1;
@@ -172,7 +172,27 @@ Tiling march_tiling(const Geom& g, int R) {
       t.nchunks = chunks;
     }
   }
-  return t;
+  return (t.pairs ? 2 : 1) * ((cols * t.nchunks + cus - 1) / cus) * (t.cz + 2 * R);
+}
+
+}  // namespace
+
+// Two tiles per block read a plane's halo rows once for both and have half the
+// barriers, so a tile's plane costs them about nine tenths of what it costs a
+// block of one; but an odd row of tiles leaves half of a block idle, and the
+// blocks are the coarser load for the CUs.  So they are taken where the fullest
+// CU has at most 10/9 of the planes then (attempt, window 7: 160x72x160, 56
+// planes either way: one tile 94.9 us, two 91.3; 300x24x300, 60 and 72: 90.2,
+// 95.6; 512x8x512, 56 and 88: 84.8, 104.1; 130x70x130, 45 and 60: 81.5, 84.4;
+// window 5, 256x40x256, 60 and 68: 93.8, 96.0).  The tiling does not depend on
+// the kernel: a box sum's rounding depends on where its chunk starts, and the
+// batched form (blocks of one tile) reproduces a pair's run by using the same
+// tiling for all passes.
+Tiling march_tiling(const Geom& g, int R) {
+  Tiling one = make_tiling(g.nz, g.ny, g.nx, kTY), two = one;
+  two.pairs = 1;
+  const long long c1 = set_chunks(one, g, R), c2 = set_chunks(two, g, R);
+  return 9 * c2 <= 10 * c1 ? two : one;
 }
 
 namespace {
@@ -227,13 +247,13 @@ hipError_t run(const P& pol, const Geom& g, bool cubes, const DevState* st, int 
       return hipGetLastError();
     }
     const Tiling t = march_tiling(g, R);
-    const int blocks = t.tiles_x * march_rows(t) * t.nchunks;
-    if (blocks < device_cus())
-      hipLaunchKernelGGL((k_stencil<R, kTY, P, DEC>), dim3(t.tiles()), dim3(kTX * kTY), 0, s,
-                         pol, g, t, st, need, pd);
+    const dim3 grid(t.tiles_x * march_rows(t) * t.nchunks);
+    if (t.pairs)
+      hipLaunchKernelGGL((k_stencil<R, kMarchTY, P, DEC>), grid, dim3(kTX * kMarchTY), 0, s, pol,
+                         g, t, st, need, pd);
     else
-      hipLaunchKernelGGL((k_stencil<R, kMarchTY, P, DEC>), dim3(blocks), dim3(kTX * kMarchTY),
-                         0, s, pol, g, t, st, need, pd);
+      hipLaunchKernelGGL((k_stencil<R, kTY, P, DEC>), grid, dim3(kTX * kTY), 0, s, pol, g, t, st,
+                         need, pd);
     return hipGetLastError();
   }
 }

@@ -78,6 +78,7 @@ __device__ __forceinline__ double to_f64(const F32C& v) {
 
 struct Tiling {
   int ty, tiles_x, tiles_y, nchunks, cz;
+  int pairs;  // 1: a stand-alone context's blocks run two tiles (march_tiling)
   __host__ __device__ int tiles() const { return tiles_x * tiles_y * nchunks; }
 };
 
@@ -100,6 +101,7 @@ __host__ __device__ inline Tiling make_tiling(int nz, int ny, int nx, int ty,
                                               int target_tiles = 2048, int min_cz = 16) {
   Tiling t;
   t.ty = ty;
+  t.pairs = 0;
   t.tiles_x = (nx + kTX - 1) / kTX;
   t.tiles_y = (ny + ty - 1) / ty;
   const int cols = t.tiles_x * t.tiles_y;
@@ -281,16 +283,21 @@ __device__ __forceinline__ void tile_step(March<R, TY, P>& m, int zi, typename P
   // w 7: 90.5 -> 85.5 us).  The compensated sums have no registers to hold
   // them (121x145x119, w 9: 346 -> 351 us).
   constexpr bool kEarly = !std::is_same<typename P::Acc, F32C>::value;
+  // and their windows from radius 3 on are fenced (stencil_march), which keeps
+  // the backward pass at 117 registers and four waves per SIMD (left alone 164
+  // and three; attempt at 160x72x160, window 7: 100.3 -> 94.9 us); compensated
+  // sums are a percent faster without
+  constexpr bool kFenced = P::kBox && kEarly && R >= 3;
   m.commit(sm);
   const unsigned io = m.out_index(zi - R);
   typename P::Pre q;
   if (kEarly) m.operands(io, q);
   m.fetch(loc, zi + 1);
   __syncthreads();
-  m.template ypass<0>(sm);
+  m.template ypass<kFenced ? 4 : 0>(sm);
   __syncthreads();
   typename P::Acc o[P::NCH];
-  m.template xpass<S, 0>(sm, o);
+  m.template xpass<S, kFenced ? 1 : 0>(sm, o);
   if (!kEarly) m.operands(io, q);
   m.pol.emit(loc, io, q, o);
 }
