@@ -392,8 +392,10 @@ __device__ __forceinline__ void stencil_march(const P& pol, const Geom& g, int x
 // 128-byte lines), and a 22-voxel row serves twice the outputs (15 us; the
 // backward pass 23 -> 19, the Gaussian 13.6 -> 11).
 //
-// Every output is the sum of its terms in ascending z, then y, then x, so it
-// does not depend on the brick that computes it.
+// Every output is the sum of its terms in ascending y, then x, of z sums: those
+// of its column in ascending z or, for compensated sums from radius 2 on,
+// running sums that start where kBrickZ divides z.  So it does not depend on the brick that
+// computes it.
 constexpr int kT3 = 8, kWide = 16, kBrickZ = 4;
 constexpr int kCubeThreads = 256, kWideThreads = 512;
 
@@ -458,6 +460,33 @@ __device__ __forceinline__ void brick_zsum(const P& pol,
   using A = typename P::Acc;
   constexpr int NC = P::NCH, L = SIDE + 2 * R;
   const int yy = col / L, xx = col - yy * L;
+  if constexpr (std::is_same<A, F32C>::value && R >= 2) {
+    // the entering position's terms added, the leaving one's (formed again)
+    // subtracted: an addition of compensated sums is eight operations, and from
+    // radius 2 on this takes fewer of them than every sum by itself (19 instead
+    // of 28 a channel at radius 3: attempts 3 to 6 % faster; radius 2, 1 to 3 %;
+    // with FP64 sums nothing)
+    A a[NC];
+#pragma unroll
+    for (int c = 0; c < NC; ++c) a[c] = A();
+#pragma unroll
+    for (int k = 0; k <= 2 * R; ++k) pol.accum(a, r[k], k);
+#pragma unroll
+    for (int oz = 0; oz < kBrickZ; ++oz) {
+#pragma unroll
+      for (int c = 0; c < NC; ++c) sm.z[c][oz][yy][xx] = a[c];
+      if (oz + 1 < kBrickZ) {
+        A enter[NC], leave[NC];
+#pragma unroll
+        for (int c = 0; c < NC; ++c) enter[c] = leave[c] = A();
+        pol.accum(enter, r[oz + 2 * R + 1], 0);
+        pol.accum(leave, r[oz], 0);
+#pragma unroll
+        for (int c = 0; c < NC; ++c) a[c] += enter[c] - leave[c];
+      }
+    }
+    return;
+  }
 #pragma unroll
   for (int oz = 0; oz < kBrickZ; ++oz) {
     A a[NC];
