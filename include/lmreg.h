@@ -108,9 +108,10 @@ typedef enum {
 
 /* How the three stencil passes (LNCC forward and backward, Gaussian) tile
  * the volume.  LMR_STENCIL_MARCH: 32 x 8 columns marching through chunks of
- * z planes (large volumes).  LMR_STENCIL_CUBE: bricks of outputs 4 planes
- * deep, 16 x 16 columns or, in the smallest volumes, 8 x 8, each reduced along
- * z, y and x in three steps (small volumes, where a march is latency).
+ * z planes (large volumes).  LMR_STENCIL_CUBE: bricks of outputs, 8 x 8
+ * columns of 4 planes in the smallest volumes, else whichever of these, 8 x 8 x
+ * 8 and 16 x 16 x 4 suits the volume and the stencil, each reduced along z, y
+ * and x in three steps (small volumes, where a march is latency).
  * LMR_STENCIL_AUTO (default): bricks up to 2^20 voxels, else the march.  The
  * two forms sum the same terms in different orders (FP64 or compensated sums
  * either way). */
@@ -317,7 +318,7 @@ typedef enum {
   LMR_K_FWD = 1,     /* LNCC forward (box sums, cc, adjoint maps, partials) */
   LMR_K_DECIDE = 2,  /* FP64 loss reduction and decision (LNCC levels with at most
                         1024 partials and a window of at most 7, marching or on
-                        8 x 8 bricks, take it inside the backward pass, and
+                        8 x 8 x 4 bricks, take it inside the backward pass, and
                         mutual information where it is formed: this interval is
                         then its event alone) */
   LMR_K_BWD = 3,     /* LNCC backward and warp backward */
@@ -422,9 +423,9 @@ lmr_ctx* lmr_batch_pair(lmr_batch* b, int i);
  * no persistent kernel, each phase of an attempt is one launch over the work
  * items of all pairs, the same items and results, 5 to 8 launches per
  * attempt, and no co-residency requirement; 0 = one persistent launch per
- * attempt with as many blocks as fit; n > 0 = n blocks per CU).  Pairs that a
- * stand-alone context runs on 8 x 8 bricks run on bricks here (either mode);
- * the others march. */
+ * attempt with as many blocks as fit; n > 0 = n blocks per CU).  Pairs of at
+ * most 2^19 voxels that a stand-alone context runs on bricks run on bricks here
+ * (either mode); the others march. */
 lmr_status lmr_batch_set_config(lmr_batch* b, int target_tiles, int min_cz,
                                 int blocks_per_cu);
 lmr_status lmr_batch_get_config(lmr_batch* b, int cfg[3]);

@@ -244,7 +244,9 @@ lmr_status lmr_create(lmr_ctx** out, int nz, int ny, int nx, lmr_dtype img,
                        p->adam_beta1, p->adam_beta2,     p->similarity,
                        p->mi_bins};
   c->stream = stream;
-  c->nparts = fwd_num_blocks(c->g, *p);
+  c->nparts = p->similarity == LMR_SIM_MSE || p->similarity == LMR_SIM_DEMONS
+                  ? mse_num_blocks(N)
+                  : fwd_num_blocks(c->g, *p);
 
   const size_t f3 = align256(sizeof(float) * 3 * N);
   const size_t sizes[] = {f3,

@@ -231,7 +231,8 @@ lmr_status lmr_batch_create(lmr_batch** out, int npairs, const int* shapes, lmr_
     memset(&P, 0, sizeof P);
     P.g = c->g;
     P.bricks = bricks[i] ? 1 : 0;
-    P.nwide = bricks[i] && wide_partials_of(gi, *p) ? bricks_of(gi, kWide, kBrickZ) : 0;
+    P.form = bricks[i] ? box_brick(gi, rb) : Brick::kSmall;
+    P.nform = brick_blocks(gi, P.form);
     P.U0 = c->U[0];
     P.U1 = c->U[1];
     P.G = c->G;

@@ -163,16 +163,26 @@ template <int R, class P, int BR>
 using SmallLds = std::conditional_t<BR != 0, BrickLds<R, P, kT3>, char>;
 
 // The decision of pair P, or its begin, by one block.  The partials are in
-// the order of a stand-alone context's: a wide brick's is the sum of its
-// small bricks', row by row (those outside the volume count as 0).
+// the order of a stand-alone context's: a deep or wide brick's is the sum of its
+// small bricks', plane by plane or row by row (those outside the volume count
+// as 0).
 __device__ __forceinline__ void decide_pair(const BatchPair& P, const DecideParams& dp,
                                             int mode) {
-  if (P.nwide == 0) {
+  if (P.form == Brick::kSmall) {
     decide_block<kNT>(P.st, [&](int k) { return P.partials[k]; }, P.ntiles, P.g.N, dp, mode,
                       -1, P.lambda0, nullptr);
     return;
   }
   const int cx = (P.g.nx + kT3 - 1) / kT3, cy = (P.g.ny + kT3 - 1) / kT3;
+  if (P.form == Brick::kDeep) {
+    const int plane = cx * cy;
+    auto part = [&](int k) {
+      const int b = 2 * (k / plane) * plane + k % plane;
+      return P.partials[b] + (b + plane < P.ntiles ? P.partials[b + plane] : 0.0);
+    };
+    decide_block<kNT>(P.st, part, P.nform, P.g.N, dp, mode, -1, P.lambda0, nullptr);
+    return;
+  }
   const int wx = (P.g.nx + kWide - 1) / kWide, wy = (P.g.ny + kWide - 1) / kWide;
   auto part = [&](int k) {
     const int bx = 2 * (k % wx), by = 2 * ((k / wx) % wy), bz = k / (wx * wy);
@@ -182,7 +192,7 @@ __device__ __forceinline__ void decide_pair(const BatchPair& P, const DecidePara
     const double q2 = y1 ? row[cx] : 0.0, q3 = x1 && y1 ? row[cx + 1] : 0.0;
     return ((q0 + q1) + q2) + q3;
   };
-  decide_block<kNT>(P.st, part, P.nwide, P.g.N, dp, mode, -1, P.lambda0, nullptr);
+  decide_block<kNT>(P.st, part, P.nform, P.g.N, dp, mode, -1, P.lambda0, nullptr);
 }
 
 // One work item of each phase, shared by the persistent kernel (a grid-stride

@@ -91,7 +91,7 @@ __global__ void __launch_bounds__(kTX* TY)
   if (!pass_state<kTX * TY, DEC>(st, need, pd, rs)) return;
   __shared__ StencilLds<R, TY, P> sm[TY == kMarchTY ? 2 : 1];
   const int b = xcd_remap(blockIdx.x, gridDim.x);
-  const int rows = march_rows(t);
+  const int rows = TY == kMarchTY ? (t.tiles_y + 1) / 2 : t.tiles_y;  // march_rows(t)
   const int tx = b % t.tiles_x, row = (b / t.tiles_x) % rows, chunk = b / (t.tiles_x * rows);
   const int z0 = chunk * t.cz;
   typename P::Local loc = pol.begin_block(rs);
@@ -111,20 +111,48 @@ __global__ void __launch_bounds__(kTX* TY)
   }
 }
 
-// The same stencil on small bricks (stencil.h).
-template <int R, class P, bool DEC>
+// The partial of a deep brick: the sums over its halves, each in the order of
+// block_sum_to over a small brick's block, added.
+__device__ __forceinline__ void deep_sum_to(double lower, double upper, double* out) {
+  constexpr int kWaves = kCubeThreads / 64;
+  __shared__ double red[2][kWaves];
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) {
+    lower += __shfl_xor(lower, off, 64);
+    upper += __shfl_xor(upper, off, 64);
+  }
+  if ((threadIdx.x & 63) == 0) {
+    red[0][threadIdx.x >> 6] = lower;
+    red[1][threadIdx.x >> 6] = upper;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    double s[2] = {0.0, 0.0};
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int k = 0; k < kWaves; ++k) s[h] += red[h][k];
+    *out = s[0] + s[1];
+  }
+}
+
+// The same stencil on small or deep bricks (stencil.h).
+template <int R, class P, int DEPTH, bool DEC>
 __global__ void __launch_bounds__(kCubeThreads)
     __attribute__((amdgpu_waves_per_eu(DEC ? 4 : 1)))
     k_cube(const P pol, Geom g, const DevState* st, int need, PassDecision pd) {
   const DevState* rs;
   if (!pass_state<kCubeThreads, DEC>(st, need, pd, rs)) return;
-  __shared__ BrickLds<R, P, kT3> sm;
+  __shared__ BrickLds<R, P, kT3, DEPTH> sm;
   const int b = xcd_remap(blockIdx.x, gridDim.x);
   int x0, y0, z0;
-  brick_origin<kT3>(g, b, x0, y0, z0);
+  brick_origin<kT3, DEPTH>(g, b, x0, y0, z0);
   typename P::Local loc = pol.begin_block(rs);
-  stencil_cube<R>(pol, g, x0, y0, z0, loc, sm);
-  pol.end_tile(loc, b);
+  const double others = stencil_cube<R>(pol, g, x0, y0, z0, loc, sm);
+  if constexpr (P::kSum && DEPTH > kBrickZ)
+    deep_sum_to(loc.sum, others, pol.partials + b);
+  else
+    pol.end_tile(loc, b);
 }
 
 // And on wide bricks.
@@ -210,24 +238,30 @@ bool use_cubes(const Geom& g, const lmr_params& p) {
          (p.stencil == LMR_STENCIL_AUTO && g.N <= kCubeMaxVoxels);
 }
 
-// Wide bricks where the volume gives more small ones than the backward pass
-// takes the decision on (67x51x57, 952 small or 272 wide bricks, window 7: an
-// attempt 25.8 us small, 29.2 wide; 57x63x85, 1320 or 360: 33.0, 32.1;
-// 80x96x112: 56.9, 50.0).  With radii up to 2 the rows of a small brick's halo
-// are short of a cache line by less, and the larger padding of wide bricks
-// counts: they have to be the more, the more they are padded (window 3, wide
-// bricks and their area over the small ones': 840, 1.00: 45.0 us small, 43.7
-// wide; 456, 1.00: 32.9, 32.0; 720, 1.21: 40.2, 40.3; 450, 1.21: 29.8, 31.3;
-// 624, 1.25: 33.7, 36.1).
-bool use_wide(const Geom& g, int R) {
-  const long long wide = bricks_of(g, kWide, kBrickZ), small = bricks_of(g, kT3, kBrickZ);
-  if (small <= kPassDecisionMaxParts) return false;
-  return R > 2 || small * (wide + 800) >= 4800 * wide;
+// The bricks of a pass.  Blocks are spread over the CUs, so a pass takes about
+// as long as its fullest CU: ceil(blocks / CUs) deep or wide bricks; small ones
+// are short enough that their number over the CUs describes them.  Times of a
+// deep and a wide brick in hundredths of a small one's, each with a constant,
+// from attempts of 28 shapes of 2.2e5 to 1e6 voxels (cubes to needles and
+// slabs) in every form of the box passes and of the Gaussian.  Up to
+// kPassDecisionMaxParts small bricks there is no other: the backward pass takes
+// the decision on those.
+struct BrickTimes {
+  int deep, deep0, wide, wide0;
+};
+Brick fastest_brick(const Geom& g, const BrickTimes& t) {
+  const long long small = bricks_of(g, kT3, kBrickZ), deep = bricks_of(g, kT3, kDeepZ),
+                  wide = bricks_of(g, kWide, kBrickZ), cus = device_cus();
+  if (small <= kPassDecisionMaxParts) return Brick::kSmall;
+  const long long s = 100 * small, d = cus * (t.deep * ((deep + cus - 1) / cus) + t.deep0),
+                  w = cus * (t.wide * ((wide + cus - 1) / cus) + t.wide0);
+  return w <= s && w <= d ? Brick::kWide : d < s ? Brick::kDeep : Brick::kSmall;
 }
 
-int brick_blocks(const Geom& g, int R) {
-  return bricks_of(g, use_wide(g, R) ? kWide : kT3, kBrickZ);
-}
+// The Gaussian (attempt, window 7, box passes wide: 80x96x112, small 52.6 us,
+// deep 51.4, wide 50.8; 300x5x400 56.7, 56.3, 57.3; 2000x20x20 76.9, 74.9,
+// 77.2).
+Brick gauss_brick(const Geom& g) { return fastest_brick(g, {125, 120, 200, 26}); }
 
 template <class P, int R, bool DEC = false>
 hipError_t run(const P& pol, const Geom& g, bool cubes, const DevState* st, int need,
@@ -236,14 +270,20 @@ hipError_t run(const P& pol, const Geom& g, bool cubes, const DevState* st, int 
     return hipErrorInvalidValue;  // wider windows keep the decision kernel
   } else {
     if (cubes) {
-      if (!use_wide(g, R))
-        hipLaunchKernelGGL((k_cube<R, P, DEC>), dim3(brick_blocks(g, R)), dim3(kCubeThreads), 0, s,
-                           pol, g, st, need, pd);
+      const Brick form = P::kBox ? box_brick(g, R) : gauss_brick(g);
+      const dim3 grid(brick_blocks(g, form));
+      if (form == Brick::kSmall)
+        hipLaunchKernelGGL((k_cube<R, P, kBrickZ, DEC>), grid, dim3(kCubeThreads), 0, s, pol, g,
+                           st, need, pd);
       else if constexpr (DEC)
-        return hipErrorInvalidValue;  // wide bricks keep the decision kernel
+        return hipErrorInvalidValue;  // the others keep the decision kernel
+      else if (form == Brick::kWide)
+        hipLaunchKernelGGL((k_wide<R, P>), grid, dim3(kWideThreads), 0, s, pol, g, st, need, pd);
+      else if constexpr (!P::kBox || R <= 2)
+        hipLaunchKernelGGL((k_cube<R, P, kDeepZ, false>), grid, dim3(kCubeThreads), 0, s, pol, g,
+                           st, need, pd);
       else
-        hipLaunchKernelGGL((k_wide<R, P>), dim3(brick_blocks(g, R)), dim3(kWideThreads), 0, s, pol,
-                           g, st, need, pd);
+        return hipErrorInvalidValue;
       return hipGetLastError();
     }
     const Tiling t = march_tiling(g, R);
@@ -334,12 +374,25 @@ bool batch_bricks(const Geom& g, const lmr_params& p) {
   return use_cubes(g, p) && g.N <= kBatchBrickMaxVoxels;
 }
 
-bool wide_partials_of(const Geom& g, const lmr_params& p) {
-  return use_wide(g, p.window / 2);
+int brick_blocks(const Geom& g, Brick form) {
+  return bricks_of(g, form == Brick::kWide ? kWide : kT3,
+                   form == Brick::kDeep ? kDeepZ : kBrickZ);
+}
+
+// Attempts, Gaussian wide, small / deep / wide: window 3, 80x96x112 46.8, 45.4,
+// 46.4 us, 2000x20x20 60.2, 57.6, 65.7, 80x49x57 24.4, 25.3, 26.7; window 5,
+// 80x96x112 50.1, 48.7, 48.3, 65x89x77 37.2, 38.9, 36.2, 300x5x400 46.8, 46.7,
+// 51.7; window 7, 80x96x112 55.5, 55.9, 50.8, 102x56x81 41.5, 42.1, 42.3,
+// 300x5x400 51.6, 53.7, 57.3; window 9 as 7.  Deep ones are not built for radii
+// above 2.
+Brick box_brick(const Geom& g, int R) {
+  constexpr BrickTimes kTimes[3] = {
+      {143, 160, 283, 175}, {170, 65, 274, 89}, {1000, 0, 240, 63}};
+  return fastest_brick(g, kTimes[std::min(R, 3) - 1]);
 }
 
 int fwd_num_blocks(const Geom& g, const lmr_params& p) {
-  return use_cubes(g, p) ? brick_blocks(g, p.window / 2)
+  return use_cubes(g, p) ? brick_blocks(g, box_brick(g, p.window / 2))
                          : march_tiling(g, p.window / 2).tiles();
 }
 
@@ -410,7 +463,7 @@ hipError_t launch_smooth(const float* graw, const Geom& g, const lmr_params& p,
 
 bool bwd_takes_decision(const Geom& g, const lmr_params& p, int nparts) {
   return nparts <= kPassDecisionMaxParts && p.window / 2 <= kPassDecisionMaxRadius &&
-         !(use_cubes(g, p) && use_wide(g, p.window / 2));
+         !(use_cubes(g, p) && box_brick(g, p.window / 2) != Brick::kSmall);
 }
 
 hipError_t launch_bwd_decide(const void* F, lmr_dtype t, const float* Mw, const float* maps,

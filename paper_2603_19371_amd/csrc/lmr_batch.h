@@ -23,7 +23,8 @@ struct BatchPair {
   Tiling t;          // stencil tiling of this pair (marching form)
   int bricks;        // 1: the stencil work items are bricks
   int ntiles;        // cc partials of this pair: its marching tiles or small bricks
-  int nwide;         // > 0: its loss sums them by wide bricks, of which there are so many
+  Brick form;        // the bricks by which its loss sums the small ones' partials,
+  int nform;         // and their number
   int utile0;        // first update work item of this pair
   int ucz;           // planes per update work item of this pair
   int tile0;         // first stencil work item of this pair (marching tiles, small bricks)

@@ -429,6 +429,7 @@ hipError_t launch_mi_bwd(const void* F, lmr_dtype t, const float* Mw, const floa
 // errors); a frozen pair is skipped.  mse_bwd: g = (Mw - F) dMw / r with r
 // the state's residual (only after an acceptance) or sqrt(*loss) without a
 // state; dMw may alias graw.
+int mse_num_blocks(long long N);  // of the forward reduction
 hipError_t launch_mse_fwd(const void* F, lmr_dtype t, const float* Mw, const Geom& g,
                           int nparts, double* partials, float* sq_map, const DevState* st,
                           hipStream_t s);

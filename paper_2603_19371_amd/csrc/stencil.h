@@ -119,15 +119,16 @@ __host__ __device__ inline Tiling make_tiling(int nz, int ny, int nx, int ty,
 // Whether a pair of a batch runs on bricks: where a stand-alone context does,
 // up to kBatchBrickMaxVoxels (larger pairs fill the GPU together and march as
 // fast: 16 of 64x64x72 on bricks 303 us per attempt, marching 360; 4 of
-// 96x96x96 198 and 180); whether that context's bricks are wide ones, so
-// that its partial sums of cc are (k_stencil.hip); and the number of small and
-// of wide bricks of a volume.
+// 96x96x96 198 and 180); the bricks of that context's box passes, and so of its
+// partial sums of cc (k_stencil.hip); and the number of bricks of a volume.
 constexpr long long kBatchBrickMaxVoxels = 1LL << 19;
 bool batch_bricks(const Geom& g, const lmr_params& p);
-bool wide_partials_of(const Geom& g, const lmr_params& p);
+enum class Brick : int { kSmall, kDeep, kWide };
+Brick box_brick(const Geom& g, int R);
 __host__ __device__ inline int bricks_of(const Geom& g, int side, int depth) {
   return ((g.nx + side - 1) / side) * ((g.ny + side - 1) / side) * ((g.nz + depth - 1) / depth);
 }
+int brick_blocks(const Geom& g, Brick form);
 
 // The march's tiling of a volume for stencil radius R on the current device
 // (k_stencil.hip): every pass of a per-pair attempt, and by default each pair
@@ -384,8 +385,9 @@ __device__ __forceinline__ void stencil_march(const P& pol, const Geom& g, int x
 // along z; then the block reduces along y and along x in LDS and emits.  Three
 // steps instead of a march.
 //
-// Two sizes.  Small bricks, kT3 x kT3 columns, where few blocks are the
-// limit (40x48x56: 420 of them).  Wide bricks, kWide x kWide columns, for
+// Two sizes, and a third for the Gaussian (deep bricks, kT3 x kT3 columns of
+// kDeepZ planes, k_stencil.hip).  Small bricks, kT3 x kT3 columns, where few
+// blocks are the limit (40x48x56: 420 of them).  Wide bricks, kWide x kWide columns, for
 // larger volumes: what bounds a pass there is the cache lines its halo rows
 // touch (loads and stores alone take 14 of the forward pass's 18 us on 8 x 8
 // x 8 bricks at 80x96x112, whose 14-voxel rows use 56 bytes of one or two
@@ -396,20 +398,20 @@ __device__ __forceinline__ void stencil_march(const P& pol, const Geom& g, int x
 // of its column in ascending z or, for compensated sums from radius 2 on,
 // running sums that start where kBrickZ divides z.  So it does not depend on the brick that
 // computes it.
-constexpr int kT3 = 8, kWide = 16, kBrickZ = 4;
+constexpr int kT3 = 8, kWide = 16, kBrickZ = 4, kDeepZ = 8;
 constexpr int kCubeThreads = 256, kWideThreads = 512;
 
 // The z sums of the halo columns of a brick of SIDE x SIDE columns.  The y
 // pass reads them, keeps its own (fewer) results in registers and, after a
 // barrier, writes them over the z sums, so one array serves both passes and
 // more blocks fit on a CU.
-template <int R, class P, int SIDE>
+template <int R, class P, int SIDE, int DEPTH = kBrickZ>
 struct BrickLds {
   using A = typename P::Acc;
   static constexpr int L = SIDE + 2 * R;
-  A z[P::NCH][kBrickZ][L][L];
-  __device__ __forceinline__ A (&y())[P::NCH][kBrickZ][SIDE][L] {
-    return *reinterpret_cast<A(*)[P::NCH][kBrickZ][SIDE][L]>(&z[0][0][0][0]);
+  A z[P::NCH][DEPTH][L][L];
+  __device__ __forceinline__ A (&y())[P::NCH][DEPTH][SIDE][L] {
+    return *reinterpret_cast<A(*)[P::NCH][DEPTH][SIDE][L]>(&z[0][0][0][0]);
   }
 };
 
@@ -434,16 +436,16 @@ __device__ __forceinline__ void window_outputs(const P& pol,
 }
 
 // Halo column `col` of the brick at (x0, y0, z0).
-template <int R, int SIDE, class P>
+template <int R, int SIDE, int DEPTH = kBrickZ, class P>
 __device__ __forceinline__ void brick_column(const P& pol, const Geom& g, int x0, int y0,
                                              int z0, const typename P::Local& loc, int col,
-                                             float (&r)[kBrickZ + 2 * R][P::NRAW]) {
+                                             float (&r)[DEPTH + 2 * R][P::NRAW]) {
   constexpr int L = SIDE + 2 * R;
   const int yy = col / L, xx = col - yy * L;
   const int gy = y0 - R + yy, gx = x0 - R + xx;
   const bool in = (unsigned)gy < (unsigned)g.ny && (unsigned)gx < (unsigned)g.nx;
 #pragma unroll
-  for (int k = 0; k < kBrickZ + 2 * R; ++k) {
+  for (int k = 0; k < DEPTH + 2 * R; ++k) {
     const int gz = z0 - R + k;
     const unsigned i = (in && (unsigned)gz < (unsigned)g.nz)
                            ? static_cast<unsigned>((gz * g.ny + gy) * g.nx + gx)
@@ -453,10 +455,10 @@ __device__ __forceinline__ void brick_column(const P& pol, const Geom& g, int x0
 }
 
 // Its z sums into LDS, the raw inputs expanded into the accumulated channels.
-template <int R, int SIDE, class P>
+template <int R, int SIDE, int DEPTH = kBrickZ, class P>
 __device__ __forceinline__ void brick_zsum(const P& pol,
-                                           const float (&r)[kBrickZ + 2 * R][P::NRAW], int col,
-                                           BrickLds<R, P, SIDE>& sm) {
+                                           const float (&r)[DEPTH + 2 * R][P::NRAW], int col,
+                                           BrickLds<R, P, SIDE, DEPTH>& sm) {
   using A = typename P::Acc;
   constexpr int NC = P::NCH, L = SIDE + 2 * R;
   const int yy = col / L, xx = col - yy * L;
@@ -468,14 +470,16 @@ __device__ __forceinline__ void brick_zsum(const P& pol,
     // with FP64 sums nothing)
     A a[NC];
 #pragma unroll
-    for (int c = 0; c < NC; ++c) a[c] = A();
+    for (int oz = 0; oz < DEPTH; ++oz) {
+      if (oz % kBrickZ == 0) {
 #pragma unroll
-    for (int k = 0; k <= 2 * R; ++k) pol.accum(a, r[k], k);
+        for (int c = 0; c < NC; ++c) a[c] = A();
 #pragma unroll
-    for (int oz = 0; oz < kBrickZ; ++oz) {
+        for (int k = 0; k <= 2 * R; ++k) pol.accum(a, r[oz + k], k);
+      }
 #pragma unroll
       for (int c = 0; c < NC; ++c) sm.z[c][oz][yy][xx] = a[c];
-      if (oz + 1 < kBrickZ) {
+      if ((oz + 1) % kBrickZ != 0) {
         A enter[NC], leave[NC];
 #pragma unroll
         for (int c = 0; c < NC; ++c) enter[c] = leave[c] = A();
@@ -488,7 +492,7 @@ __device__ __forceinline__ void brick_zsum(const P& pol,
     return;
   }
 #pragma unroll
-  for (int oz = 0; oz < kBrickZ; ++oz) {
+  for (int oz = 0; oz < DEPTH; ++oz) {
     A a[NC];
 #pragma unroll
     for (int c = 0; c < NC; ++c) a[c] = A();
@@ -500,10 +504,10 @@ __device__ __forceinline__ void brick_zsum(const P& pol,
 }
 
 // The y pass of a brick by NT threads, KY outputs per item.
-template <int R, int SIDE, int NT, int KY, class P>
-__device__ __forceinline__ void brick_ypass(const P& pol, BrickLds<R, P, SIDE>& sm) {
+template <int R, int SIDE, int NT, int KY, int DEPTH, class P>
+__device__ __forceinline__ void brick_ypass(const P& pol, BrickLds<R, P, SIDE, DEPTH>& sm) {
   using A = typename P::Acc;
-  constexpr int NC = P::NCH, L = SIDE + 2 * R, NY = kBrickZ * (SIDE / KY) * L,
+  constexpr int NC = P::NCH, L = SIDE + 2 * R, NY = DEPTH * (SIDE / KY) * L,
                 PY = (NY + NT - 1) / NT;
   A ay[PY][NC][KY];
 #pragma unroll
@@ -537,41 +541,52 @@ __device__ __forceinline__ void brick_ypass(const P& pol, BrickLds<R, P, SIDE>& 
   }
 }
 
-// A small brick by kCubeThreads threads, one output each.
-template <int R, class P>
-__device__ __forceinline__ void stencil_cube(const P& pol, const Geom& g, int x0, int y0,
+// A small or deep brick by kCubeThreads threads, an output per kBrickZ planes
+// each.  Summing policies: loc.sum receives that of the first kBrickZ planes,
+// the return value is that of a deep brick's others.
+template <int R, int DEPTH, class P>
+__device__ __forceinline__ double stencil_cube(const P& pol, const Geom& g, int x0, int y0,
                                              int z0, typename P::Local& loc,
-                                             BrickLds<R, P, kT3>& sm) {
+                                             BrickLds<R, P, kT3, DEPTH>& sm) {
   using A = typename P::Acc;
   constexpr int NC = P::NCH, L = kT3 + 2 * R, NT = kCubeThreads;
-  static_assert(kBrickZ * kT3 * kT3 == NT, "one output per thread");
+  static_assert(kBrickZ * kT3 * kT3 == NT, "one output per thread and kBrickZ planes");
   for (int col = threadIdx.x; col < L * L; col += NT) {
-    float r[kBrickZ + 2 * R][P::NRAW];
-    brick_column<R, kT3>(pol, g, x0, y0, z0, loc, col, r);
-    brick_zsum<R, kT3>(pol, r, col, sm);
+    float r[DEPTH + 2 * R][P::NRAW];
+    brick_column<R, kT3, DEPTH>(pol, g, x0, y0, z0, loc, col, r);
+    brick_zsum<R, kT3, DEPTH>(pol, r, col, sm);
   }
   __syncthreads();
   brick_ypass<R, kT3, NT, 1>(pol, sm);
   __syncthreads();
   auto& sy = sm.y();
-  const int oz = threadIdx.x / (kT3 * kT3), oy = (threadIdx.x / kT3) % kT3,
-            ox = threadIdx.x % kT3;
-  A a[NC];
+  const int oy = (threadIdx.x / kT3) % kT3, ox = threadIdx.x % kT3;
+  const int gx = x0 + ox, gy = y0 + oy;
+  double first = 0.0, others = 0.0;
 #pragma unroll
-  for (int c = 0; c < NC; ++c) {
-    A v[1 + 2 * R], o[1];
+  for (int j = 0; j < DEPTH; j += kBrickZ) {
+    const int oz = threadIdx.x / (kT3 * kT3) + j, gz = z0 + oz;
+    A a[NC];
 #pragma unroll
-    for (int k = 0; k <= 2 * R; ++k) v[k] = sy[c][oz][oy][ox + k];
-    window_outputs<R, 1>(pol, v, o);
-    a[c] = o[0];
+    for (int c = 0; c < NC; ++c) {
+      A v[1 + 2 * R], o[1];
+#pragma unroll
+      for (int k = 0; k <= 2 * R; ++k) v[k] = sy[c][oz][oy][ox + k];
+      window_outputs<R, 1>(pol, v, o);
+      a[c] = o[0];
+    }
+    if (gx < g.nx && gy < g.ny && gz < g.nz) {
+      const int i = (gz * g.ny + gy) * g.nx + gx;
+      typename P::Pre q;
+      pol.pre(i, q);
+      pol.emit(loc, i, q, a);
+    }
+    if constexpr (P::kSum && DEPTH > kBrickZ) {
+      (j == 0 ? first : others) = loc.sum;
+      loc.sum = j == 0 ? 0.0 : first;
+    }
   }
-  const int gx = x0 + ox, gy = y0 + oy, gz = z0 + oz;
-  if (gx < g.nx && gy < g.ny && gz < g.nz) {
-    const int i = (gz * g.ny + gy) * g.nx + gx;
-    typename P::Pre q;
-    pol.pre(i, q);
-    pol.emit(loc, i, q, a);
-  }
+  return others;
 }
 
 // ---- wide bricks: kWideThreads threads, two outputs adjacent in x each
@@ -689,12 +704,12 @@ __device__ __forceinline__ void stencil_wide(const P& pol, const Geom& g, int x0
 }
 
 // Origin of brick b of a volume (x fastest, then y, then z).
-template <int SIDE>
+template <int SIDE, int DEPTH = kBrickZ>
 __device__ __forceinline__ void brick_origin(const Geom& g, int b, int& x0, int& y0, int& z0) {
   const int cx = (g.nx + SIDE - 1) / SIDE, cy = (g.ny + SIDE - 1) / SIDE;
   x0 = (b % cx) * SIDE;
   y0 = ((b / cx) % cy) * SIDE;
-  z0 = (b / (cx * cy)) * kBrickZ;
+  z0 = (b / (cx * cy)) * DEPTH;
 }
 
 // Block sum of one double per thread; thread 0 writes it to *out.
