@@ -241,7 +241,7 @@ __device__ __forceinline__ void stencil_item(const Pol& pol, const BatchPair& P,
     }
   } else {
     tile_origin(P.t, local, kTY, x0, y0, z0);
-    stencil_tile<R, kTY>(pol, P.g, x0, y0, z0, min(z0 + P.t.cz, P.g.nz), loc, lm);
+    stencil_tile<R, kTY, FORM != 2>(pol, P.g, x0, y0, z0, min(z0 + P.t.cz, P.g.nz), loc, lm);
   }
 }
 

@@ -275,7 +275,7 @@ struct March {
 };
 
 // One step of stencil_tile: plane zi, in ring slot S.
-template <int S, int R, int TY, class P>
+template <int S, bool FENCE, int R, int TY, class P>
 __device__ __forceinline__ void tile_step(March<R, TY, P>& m, int zi, typename P::Local& loc,
                                           StencilLds<R, TY, P>& sm) {
   // with FP64 sums the operands of this step's output are requested before the
@@ -287,8 +287,10 @@ __device__ __forceinline__ void tile_step(March<R, TY, P>& m, int zi, typename P
   // and their windows from radius 3 on are fenced (stencil_march), which keeps
   // the backward pass at 117 registers and four waves per SIMD (left alone 164
   // and three; attempt at 160x72x160, window 7: 100.3 -> 94.9 us); compensated
-  // sums are a percent faster without
-  constexpr bool kFenced = P::kBox && kEarly && R >= 3;
+  // sums are a percent faster without.  (FENCE: not in the persistent kernel
+  // that also runs bricks: 166 registers for 213 let a third of its blocks onto
+  // a CU, and its grid barriers wait for all of them: 32^3, 60 -> 75 us.)
+  constexpr bool kFenced = FENCE && P::kBox && kEarly && R >= 3;
   m.commit(sm);
   const unsigned io = m.out_index(zi - R);
   typename P::Pre q;
@@ -317,7 +319,7 @@ __device__ __forceinline__ bool each_slot(F&& f) {
 // The stencil over a tile, two barriers per plane, in the LDS `sm` (the
 // batched kernels, whose phases overlay their LDS and fill the GPU with blocks
 // of one size).
-template <int R, int TY, class P>
+template <int R, int TY, bool FENCE = true, class P>
 __device__ __forceinline__ void stencil_tile(const P& pol, const Geom& g, int x0, int y0,
                                              int z0, int z1, typename P::Local& loc,
                                              StencilLds<R, TY, P>& sm) {
@@ -325,7 +327,7 @@ __device__ __forceinline__ void stencil_tile(const P& pol, const Geom& g, int x0
   int zi = z0 - R;
   m.fetch(loc, zi);
   while (!each_slot<0, 2 * R + 1>([&](auto s) {
-    tile_step<decltype(s)::value>(m, zi, loc, sm);
+    tile_step<decltype(s)::value, FENCE>(m, zi, loc, sm);
     return ++zi == m.zend;
   })) {
   }

@@ -26,7 +26,7 @@ static void __syncthreads() { putchar('|'); }
 template <int S> void brick_origin(const Geom&, int, int&, int&, int&) {}
 void tile_origin(const Tiling&, int, int, int& x, int& y, int& z) { x = y = z = 0; }
 template <int R, class... A> void stencil_cube(A&&...) { putchar('b'); }
-template <int R, int TY, class... A> void stencil_tile(A&&...) { putchar('t'); }
+template <int R, int TY, bool FENCE = true, class... A> void stencil_tile(A&&...) { putchar('t'); }
 %s
 int main(int, char** argv) {
   int lm = 0, lb = 0;
