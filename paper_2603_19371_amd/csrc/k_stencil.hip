@@ -206,10 +206,10 @@ long long set_chunks(Tiling& t, const Geom& g, int R) {
 }  // namespace
 
 // Two tiles per block read a plane's halo rows once for both and have half the
-// barriers, so a tile's plane costs them about nine tenths of what it costs a
-// block of one; but an odd row of tiles leaves half of a block idle, and the
-// blocks are the coarser load for the CUs.  So they are taken where the fullest
-// CU has at most 10/9 of the planes then (attempt, window 7: 160x72x160, 56
+// barriers, so a tile's plane costs them some 3 R percent less than a block of
+// one; but an odd row of tiles leaves half of a block idle, and the blocks are
+// the coarser load for the CUs.  So they are taken where the fullest CU has at
+// most that share of planes more then (attempt, window 7: 160x72x160, 56
 // planes either way: one tile 94.9 us, two 91.3; 300x24x300, 60 and 72: 90.2,
 // 95.6; 512x8x512, 56 and 88: 84.8, 104.1; 130x70x130, 45 and 60: 81.5, 84.4;
 // window 5, 256x40x256, 60 and 68: 93.8, 96.0).  The tiling does not depend on
@@ -220,7 +220,7 @@ Tiling march_tiling(const Geom& g, int R) {
   Tiling one = make_tiling(g.nz, g.ny, g.nx, kTY), two = one;
   two.pairs = 1;
   const long long c1 = set_chunks(one, g, R), c2 = set_chunks(two, g, R);
-  return 9 * c2 <= 10 * c1 ? two : one;
+  return 100 * c2 <= (100 + 3 * R) * c1 ? two : one;
 }
 
 namespace {
