@@ -233,8 +233,12 @@ static_assert(kTX * kTY == kCubeThreads, "marching tiles and cubes share FwdPol<
 // (the half- and quarter-resolution levels of a brain-sized pair).
 constexpr long long kCubeMaxVoxels = 1LL << 20;
 
+// Asked for bricks, a volume marches all the same where they would be more than
+// a launch holds (2^32 threads; a slab one voxel thick of half a billion).
+constexpr long long kMaxBricks = (1LL << 32) / kWideThreads;
+
 bool use_cubes(const Geom& g, const lmr_params& p) {
-  return p.stencil == LMR_STENCIL_CUBE ||
+  return (p.stencil == LMR_STENCIL_CUBE && bricks_of(g, kT3, kBrickZ) < kMaxBricks) ||
          (p.stencil == LMR_STENCIL_AUTO && g.N <= kCubeMaxVoxels);
 }
 

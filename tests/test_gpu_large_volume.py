@@ -63,3 +63,22 @@ def test_last_planes_match_a_volume_of_their_own():
     u.zero_()
     u[:, -TAIL:] = us
     same(ctx.update(u, u, 0.5, 0.1), ref.update(us, us, 0.5, 0.1), 0.0, "pooled update")
+
+
+def test_more_bricks_than_a_launch_holds():
+    """65535 x 1 x 8192 has 16.8 million small bricks, 8.4 million wide ones of
+    512 threads: asked for bricks, it marches."""
+    import torch
+    from paper_2603_19371_amd import _lib as L
+    shape = (65535, 1, 8192)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(2)
+    F = torch.rand(shape, generator=g, device="cuda", dtype=torch.bfloat16)
+    u = torch.zeros((3,) + shape, device="cuda")
+    got = []
+    for form in (L.LMR_STENCIL_CUBE, L.LMR_STENCIL_MARCH):
+        ctx = L.Context(shape, img_dtype=torch.bfloat16, window=7, stencil=form)
+        got.append(ctx.loss_grad(F, F, u, smooth=False))
+        ctx.close()
+    assert got[0][0] == got[1][0]
+    assert torch.equal(got[0][1], got[1][1])
