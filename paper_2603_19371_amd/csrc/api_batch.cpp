@@ -57,8 +57,8 @@ void drop_graphs(lmr_batch* b) {
 // Rebuild the work lists for the current tiling knobs and upload the table.
 lmr_status layout(lmr_batch* b) {
   int vox = 0, tiles = 0, wide = 0;
-  const int want = std::max(1, std::min(kBatchUpdateItems,
-                                        kBatchUpdateTotal * b->cus / b->npairs));
+  long long all = 0;
+  for (const BatchPair& P : b->host) all += P.g.N;
   const int ty = batch_tile_rows();
   for (int i = 0; i < b->npairs; ++i) {
     BatchPair& P = b->host[i];
@@ -67,6 +67,8 @@ lmr_status layout(lmr_batch* b) {
               : march_tiling(P.g, b->p.window / 2);
     const int ucols = ((P.g.nx + kBatchUpdateTX - 1) / kBatchUpdateTX) *
                       ((P.g.ny + kBatchUpdateTY - 1) / kBatchUpdateTY);
+    const long long want = std::max(
+        1LL, std::min<long long>(kBatchUpdateItems, kBatchUpdateTotal * b->cus * P.g.N / all));
     P.ucz = static_cast<int>(((long long)P.g.nz * ucols + want - 1) / want);
     P.ucz = std::min(std::max(P.ucz, kBatchUpdateMinCz), kBatchUpdateMaxCz);
     P.ntiles = P.bricks ? bricks_of(P.g, kT3, kBrickZ) : P.t.tiles();

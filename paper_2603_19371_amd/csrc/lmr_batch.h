@@ -56,10 +56,11 @@ constexpr int kBarGroups = 8;
 // update work item: a 32 x 8 column (the staged update's tile) over ucz
 // planes: about kBatchUpdateItems items per pair, 2..32 planes each (long
 // marches for large pairs, short ones where a pair has few columns), but no
-// more than kBatchUpdateTotal per compute unit over all pairs: an item stages
-// two planes more than it updates, one after another before its first step
-// (32 pairs of 48^3, update phase: 4 per unit 104 us, 8: 87, 16: 87; without
-// the limit, 32 per unit there, 93)
+// more than kBatchUpdateTotal per compute unit over all pairs, shared out by
+// voxels: an item stages two planes more than it updates, one after another
+// before its first step (32 pairs of 48^3, update phase: 4 per unit 104 us, 8:
+// 87, 16: 87; without the limit, 32 per unit there, 93; attempts of 48 batches
+// of 1 to 128 pairs: 8 within 2 % of the best of 2, 4, 8, 16 and no limit)
 constexpr int kBatchUpdateTX = 32, kBatchUpdateTY = 8, kBatchUpdateItems = 256;
 constexpr int kBatchUpdateTotal = 8;
 constexpr int kBatchUpdateMinCz = 2, kBatchUpdateMaxCz = 32;
