@@ -89,8 +89,10 @@ __global__ void __launch_bounds__(kNT) k_bp_smooth(const BatchPair* __restrict__
 // And of the pairs on bricks, one brick per block: wide ones (32 pairs of
 // about 48^3 on small bricks, then wide ones: forward 82 -> 68 us, backward of
 // accepted pairs 125 -> 95, smoothing 68 -> 50), but small ones where all
-// pairs together have fewer than kWideItems wide ones (attempt of one pair of
-// 30^3, 32 wide bricks: small 22 us, wide 25; of four: 30, 29).
+// pairs together have fewer than kWideItems wide ones (attempts: with 24 to 90
+// wide ones small 11 to 19 % faster; 96 to 192, nine batches, either up to 7 %;
+// from 300 on wide 5 to 27 % faster but for pairs that pad them, 64 of 16x20x24:
+// 70 us, small 63, and for one pair of 64x64x72, 320 of them: 53, 49).
 constexpr int kWideItems = 96;
 
 template <int R, bool WIDE, class Pol>

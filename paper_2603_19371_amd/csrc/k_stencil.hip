@@ -1,7 +1,8 @@
 // Per-pair launches of the three stencils of an LM attempt (stencil.h):
 // LNCC forward (P2), LNCC + warp backward (P4) and Gaussian smoothing (P5).
-// One block per pair of tiles or brick; block ids are remapped so that each XCD receives a
-// contiguous range of tiles and shares their halos in its L2.
+// A block per brick, or per one or two tiles of the march; block ids are
+// remapped so that each XCD receives a contiguous range of tiles and shares
+// their halos in its L2.
 #include <algorithm>
 
 #include "decide.h"

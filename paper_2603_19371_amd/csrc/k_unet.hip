@@ -152,8 +152,8 @@ __global__ void __launch_bounds__(256) k_conv(ConvArgs a) {
 // a wave holds the (RW + 2) x 3 input operands of a tap plane in registers: a
 // halo row serves the y taps of up to three output rows, 18 reads where 36
 // would be made at RW = 4.  Forward pass at 80x96x112 per layer: 16 -> 16
-// channels at full resolution 39 -> 28 us, 48 -> 16 88 -> 61, 96 -> 32 at half
-// 41 -> 31, 192 -> 64 at a quarter 45 -> 24, 128 -> 128 at an eighth 29 -> 15
+// channels at full resolution 39 -> 26 us, 48 -> 16 88 -> 55, 96 -> 32 at half
+// 41 -> 31, 192 -> 64 at a quarter 45 -> 25, 128 -> 128 at an eighth 29 -> 17
 // us.  Each output is the same sequence of products for every tile shape:
 // chunks, tap planes and tap pairs in order.
 //
@@ -171,7 +171,7 @@ __global__ void __launch_bounds__(256) k_conv(ConvArgs a) {
 //
 // V16: the input is staged in 16-byte items (channel stride, offset and
 // count multiples of 8); otherwise in 8-byte quads, those past cin_valid
-// written as zeros without a read (the 2-channel input: 36 -> 25 us).
+// written as zeros without a read (the 2-channel input: 36 -> 23 us).
 // MFMAs keep the order in which they are written; anything else may move.  A
 // 16x16x16 and a 16x16x32 product in a row on one accumulator, either way
 // round, need five wait states that the compiler does not insert: the second

@@ -316,9 +316,10 @@ __device__ __forceinline__ bool each_slot(F&& f) {
   }
 }
 
-// The stencil over a tile, two barriers per plane, in the LDS `sm` (the
-// batched kernels, whose phases overlay their LDS and fill the GPU with blocks
-// of one size).
+// The stencil over a tile, two barriers per plane, in the LDS `sm`: where a
+// stand-alone context's blocks run one tile (march_tiling), and in the batch.
+// (The persistent kernel's phases overlay their LDS; those of one launch per
+// phase have their own and could run stencil_march.)
 template <int R, int TY, bool FENCE = true, class P>
 __device__ __forceinline__ void stencil_tile(const P& pol, const Geom& g, int x0, int y0,
                                              int z0, int z1, typename P::Local& loc,
@@ -387,9 +388,9 @@ __device__ __forceinline__ void stencil_march(const P& pol, const Geom& g, int x
 // along z; then the block reduces along y and along x in LDS and emits.  Three
 // steps instead of a march.
 //
-// Two sizes, and a third for the Gaussian (deep bricks, kT3 x kT3 columns of
-// kDeepZ planes, k_stencil.hip).  Small bricks, kT3 x kT3 columns, where few
-// blocks are the limit (40x48x56: 420 of them).  Wide bricks, kWide x kWide columns, for
+// Three sizes (fastest_brick in k_stencil.hip).  Small bricks, kT3 x kT3
+// columns, where few blocks are the limit (40x48x56: 420 of them); deep bricks,
+// the same columns of kDeepZ planes; and wide bricks, kWide x kWide columns, for
 // larger volumes: what bounds a pass there is the cache lines its halo rows
 // touch (loads and stores alone take 14 of the forward pass's 18 us on 8 x 8
 // x 8 bricks at 80x96x112, whose 14-voxel rows use 56 bytes of one or two
