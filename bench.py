@@ -24,7 +24,9 @@ Printed on one JSON line, with
                 traffic = HBM bytes per attempt from the committed rocprofv3
                 counter summaries when they were taken on the current kernel
                 sources; per_kernel gives each kernel's own figure against the
-                bytes its design reads and writes;
+                bytes its design reads and writes, of the two passes after the
+                decision, which a rejected attempt skips, against the counted
+                bytes;
   cpu_baseline  the FP64 oracle on the host's cores on a bounded sample of the
                 same workload (attempts at the full-resolution level, at the
                 host's thread count and at one thread; the whole 50-attempt run
@@ -97,6 +99,24 @@ def kernel_bytes(s):
 
 # Whole attempt (what the method itself must move): read F, M, u, write u~,
 # persist the smoothed gradient between attempts (write + read).
+def kernel_rates(kb, timed, moved, nfine):
+    """Each kernel's rate over its mean time.  The passes after the decision
+    return at once on a rejected attempt, so their mean goes with the counted
+    bytes, a mean over the same attempts, and not with the design's."""
+    out = {}
+    for k, v in timed.items():
+        e = {"design_bytes_per_voxel": kb[k], "mean_ms": round(v["avg_ms"], 5),
+             "launches": v["count"]}
+        b = moved.get(k) if k in ("lncc_bwd", "smooth") else kb[k] * nfine
+        if b:
+            gbs = b / (v["avg_ms"] * 1e-3) / 1e9
+            e.update({"achieved": round(gbs, 1), "frac": round(gbs / HBM_PEAK_GBS, 4)})
+        if moved.get(k) is not None:
+            e["traffic"] = moved[k]
+        out[k] = e
+    return out
+
+
 def attempt_bytes(s):
     return 2 * s + 12 + 12 + 24
 
@@ -267,16 +287,7 @@ def _pyramid_line(a, F, M, img_dtype, factors, iters, workload, s):
     complete = all(v is not None for v in moved.values())
     ab = attempt_bytes(s) * nfine
     achieved = ab / (attempt_ms * 1e-3) / 1e9
-    per_kernel = {}
-    for k, v in timed.items():
-        e = {"design_bytes_per_voxel": kb[k], "mean_ms": round(v["avg_ms"], 5),
-             "launches": v["count"]}
-        if kb[k]:
-            gbs = kb[k] * nfine / (v["avg_ms"] * 1e-3) / 1e9
-            e.update({"achieved": round(gbs, 1), "frac": round(gbs / HBM_PEAK_GBS, 4)})
-        if moved.get(k) is not None:
-            e["traffic"] = moved[k]
-        per_kernel[k] = e
+    per_kernel = kernel_rates(kb, timed, moved, nfine)
     roofline = {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS,
                 "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4),
                 "traffic": sum(moved.values()) if complete else None,
