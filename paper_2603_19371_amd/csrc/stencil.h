@@ -459,7 +459,8 @@ __device__ __forceinline__ void brick_column(const P& pol, const Geom& g, int x0
 
 // Its z sums into LDS, the raw inputs expanded into the accumulated channels.
 template <int R, int SIDE, int DEPTH = kBrickZ, class P>
-__device__ __forceinline__ void brick_zsum(const P& pol,
+__device__ __forceinline__ void brick_zsum(const P& pol, const Geom& g, int x0, int y0, int z0,
+                                           const typename P::Local& loc,
                                            const float (&r)[DEPTH + 2 * R][P::NRAW], int col,
                                            BrickLds<R, P, SIDE, DEPTH>& sm) {
   using A = typename P::Acc;
@@ -497,17 +498,37 @@ __device__ __forceinline__ void brick_zsum(const P& pol,
         for (int c = 0; c < NC; ++c) a[c] += enter[c] - leave[c];
         write(oz, a);
       }
-      // a term that is not finite does not leave a sum again: every sum by itself
-      // (the check: 0.2 % of an attempt, 100 shapes)
+      // a term that is not finite does not leave a sum again: there every sum by
+      // itself, its terms loaded again (kept in r they take 20 registers and a
+      // third of a CU's wide bricks: attempts of 24 batches 2 % slower, 16 of
+      // 64x64x60 287 us, 300; loaded again, no slower)
       bool lost = false;
 #pragma unroll
       for (int c = 0; c < NC; ++c) lost |= a[c].lo != a[c].lo;
-      if (!lost) continue;
-    }
+      if (lost) {
+#pragma unroll 1
+        for (int oz = z + 1; oz < z + kBrickZ; ++oz) {
 #pragma unroll
-    for (int oz = z + 1; oz < z + kBrickZ; ++oz) {
-      sum(oz, a);
-      write(oz, a);
+          for (int c = 0; c < NC; ++c) a[c] = A();
+#pragma unroll 1
+          for (int k = oz; k <= oz + 2 * R; ++k) {
+            const int gx = x0 - R + xx, gy = y0 - R + yy, gz = z0 - R + k;
+            float v[P::NRAW];
+            if ((unsigned)gx < (unsigned)g.nx && (unsigned)gy < (unsigned)g.ny &&
+                (unsigned)gz < (unsigned)g.nz) {
+              pol.load(loc, (gz * g.ny + gy) * g.nx + gx, v);
+              pol.accum(a, v, 0);
+            }
+          }
+          write(oz, a);
+        }
+      }
+    } else {
+#pragma unroll
+      for (int oz = z + 1; oz < z + kBrickZ; ++oz) {
+        sum(oz, a);
+        write(oz, a);
+      }
     }
   }
 }
@@ -563,7 +584,7 @@ __device__ __forceinline__ double stencil_cube(const P& pol, const Geom& g, int 
   for (int col = threadIdx.x; col < L * L; col += NT) {
     float r[DEPTH + 2 * R][P::NRAW];
     brick_column<R, kT3, DEPTH>(pol, g, x0, y0, z0, loc, col, r);
-    brick_zsum<R, kT3, DEPTH>(pol, r, col, sm);
+    brick_zsum<R, kT3, DEPTH>(pol, g, x0, y0, z0, loc, r, col, sm);
   }
   __syncthreads();
   brick_ypass<R, kT3, NT, 1>(pol, sm);
@@ -631,11 +652,12 @@ __device__ __forceinline__ void wide_passes(const P& pol, const Geom& g, int x0,
                                             BrickLds<R, P, kWide>& sm, double (&cc)[2]) {
   using A = typename P::Acc;
   constexpr int NC = P::NCH, L = kWide + 2 * R, NT = kWideThreads;
-  if (L * L >= NT || threadIdx.x < L * L) brick_zsum<R, kWide>(pol, f.r, threadIdx.x, sm);
+  if (L * L >= NT || threadIdx.x < L * L)
+    brick_zsum<R, kWide>(pol, g, x0, y0, z0, loc, f.r, threadIdx.x, sm);
   for (int col = threadIdx.x + NT; col < L * L; col += NT) {  // R > 3
     float r[kBrickZ + 2 * R][P::NRAW];
     brick_column<R, kWide>(pol, g, x0, y0, z0, loc, col, r);
-    brick_zsum<R, kWide>(pol, r, col, sm);
+    brick_zsum<R, kWide>(pol, g, x0, y0, z0, loc, r, col, sm);
   }
   __syncthreads();
   brick_ypass<R, kWide, NT, 4>(pol, sm);
